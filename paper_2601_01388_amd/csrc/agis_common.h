@@ -147,7 +147,8 @@ struct DevTables {
     AGIS_GMEM const int32_t* hub_slot;
     uint64_t hub_words;  // 32-bit words per bitmap row
     // common-neighbour counts of the "pair hubs" (the highest-degree hubs):
-    // pair_count[pair_slot[a] * pairs + pair_slot[b]] = |N(a) cap N(b)|
+    // pair_count[pair_slot[a] * pairs + pair_slot[b]] = |N(a) cap N(b)| for
+    // pair_slot[a] > pair_slot[b], the rank by (degree, id), largest first
     // (pair_slot < 0: not a pair hub; pairs = 0: no table)
     AGIS_GMEM const int32_t* pair_slot;
     AGIS_GMEM const uint32_t* pair_count;

@@ -135,14 +135,14 @@ hipError_t launch_build_tables(const DevGraph& g, const DevGraph& adj, uint4* re
 hipError_t launch_degree_histogram(const DevGraph& g, uint32_t* hist, hipStream_t stream);
 hipError_t launch_hub_slots(agis_ctx* ctx, const DevGraph& g, uint32_t min_deg, uint32_t* flags, int32_t* hub_slot,
                             uint64_t* d_count);
-// pair_count[a * H + b] = |N(u_a) cap N(u_b)| for the H vertices with
-// pair_slot >= 0 (all of them hubs with bitmaps); the diagonal is 0.
+// Ranks the H vertices with pair_slot >= 0 by (degree, id), largest first:
+// pair_slot becomes the rank and pair_hub[rank] the vertex.  Then, for every
+// a > b of the ranks: pair_count[a * H + b] = |N(u_a) cap N(u_b)| and
 // pair_quart[(a * H + b) * (kPairParts - 1) + j - 1] = common neighbours
-// before position j d / kPairParts of the walked list (the shorter of the
-// two by (degree, id)).
-hipError_t launch_pair_counts(agis_ctx* ctx, const DevGraph& g, const int32_t* hub_slot, const uint32_t* hub_bits,
-                              uint64_t hub_words, const int32_t* pair_slot, uint64_t H, uint32_t* pair_hub,
-                              uint32_t* pair_count, uint32_t* pair_quart);
+// before position j d / kPairParts of u_a's list (the shorter of the two).
+// Entries with a <= b are not written.  Synchronises the stream.
+hipError_t launch_pair_counts(agis_ctx* ctx, const DevGraph& g, uint32_t max_deg, int32_t* pair_slot, uint64_t H,
+                              uint32_t* pair_hub, uint32_t* pair_count, uint32_t* pair_quart);
 hipError_t launch_hub_bits(const DevGraph& g, const int32_t* hub_slot, uint64_t words, uint32_t* bits,
                            hipStream_t stream);
 // Degree orientation: out-degrees into outdeg (n entries of scratch), the
@@ -237,9 +237,6 @@ struct SampleLaunch {
 // The sampling kernel for (record-writing?, register-budget variant 0..2,
 // pair-hub paths?).
 const void* sample_kernel(bool dump, int variant, bool pairs, bool meter);
-// Degrees of the pair hubs (deg[i] of pair_hub[i]).
-hipError_t launch_pair_hub_degrees(agis_ctx* ctx, const DevGraph& g, const uint32_t* pair_hub, uint64_t H,
-                                   uint32_t* deg);
 // Core-pair lists: core_slot[core_vertex[c]] = c, and for every pair a < b
 // of core slots the common neighbours of the two vertices, ascending, at
 // core_nbr + core_start[a * C + b] (walking the shorter list and probing the

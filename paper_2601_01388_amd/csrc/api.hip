@@ -305,22 +305,12 @@ constexpr uint64_t kCoreMax = 4096;
 hipError_t build_core_pairs(agis_ctx* ctx, const agis_graph* g, agis_tables* t, const uint32_t* pair_hub,
                             uint64_t H) {
     const uint64_t n = g->g.n;
-    std::vector<uint32_t> hub(H), deg(H), cnt(H * H);
-    uint32_t* d_deg = nullptr;
-    hipError_t e = hipMalloc(&d_deg, H * sizeof(uint32_t));
-    if (e == hipSuccess) e = agis::launch_pair_hub_degrees(ctx, g->g, pair_hub, H, d_deg);
-    if (e == hipSuccess) e = hipMemcpyAsync(deg.data(), d_deg, H * sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(hub.data(), pair_hub, H * sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream);
+    std::vector<uint32_t> hub(H), cnt(H * H);
+    hipError_t e = hipMemcpyAsync(hub.data(), pair_hub, H * sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(cnt.data(), t->pair_count, H * H * sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    if (d_deg) (void)hipFree(d_deg);
     if (e != hipSuccess) return e;
-    std::vector<uint32_t> order(H);
-    for (uint32_t i = 0; i < H; ++i) order[i] = i;
-    std::sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) {
-        return deg[a] != deg[b] ? deg[a] > deg[b] : hub[a] < hub[b];
-    });
     uint64_t budget = kCorePairBudget;
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) == hipSuccess) budget = std::min<uint64_t>(budget, (uint64_t)free_b / 8);
@@ -331,7 +321,7 @@ hipError_t build_core_pairs(agis_ctx* ctx, const agis_graph* g, agis_tables* t, 
     uint64_t total = 0, C = 0;
     for (uint64_t c = 0; c < std::min<uint64_t>(H, kCoreMax); ++c) {
         uint64_t add = 0;
-        for (uint64_t j = 0; j < c; ++j) add += padded(cnt[(uint64_t)order[c] * H + order[j]]);
+        for (uint64_t j = 0; j < c; ++j) add += padded(cnt[c * H + j]);
         const uint64_t index_bytes = (c + 1) * (c + 1) * (sizeof(uint64_t) + sizeof(uint32_t));
         if ((total + add) * sizeof(uint32_t) + index_bytes > budget || total + add > cap) break;
         total += add;
@@ -340,11 +330,11 @@ hipError_t build_core_pairs(agis_ctx* ctx, const agis_graph* g, agis_tables* t, 
     if (C < 2) return hipSuccess;
     std::vector<uint32_t> vert(C), len(C * C, 0u);
     std::vector<uint64_t> start(C * C, 0ull);
-    for (uint64_t c = 0; c < C; ++c) vert[c] = hub[order[c]];
+    for (uint64_t c = 0; c < C; ++c) vert[c] = hub[c];
     uint64_t run = 0;
     for (uint64_t a = 0; a < C; ++a)
         for (uint64_t b = a + 1; b < C; ++b) {
-            const uint32_t l = cnt[(uint64_t)order[a] * H + order[b]];
+            const uint32_t l = cnt[b * H + a];
             start[a * C + b] = start[b * C + a] = run;
             len[a * C + b] = len[b * C + a] = l;
             run += padded(l);
@@ -474,6 +464,9 @@ hipError_t build_hub_bitmaps(agis_ctx* ctx, const agis_graph* g, agis_tables* t)
         e = hipMalloc(&pair_hub, H * sizeof(uint32_t));
         if (e == hipSuccess) e = hipMalloc(&t->pair_count, H * H * sizeof(uint32_t));
         if (e == hipSuccess) e = hipMalloc(&t->pair_quart, H * H * (agis::kPairParts - 1) * sizeof(uint32_t));
+        if (e == hipSuccess)
+            e = agis::launch_pair_counts(ctx, g->g, g->max_deg, t->pair_slot, H, pair_hub, t->pair_count,
+                                         t->pair_quart);
         if (e == hipErrorOutOfMemory) {
             // no room for the pair-hub table: keep the bitmaps without it
             (void)hipGetLastError();
@@ -483,10 +476,7 @@ hipError_t build_hub_bitmaps(agis_ctx* ctx, const agis_graph* g, agis_tables* t)
             t->pair_quart = nullptr;
             H = 0;
             e = hipSuccess;
-        } else if (e == hipSuccess)
-            e = agis::launch_pair_counts(ctx, g->g, t->hub_slot, t->hub_bits, words, t->pair_slot, H, pair_hub,
-                                         t->pair_count, t->pair_quart);
-        if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+        }
         if (e == hipSuccess) {
             t->pairs = H;
             t->pair_min_degree = 1u << pb;

@@ -1024,84 +1024,211 @@ hipError_t launch_hub_bits(const DevGraph& g, const int32_t* hub_slot, uint64_t 
     return hipGetLastError();
 }
 
-// Pair hubs in slot order, then one wave per pair (a, b), a < b: the
-// shorter of the two lists is walked and each element probed in the other
-// vertex's bitmap (every pair hub has one); both orders of the pair get
-// the count, the diagonal 0.
-__global__ void k_pair_hubs(const int32_t* __restrict__ pair_slot, uint64_t n, uint32_t* __restrict__ pair_hub) {
+// Pair hubs: listed in id order first, then ranked by (degree, id), largest
+// first; the rank is the vertex's pair slot.  Of two pair hubs the one with
+// the larger slot has the smaller (degree, id), so it is the one whose list
+// is walked, and the tables are kept for (larger slot, smaller slot) only.
+__global__ void k_pair_hubs(const int32_t* __restrict__ pair_slot, uint64_t n, uint32_t* __restrict__ hub) {
     const uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v < n && pair_slot[v] >= 0) pair_hub[pair_slot[v]] = (uint32_t)v;
+    if (v < n && pair_slot[v] >= 0) hub[pair_slot[v]] = (uint32_t)v;
 }
 
-__global__ __launch_bounds__(256) void k_pair_counts(DevGraph g, const int32_t* __restrict__ hub_slot,
-                                                      const uint32_t* __restrict__ hub_bits, uint64_t hub_words,
-                                                      const uint32_t* __restrict__ pair_hub, uint64_t H,
-                                                      uint32_t* __restrict__ pair_count,
-                                                      uint32_t* __restrict__ pair_quart) {
+__global__ __launch_bounds__(256) void k_pair_rank(DevGraph g, const uint32_t* __restrict__ hub, uint64_t H,
+                                                   uint32_t* __restrict__ pair_hub, int32_t* __restrict__ pair_slot) {
+    __shared__ uint64_t keys[256];
+    const uint64_t i = (uint64_t)blockIdx.x * 256u + threadIdx.x;
+    auto key_of = [&](uint64_t h) -> uint64_t {
+        const uint32_t v = hub[h];
+        return ((g.off[v + 1] - g.off[v]) << 32) | (uint64_t)v;
+    };
+    const uint64_t mine = i < H ? key_of(i) : ~0ull;
+    uint32_t above = 0;
+    for (uint64_t b = 0; b < H; b += 256u) {
+        keys[threadIdx.x] = b + threadIdx.x < H ? key_of(b + threadIdx.x) : 0ull;
+        __syncthreads();
+        for (int j = 0; j < 256; ++j) above += keys[j] > mine ? 1u : 0u;
+        __syncthreads();
+    }
+    if (i < H) {
+        pair_hub[above] = hub[i];
+        pair_slot[hub[i]] = (int32_t)above;
+    }
+}
+
+// Common-neighbour counts of every pair of pair hubs, with the running
+// counts at the eighths of the walked list.
+//
+// Counting by probes (one bit test per element of the shorter list of every
+// pair, 6e10 of them on R-MAT-20) is bound by the gather rate: 148 ms there.
+// Here the membership bits are transposed: a row per data vertex holds one
+// bit per hub, so one row read serves up to 2,048 pairs of an element, and
+// the ones are counted in bit planes (carry-save adders over 32 hubs a
+// word), about four vector operations for 32 pairs.  What is left is the row
+// reads, 256 bytes each and whole lines: 2.1 ms on the same graph (6,196
+// hubs; 1.0 ms counting, 0.9 ms setting the bits, 0.15 ms clearing them).
+//
+// Hubs are taken in panels of 32 lw (lw words per row, a power of two up to
+// 64): bit q / lw of word q % lw belongs to hub base + q, so that one bit of
+// all words is a run of consecutive hubs and the results are written as
+// whole lines.  A panel is counted for the lists of the hubs of larger slot
+// only: the longest lists (smallest slots) meet the fewest panels.
+constexpr uint32_t kPairRowWords = 64;
+constexpr int kPairThreads = kPairParts * kWave;
+// Scratch for the rows; narrower rows (more panels, the same row words in
+// all) where 256 bytes per vertex would pass it.
+constexpr uint64_t kPairRowsBudget = 8ull << 30;
+
+// Grid: (hubs of the panel, slices of a list).
+__global__ __launch_bounds__(256) void k_hub_rows(DevGraph g, const uint32_t* __restrict__ pair_hub, uint64_t base,
+                                                  uint32_t lw, uint32_t* __restrict__ rows) {
+    const uint32_t q = blockIdx.x;
+    const uint32_t v = pair_hub[base + q];
+    const uint64_t o = g.off[v], d = g.off[v + 1] - o;
+    const uint32_t word = q % lw, bit = 1u << (q / lw);
+    const uint64_t step = (uint64_t)gridDim.y * blockDim.x;
+    for (uint64_t e = (uint64_t)blockIdx.y * blockDim.x + threadIdx.x; e < d; e += step)
+        atomicOr(rows + (uint64_t)g.nbr[o + e] * lw + word, bit);
+}
+
+// a + b + c per bit: carry (weight 2) and sum, in that order.
+__device__ __forceinline__ void bit_add3(uint32_t& carry, uint32_t& sum, uint32_t a, uint32_t b) {
+    const uint32_t t = sum;
+    carry = (a & b) | (t & (a | b));
+    sum = t ^ a ^ b;
+}
+
+// One workgroup per walked list (hub base + 1 + blockIdx.x), one wave per
+// eighth of it.  With lw < 64 the wave's 64 / lw lane groups take elements
+// in turn and their counts are added at the end.  kPlanes bit planes count
+// up to 2^kPlanes - 1 elements of an eighth.
+template <int kPlanes>
+__global__ __launch_bounds__(kPairThreads) void k_pair_counts(DevGraph g, const uint32_t* __restrict__ rows,
+                                                              uint32_t lw, const uint32_t* __restrict__ pair_hub,
+                                                              uint64_t H, uint64_t base,
+                                                              uint32_t* __restrict__ pair_count,
+                                                              uint32_t* __restrict__ pair_quart) {
+    constexpr int kUnroll = 16;
+    __shared__ uint32_t part_cnt[2][kPairParts][kPairRowWords];
     const int lane = lane_id();
-    const uint64_t nw = (uint64_t)gridDim.x * (blockDim.x / kWave);
-    for (uint64_t pr = (uint64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave; pr < H * H; pr += nw) {
-        const uint64_t a = pr / H, b = pr % H;
-        if (a > b) continue;  // wave-uniform
-        if (a == b) {
-            if (lane == 0) {
-                pair_count[pr] = 0u;
-                for (int j = 0; j < kPairParts - 1; ++j) pair_quart[pr * (kPairParts - 1) + j] = 0u;
-            }
-            continue;
-        }
-        const uint32_t va = pair_hub[a], vb = pair_hub[b];
-        const uint64_t oa = g.off[va], ob = g.off[vb];
-        const uint64_t da = g.off[va + 1] - oa, db = g.off[vb + 1] - ob;
-        // walk the shorter list (by (degree, id)), probe the other's bitmap
-        const bool walk_a = da < db || (da == db && va < vb);
-        const uint64_t o = walk_a ? oa : ob, d = walk_a ? da : db;
-        const uint32_t* bits = hub_bits + (uint64_t)hub_slot[walk_a ? vb : va] * hub_words;
-        // members per part: part j holds positions [j d / P, (j + 1) d / P)
-        uint32_t cp[kPairParts];
+    const uint32_t part = uniform_u32(threadIdx.x / kWave);
+    const uint64_t a = base + 1 + blockIdx.x;
+    const uint64_t nb = a - base < 32ull * lw ? a - base : 32ull * lw;  // hubs of the panel below a
+    const uint32_t v = pair_hub[a];
+    const uint64_t o = g.off[v], d = g.off[v + 1] - o;
+    const uint64_t e0 = part * d / kPairParts, e1 = (part + 1) * d / kPairParts;
+    const uint32_t word = (uint32_t)lane % lw, sub = (uint32_t)lane / lw, subs = (uint32_t)kWave / lw;
+    uint32_t plane[kPlanes];
 #pragma unroll
-        for (int j = 0; j < kPairParts; ++j) cp[j] = 0u;
-        for (uint64_t e = (uint64_t)lane; e < d; e += kWave) {
-            const uint32_t x = g.nbr[o + e];
-            const uint32_t m = (bits[x >> 5] >> (x & 31u)) & 1u;
-            // the part of position e: the largest j with j d / P <= e
-            int part = (int)((e * kPairParts) / d);
-            while (part + 1 < kPairParts && (uint64_t)(part + 1) * d / kPairParts <= e) ++part;
-            while (part > 0 && (uint64_t)part * d / kPairParts > e) --part;
+    for (int p = 0; p < kPlanes; ++p) plane[p] = 0u;
+    for (uint64_t c = e0; c < e1; c += kWave) {
+        const uint32_t n = e1 - c < (uint64_t)kWave ? (uint32_t)(e1 - c) : (uint32_t)kWave;
+        const uint32_t x = (uint32_t)lane < n ? g.nbr[o + c + (uint64_t)lane] : 0u;
+        for (uint32_t s = 0; s < n; s += kUnroll * subs) {
+            uint32_t w[kUnroll];
+            if (subs == 1) {
+                // the element is wave-uniform: a scalar row address
 #pragma unroll
-            for (int j = 0; j < kPairParts; ++j) cp[j] += j == part ? m : 0u;
-        }
-        uint32_t run = 0;
-        for (int j = 0; j < kPairParts; ++j) {
-            const uint32_t sj = (uint32_t)wave_sum_u64(cp[j]);
-            if (lane == 0 && j > 0) {
-                pair_quart[(a * H + b) * (kPairParts - 1) + j - 1] = run;
-                pair_quart[(b * H + a) * (kPairParts - 1) + j - 1] = run;
+                for (int u = 0; u < kUnroll; ++u) {
+                    const uint32_t xi = readlane_u32(x, (int)s + u);
+                    w[u] = rows[(uint64_t)xi * kPairRowWords + (uint32_t)lane];
+                }
+                if (s + kUnroll > n) {
+#pragma unroll
+                    for (int u = 0; u < kUnroll; ++u) w[u] = s + (uint32_t)u < n ? w[u] : 0u;
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < kUnroll; ++u) {
+                    const uint32_t i = s + (uint32_t)u * subs + sub;
+                    const uint32_t xi = (uint32_t)__shfl((int)x, (int)(i & 63u), kWave);
+                    w[u] = i < n ? rows[(uint64_t)xi * lw + word] : 0u;
+                }
             }
-            run += sj;
+            // 16 words into the planes of weight 1, 2, 4, 8; the carry of
+            // weight 16 ripples up
+            uint32_t c2[8], c4[4], c8[2], up;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) bit_add3(c2[u], plane[0], w[2 * u], w[2 * u + 1]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) bit_add3(c4[u], plane[1], c2[2 * u], c2[2 * u + 1]);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) bit_add3(c8[u], plane[2], c4[2 * u], c4[2 * u + 1]);
+            bit_add3(up, plane[3], c8[0], c8[1]);
+#pragma unroll
+            for (int p = 4; p < kPlanes; ++p) {
+                const uint32_t t = plane[p] & up;
+                plane[p] ^= up;
+                up = t;
+            }
         }
-        if (lane == 0) {
-            pair_count[a * H + b] = run;
-            pair_count[b * H + a] = run;
+    }
+    for (uint32_t bit = 0; bit < 32u && (uint64_t)bit * lw < nb; ++bit) {
+        uint32_t cnt = 0;
+#pragma unroll
+        for (int p = 0; p < kPlanes; ++p) cnt |= ((plane[p] >> bit) & 1u) << p;
+        for (uint32_t s = lw; s < (uint32_t)kWave; s <<= 1) cnt += (uint32_t)__shfl_xor((int)cnt, (int)s, kWave);
+        uint32_t (*buf)[kPairRowWords] = part_cnt[bit & 1u];
+        if (sub == 0) buf[part][word] = cnt;
+        __syncthreads();
+        // entry r of the run, eighth j: the count before cut j + 1, and at
+        // the last eighth the total
+        const uint32_t r = threadIdx.x / kPairParts, j = threadIdx.x % kPairParts;
+        const uint64_t q = (uint64_t)bit * lw + r;
+        if (r < lw && q < nb) {
+            uint32_t run = 0;
+            for (uint32_t p = 0; p <= j; ++p) run += buf[p][r];
+            const uint64_t pr = a * H + base + q;
+            if (j + 1 < (uint32_t)kPairParts)
+                pair_quart[pr * (kPairParts - 1) + j] = run;
+            else
+                pair_count[pr] = run;
         }
     }
 }
 
-hipError_t launch_pair_counts(agis_ctx* ctx, const DevGraph& g, const int32_t* hub_slot, const uint32_t* hub_bits,
-                              uint64_t hub_words, const int32_t* pair_slot, uint64_t H, uint32_t* pair_hub,
-                              uint32_t* pair_count, uint32_t* pair_quart) {
-    hipLaunchKernelGGL(k_pair_hubs, dim3(grid_for(g.n, 256)), dim3(256), 0, ctx->stream, pair_slot, g.n, pair_hub);
-    const uint64_t waves = H * H;
-    const uint64_t blocks = std::min<uint64_t>((waves + 3) / 4, (uint64_t)ctx->num_cus * 8);
-    hipLaunchKernelGGL(k_pair_counts, dim3((unsigned)blocks), dim3(256), 0, ctx->stream, g, hub_slot, hub_bits,
-                       hub_words, pair_hub, H, pair_count, pair_quart);
-    return hipGetLastError();
-}
-
-__global__ void k_pair_hub_degrees(DevGraph g, const uint32_t* __restrict__ pair_hub, uint64_t H,
-                                   uint32_t* __restrict__ deg) {
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < H) deg[i] = (uint32_t)(g.off[pair_hub[i] + 1] - g.off[pair_hub[i]]);
+hipError_t launch_pair_counts(agis_ctx* ctx, const DevGraph& g, uint32_t max_deg, int32_t* pair_slot, uint64_t H,
+                              uint32_t* pair_hub, uint32_t* pair_count, uint32_t* pair_quart) {
+    hipStream_t st = ctx->stream;
+    uint32_t lw = kPairRowWords;
+    while (lw > 1 && 32ull * (lw / 2) >= H) lw /= 2;
+    size_t free_b = 0, total_b = 0;
+    uint64_t budget = kPairRowsBudget;
+    if (hipMemGetInfo(&free_b, &total_b) == hipSuccess) budget = std::min<uint64_t>(budget, (uint64_t)free_b / 2);
+    while (lw > 1 && g.n * lw * sizeof(uint32_t) > budget) lw /= 2;
+    uint32_t *hub = nullptr, *rows = nullptr;
+    hipError_t e = hipMalloc(&hub, H * sizeof(uint32_t));
+    if (e != hipSuccess) return e;
+    for (;; lw /= 2) {
+        e = hipMalloc(&rows, g.n * lw * sizeof(uint32_t));
+        if (e != hipErrorOutOfMemory || lw == 1) break;
+        (void)hipGetLastError();
+    }
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k_pair_hubs, dim3(grid_for(g.n, 256)), dim3(256), 0, st, pair_slot, g.n, hub);
+        hipLaunchKernelGGL(k_pair_rank, dim3(grid_for(H, 256)), dim3(256), 0, st, g, hub, H, pair_hub, pair_slot);
+        // an eighth of the longest list must fit the planes
+        const bool small = max_deg / kPairParts + 1 < (1u << 16);
+        const uint64_t panel = 32ull * lw;
+        for (uint64_t base = 0; base + 1 < H && e == hipSuccess; base += panel) {
+            const uint64_t hubs = std::min<uint64_t>(panel, H - base);
+            e = hipMemsetAsync(rows, 0, g.n * lw * sizeof(uint32_t), st);
+            if (e != hipSuccess) break;
+            hipLaunchKernelGGL(k_hub_rows, dim3((unsigned)hubs, 4), dim3(256), 0, st, g, pair_hub, base, lw, rows);
+            const dim3 grid((unsigned)(H - base - 1));
+            if (small)
+                hipLaunchKernelGGL(k_pair_counts<16>, grid, dim3(kPairThreads), 0, st, g, rows, lw, pair_hub, H, base,
+                                   pair_count, pair_quart);
+            else
+                hipLaunchKernelGGL(k_pair_counts<30>, grid, dim3(kPairThreads), 0, st, g, rows, lw, pair_hub, H, base,
+                                   pair_count, pair_quart);
+            e = hipGetLastError();
+        }
+        const hipError_t es = hipStreamSynchronize(st);  // the rows are freed below
+        if (e == hipSuccess) e = es;
+    }
+    if (rows) (void)hipFree(rows);
+    (void)hipFree(hub);
+    return e;
 }
 
 __global__ void k_core_slots(const uint32_t* __restrict__ core_vertex, uint64_t C, int32_t* __restrict__ core_slot) {
@@ -1197,12 +1324,6 @@ hipError_t launch_core_pick(agis_ctx* ctx, const agis_tables& t, const int32_t* 
     const uint64_t blocks = std::min<uint64_t>((waves + 3) / 4, (uint64_t)ctx->num_cus * 8);
     hipLaunchKernelGGL(k_core_pick, dim3((unsigned)blocks), dim3(256), 0, ctx->stream, t.core_nbr, t.core_start,
                        t.core_len, C, sw, clm, cbp);
-    return hipGetLastError();
-}
-
-hipError_t launch_pair_hub_degrees(agis_ctx* ctx, const DevGraph& g, const uint32_t* pair_hub, uint64_t H,
-                                   uint32_t* deg) {
-    hipLaunchKernelGGL(k_pair_hub_degrees, dim3(grid_for(H, 256)), dim3(256), 0, ctx->stream, g, pair_hub, H, deg);
     return hipGetLastError();
 }
 
@@ -1555,8 +1676,9 @@ __device__ __forceinline__ bool pair_hub_count(const DevTables& t, uint32_t my_t
     mt.uni(t.pair_slot + b, 4);
     const int32_t sa = t.pair_slot[a], sb = t.pair_slot[b];
     if (sa < 0 || sb < 0) return false;
-    mt.uni(t.pair_count + (uint64_t)sa * t.pairs + (uint64_t)sb, 4);
-    const uint32_t c = t.pair_count[(uint64_t)sa * t.pairs + (uint64_t)sb];
+    const uint64_t pr = (uint64_t)(sa > sb ? sa : sb) * t.pairs + (uint64_t)(sa > sb ? sb : sa);
+    mt.uni(t.pair_count + pr, 4);
+    const uint32_t c = t.pair_count[pr];
     bool both = false;
     const bool probe = (uint32_t)lane < i && my_tau != a && my_tau != b;
     if constexpr (MT::kOn) {
@@ -1618,7 +1740,8 @@ __device__ __forceinline__ uint32_t pair_hub_select(const DevGraph& g, const Dev
     }
     // the cuts j d / P: members of S before each (the part holding rank r
     // lies between the last cut at or below r and the next)
-    const auto q = t.pair_quart + ((uint64_t)t.pair_slot[a] * t.pairs + (uint64_t)t.pair_slot[b]) * (kPairParts - 1);
+    const auto q = t.pair_quart + ((uint64_t)t.pair_slot[walk_a ? a : b] * t.pairs +
+                                   (uint64_t)t.pair_slot[walk_a ? b : a]) * (kPairParts - 1);
     uint32_t cutv[kPairParts - 1], qv[kPairParts - 1];
     mt.uni(t.pair_slot + a, 4);
     mt.uni(t.pair_slot + b, 4);
