@@ -237,13 +237,17 @@ struct SampleLaunch {
 // The sampling kernel for (record-writing?, register-budget variant 0..2,
 // pair-hub paths?).
 const void* sample_kernel(bool dump, int variant, bool pairs, bool meter);
-// Core-pair lists: core_slot[core_vertex[c]] = c, and for every pair a < b
-// of core slots the common neighbours of the two vertices, ascending, at
-// core_nbr + core_start[a * C + b] (walking the shorter list and probing the
-// other's hub bitmap).
-hipError_t launch_core_pairs(agis_ctx* ctx, const DevGraph& g, const int32_t* hub_slot, const uint32_t* hub_bits,
-                             uint64_t hub_words, const uint32_t* core_vertex, uint64_t C, int32_t* core_slot,
-                             const uint64_t* core_start, const uint32_t* core_len, uint32_t* core_nbr);
+// Entries (padded to kCoreBlock) of the common-neighbour lists of pair hub c
+// with the hubs of smaller slot, c < rows.
+hipError_t launch_core_rows(agis_ctx* ctx, const uint32_t* pair_count, uint64_t H, uint64_t rows,
+                            uint64_t* row_entries);
+// Core-pair lists of the pair hubs 0 .. C - 1: core_slot[pair_hub[c]] = c,
+// the index (see DevTables), and the lists; those of c with the hubs below
+// it start at entry row_start[c] (device).  Synchronises the stream.
+hipError_t launch_core_pairs(agis_ctx* ctx, const DevGraph& g, const uint32_t* pair_hub, uint64_t H,
+                             const uint32_t* pair_count, const uint32_t* pair_quart, uint64_t C,
+                             const uint64_t* row_start, int32_t* core_slot, uint64_t* core_start, uint32_t* core_len,
+                             uint32_t* core_nbr);
 
 // The pick table of one step signature (per-vertex log weights sw, certain
 // zeros folded in) over the core-pair lists: clm[pair] (indexed like

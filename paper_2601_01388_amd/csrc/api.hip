@@ -305,58 +305,52 @@ constexpr uint64_t kCoreMax = 4096;
 hipError_t build_core_pairs(agis_ctx* ctx, const agis_graph* g, agis_tables* t, const uint32_t* pair_hub,
                             uint64_t H) {
     const uint64_t n = g->g.n;
-    std::vector<uint32_t> hub(H), cnt(H * H);
-    hipError_t e = hipMemcpyAsync(hub.data(), pair_hub, H * sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream);
+    const uint64_t most = std::min<uint64_t>(H, kCoreMax);
+    std::vector<uint64_t> rows(most), start;
+    uint64_t* d_rows = nullptr;
+    hipError_t e = hipMalloc(&d_rows, most * sizeof(uint64_t));
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        return hipSuccess;
+    }
+    if (e == hipSuccess) e = agis::launch_core_rows(ctx, t->pair_count, H, most, d_rows);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(cnt.data(), t->pair_count, H * H * sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream);
+        e = hipMemcpyAsync(rows.data(), d_rows, most * sizeof(uint64_t), hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess) {
+        if (d_rows) (void)hipFree(d_rows);
+        return e;
+    }
     uint64_t budget = kCorePairBudget;
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) == hipSuccess) budget = std::min<uint64_t>(budget, (uint64_t)free_b / 8);
-    const uint64_t cap = budget / sizeof(uint32_t);
     // every pair's list starts on a block of agis::kCoreBlock entries (the
     // pick tables over the lists keep one prefix per block)
-    auto padded = [](uint64_t l) { return (l + agis::kCoreBlock - 1) / agis::kCoreBlock * agis::kCoreBlock; };
-    uint64_t total = 0, C = 0;
-    for (uint64_t c = 0; c < std::min<uint64_t>(H, kCoreMax); ++c) {
-        uint64_t add = 0;
-        for (uint64_t j = 0; j < c; ++j) add += padded(cnt[c * H + j]);
+    uint64_t total = 0;
+    for (uint64_t c = 0; c < most; ++c) {
         const uint64_t index_bytes = (c + 1) * (c + 1) * (sizeof(uint64_t) + sizeof(uint32_t));
-        if ((total + add) * sizeof(uint32_t) + index_bytes > budget || total + add > cap) break;
-        total += add;
-        C = c + 1;
+        if ((total + rows[c]) * sizeof(uint32_t) + index_bytes > budget) break;
+        start.push_back(total);
+        total += rows[c];
     }
-    if (C < 2) return hipSuccess;
-    std::vector<uint32_t> vert(C), len(C * C, 0u);
-    std::vector<uint64_t> start(C * C, 0ull);
-    for (uint64_t c = 0; c < C; ++c) vert[c] = hub[c];
-    uint64_t run = 0;
-    for (uint64_t a = 0; a < C; ++a)
-        for (uint64_t b = a + 1; b < C; ++b) {
-            const uint32_t l = cnt[b * H + a];
-            start[a * C + b] = start[b * C + a] = run;
-            len[a * C + b] = len[b * C + a] = l;
-            run += padded(l);
-        }
-    t->core_entries = run;
-    uint32_t* d_vert = nullptr;
+    const uint64_t C = start.size();
+    if (C < 2) {
+        (void)hipFree(d_rows);
+        return hipSuccess;
+    }
+    t->core_entries = total;
     e = hipMalloc(&t->core_slot, n * sizeof(int32_t));
     if (e == hipSuccess) e = hipMalloc(&t->core_start, C * C * sizeof(uint64_t));
     if (e == hipSuccess) e = hipMalloc(&t->core_len, C * C * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMalloc(&t->core_nbr, std::max<uint64_t>(run, 1) * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMalloc(&d_vert, C * sizeof(uint32_t));
+    if (e == hipSuccess) e = hipMalloc(&t->core_nbr, std::max<uint64_t>(total, 1) * sizeof(uint32_t));
     if (e == hipSuccess) e = agis::launch_fill_u32((uint32_t*)t->core_slot, n, 0xFFFFFFFFu, ctx->stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(t->core_start, start.data(), C * C * sizeof(uint64_t), hipMemcpyHostToDevice, ctx->stream);
+        e = hipMemcpyAsync(d_rows, start.data(), C * sizeof(uint64_t), hipMemcpyHostToDevice, ctx->stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(t->core_len, len.data(), C * C * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(d_vert, vert.data(), C * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->stream);
-    if (e == hipSuccess)
-        e = agis::launch_core_pairs(ctx, g->g, t->hub_slot, t->hub_bits, t->hub_words, d_vert, C, t->core_slot,
+        e = agis::launch_core_pairs(ctx, g->g, pair_hub, H, t->pair_count, t->pair_quart, C, d_rows, t->core_slot,
                                     t->core_start, t->core_len, t->core_nbr);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    if (d_vert) (void)hipFree(d_vert);
+    (void)hipStreamSynchronize(ctx->stream);
+    (void)hipFree(d_rows);
     if (e == hipSuccess) {
         t->cores = C;
         return hipSuccess;

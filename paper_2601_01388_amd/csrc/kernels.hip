@@ -1186,23 +1186,39 @@ __global__ __launch_bounds__(kPairThreads) void k_pair_counts(DevGraph g, const 
     }
 }
 
-hipError_t launch_pair_counts(agis_ctx* ctx, const DevGraph& g, uint32_t max_deg, int32_t* pair_slot, uint64_t H,
-                              uint32_t* pair_hub, uint32_t* pair_count, uint32_t* pair_quart) {
-    hipStream_t st = ctx->stream;
-    uint32_t lw = kPairRowWords;
-    while (lw > 1 && 32ull * (lw / 2) >= H) lw /= 2;
+// The row scratch of panels over `hubs` hubs: *lw words per vertex, at most
+// kPairRowWords, fewer for few hubs or little memory.
+static hipError_t alloc_rows(const DevGraph& g, uint64_t hubs, uint32_t* lw, uint32_t** rows) {
+    *lw = kPairRowWords;
+    while (*lw > 1 && 32ull * (*lw / 2) >= hubs) *lw /= 2;
     size_t free_b = 0, total_b = 0;
     uint64_t budget = kPairRowsBudget;
     if (hipMemGetInfo(&free_b, &total_b) == hipSuccess) budget = std::min<uint64_t>(budget, (uint64_t)free_b / 2);
-    while (lw > 1 && g.n * lw * sizeof(uint32_t) > budget) lw /= 2;
+    while (*lw > 1 && g.n * *lw * sizeof(uint32_t) > budget) *lw /= 2;
+    for (;; *lw /= 2) {
+        const hipError_t e = hipMalloc(rows, g.n * *lw * sizeof(uint32_t));
+        if (e != hipErrorOutOfMemory || *lw == 1) return e;
+        (void)hipGetLastError();
+    }
+}
+
+// The rows of the panel of hubs base .. base + hubs - 1.
+static hipError_t fill_rows(const DevGraph& g, const uint32_t* pair_hub, uint64_t base, uint64_t hubs, uint32_t lw,
+                            uint32_t* rows, hipStream_t st) {
+    const hipError_t e = hipMemsetAsync(rows, 0, g.n * lw * sizeof(uint32_t), st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_hub_rows, dim3((unsigned)hubs, 4), dim3(256), 0, st, g, pair_hub, base, lw, rows);
+    return hipGetLastError();
+}
+
+hipError_t launch_pair_counts(agis_ctx* ctx, const DevGraph& g, uint32_t max_deg, int32_t* pair_slot, uint64_t H,
+                              uint32_t* pair_hub, uint32_t* pair_count, uint32_t* pair_quart) {
+    hipStream_t st = ctx->stream;
+    uint32_t lw = 0;
     uint32_t *hub = nullptr, *rows = nullptr;
     hipError_t e = hipMalloc(&hub, H * sizeof(uint32_t));
     if (e != hipSuccess) return e;
-    for (;; lw /= 2) {
-        e = hipMalloc(&rows, g.n * lw * sizeof(uint32_t));
-        if (e != hipErrorOutOfMemory || lw == 1) break;
-        (void)hipGetLastError();
-    }
+    e = alloc_rows(g, H, &lw, &rows);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_pair_hubs, dim3(grid_for(g.n, 256)), dim3(256), 0, st, pair_slot, g.n, hub);
         hipLaunchKernelGGL(k_pair_rank, dim3(grid_for(H, 256)), dim3(256), 0, st, g, hub, H, pair_hub, pair_slot);
@@ -1210,10 +1226,8 @@ hipError_t launch_pair_counts(agis_ctx* ctx, const DevGraph& g, uint32_t max_deg
         const bool small = max_deg / kPairParts + 1 < (1u << 16);
         const uint64_t panel = 32ull * lw;
         for (uint64_t base = 0; base + 1 < H && e == hipSuccess; base += panel) {
-            const uint64_t hubs = std::min<uint64_t>(panel, H - base);
-            e = hipMemsetAsync(rows, 0, g.n * lw * sizeof(uint32_t), st);
+            e = fill_rows(g, pair_hub, base, std::min<uint64_t>(panel, H - base), lw, rows, st);
             if (e != hipSuccess) break;
-            hipLaunchKernelGGL(k_hub_rows, dim3((unsigned)hubs, 4), dim3(256), 0, st, g, pair_hub, base, lw, rows);
             const dim3 grid((unsigned)(H - base - 1));
             if (small)
                 hipLaunchKernelGGL(k_pair_counts<16>, grid, dim3(kPairThreads), 0, st, g, rows, lw, pair_hub, H, base,
@@ -1231,47 +1245,131 @@ hipError_t launch_pair_counts(agis_ctx* ctx, const DevGraph& g, uint32_t max_deg
     return e;
 }
 
-__global__ void k_core_slots(const uint32_t* __restrict__ core_vertex, uint64_t C, int32_t* __restrict__ core_slot) {
-    const uint64_t c = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c < C) core_slot[core_vertex[c]] = (int32_t)c;
+__device__ __forceinline__ uint64_t core_padded(uint32_t len) {
+    return ((uint64_t)len + kCoreBlock - 1) / kCoreBlock * kCoreBlock;
 }
 
-// One wave per pair a < b of core slots: the shorter list (by (degree, id))
-// is walked in order and its members of the other list (one bit probe of
-// that vertex's hub bitmap each) are appended by ballot, so the list comes
-// out ascending.
-__global__ __launch_bounds__(256) void k_core_fill(DevGraph g, const int32_t* __restrict__ hub_slot,
-                                                    const uint32_t* __restrict__ hub_bits, uint64_t hub_words,
-                                                    const uint32_t* __restrict__ core_vertex, uint64_t C,
+// Entries the lists of pair hub c with the hubs above it take (block c).
+__global__ __launch_bounds__(256) void k_core_rows(const uint32_t* __restrict__ pair_count, uint64_t H,
+                                                   uint64_t* __restrict__ row_entries) {
+    __shared__ uint64_t ws[256 / kWave];
+    const uint64_t c = blockIdx.x;
+    uint64_t s = 0;
+    for (uint64_t j = threadIdx.x; j < c; j += 256u) s += core_padded(pair_count[c * H + j]);
+    s = wave_sum_u64(s);
+    if (lane_id() == 0) ws[threadIdx.x / kWave] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) row_entries[c] = ws[0] + ws[1] + ws[2] + ws[3];
+}
+
+// The index of the core lists: row c's lists (with hubs j < c, ascending j)
+// lie one after the other from row_start[c]; both orders of a pair point at
+// the one list, the diagonal at nothing.  Also the core slots.
+__global__ __launch_bounds__(256) void k_core_index(const uint32_t* __restrict__ pair_count, uint64_t H,
+                                                    const uint32_t* __restrict__ pair_hub,
+                                                    const uint64_t* __restrict__ row_start, uint64_t C,
+                                                    int32_t* __restrict__ core_slot, uint64_t* __restrict__ core_start,
+                                                    uint32_t* __restrict__ core_len) {
+    __shared__ uint64_t ws[256 / kWave];
+    const uint64_t c = blockIdx.x;
+    uint64_t run = row_start[c];
+    for (uint64_t j0 = 0; j0 < c; j0 += 256u) {
+        const uint64_t j = j0 + threadIdx.x;
+        const uint32_t len = j < c ? pair_count[c * H + j] : 0u;
+        const uint64_t pad = core_padded(len);
+        const uint64_t incl = wave_incl_scan_u64(pad);
+        const uint32_t w = threadIdx.x / kWave;
+        if (lane_id() == kWave - 1) ws[w] = incl;
+        __syncthreads();
+        uint64_t at = run + incl - pad;
+        for (uint32_t k = 0; k < w; ++k) at += ws[k];
+        run += ws[0] + ws[1] + ws[2] + ws[3];
+        if (j < c) {
+            core_start[c * C + j] = at;
+            core_start[j * C + c] = at;
+            core_len[c * C + j] = len;
+            core_len[j * C + c] = len;
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        core_start[c * C + c] = 0;
+        core_len[c * C + c] = 0;
+        core_slot[pair_hub[c]] = (int32_t)c;
+    }
+}
+
+// The core-pair lists from the transposed membership rows of the pair hubs
+// (see k_hub_rows): a wave walks an eighth of core hub a's list for four
+// words of the panel, 64 elements at a time with one 16-byte row piece per
+// lane; per hub of those words, the lanes whose bit is set append their
+// element to the hub's list in lane order, so every list comes out
+// ascending.  The lists' write positions start from the pair table's counts
+// at the eighths, so the eighths are independent.  Lane l holds the
+// positions of word l / 32 and 2 + l / 32, bit l % 32.
+//
+// Walking one list per pair and probing the other hub's bitmap for every
+// element took 13.9 ms on R-MAT-20 (4 GB of lists, bound by the probes); a
+// row piece here serves 128 pairs: 3.8 ms, about 1.1 TB/s of list entries,
+// bound by the vector operations of the appends.
+//
+// Grid: (walked hubs base + 1 .. C - 1, pieces / 4, eighths).
+__global__ __launch_bounds__(256) void k_core_fill(DevGraph g, const uint32_t* __restrict__ rows, uint32_t lw,
+                                                    const uint32_t* __restrict__ pair_hub, uint64_t H, uint64_t base,
+                                                    const uint32_t* __restrict__ pair_quart, uint64_t C,
                                                     const uint64_t* __restrict__ core_start,
-                                                    const uint32_t* __restrict__ core_len,
                                                     uint32_t* __restrict__ core_nbr) {
     const int lane = lane_id();
-    const uint64_t nw = (uint64_t)gridDim.x * (blockDim.x / kWave);
-    for (uint64_t pr = (uint64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave; pr < C * C; pr += nw) {
-        const uint64_t a = pr / C, b = pr % C;
-        if (a >= b) continue;  // wave-uniform
-        const uint32_t va = core_vertex[a], vb = core_vertex[b];
-        const uint64_t oa = g.off[va], ob = g.off[vb];
-        const uint64_t da = g.off[va + 1] - oa, db = g.off[vb + 1] - ob;
-        const bool walk_a = da < db || (da == db && va < vb);
-        const uint64_t o = walk_a ? oa : ob, d = walk_a ? da : db;
-        const uint32_t* bits = hub_bits + (uint64_t)hub_slot[walk_a ? vb : va] * hub_words;
-        uint32_t* out = core_nbr + core_start[pr];
-        const uint64_t len = core_len[pr];  // the pair's range: no write beyond it
-        uint64_t at = 0;
-        for (uint64_t e0 = 0; e0 < d; e0 += kWave) {
-            const uint64_t e = e0 + (uint64_t)lane;
-            bool m = false;
-            uint32_t x = 0;
-            if (e < d) {
-                x = g.nbr[o + e];
-                m = ((bits[x >> 5] >> (x & 31u)) & 1u) != 0u;
+    const uint64_t a = base + 1 + blockIdx.x;
+    const uint32_t w0 = (blockIdx.y * 4 + uniform_u32(threadIdx.x / kWave)) * 4;  // first word of the piece
+    if (w0 >= lw) return;
+    const uint32_t nw = lw - w0 < 4u ? lw - w0 : 4u;
+    const uint64_t nb = a - base < 32ull * lw ? a - base : 32ull * lw;  // hubs of the panel below a
+    if (w0 >= nb) return;
+    const uint32_t v = pair_hub[a];
+    const uint64_t o = g.off[v], d = g.off[v + 1] - o;
+    const uint32_t part = blockIdx.z;
+    const uint64_t e0 = part * d / kPairParts, e1 = (part + 1) * d / kPairParts;
+    // write positions (entries of core_nbr, fewer than 2^31)
+    uint32_t at[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint64_t q = (uint64_t)(lane & 31) * lw + w0 + 2u * h + ((uint32_t)lane >> 5);
+        at[h] = 0;
+        if (2u * h + ((uint32_t)lane >> 5) < nw && q < nb) {
+            at[h] = (uint32_t)core_start[a * C + base + q];
+            if (part) at[h] += pair_quart[(a * H + base + q) * (kPairParts - 1) + part - 1];
+        }
+    }
+    for (uint64_t c = e0; c < e1; c += kWave) {
+        const bool valid = c + (uint64_t)lane < e1;
+        const uint32_t x = valid ? g.nbr[o + c + (uint64_t)lane] : 0u;
+        uint32_t r[4] = {0u, 0u, 0u, 0u};
+        if (valid) {
+            const uint32_t* row = rows + (uint64_t)x * lw + w0;
+            if (nw == 4) {
+                const uint4 t = *(const uint4*)row;
+                r[0] = t.x;
+                r[1] = t.y;
+                r[2] = t.z;
+                r[3] = t.w;
+            } else {
+                for (uint32_t j = 0; j < nw; ++j) r[j] = row[j];
             }
-            const uint64_t bm = __ballot(m);
-            const uint64_t w = at + (uint64_t)__popcll(bm & lanemask_lt());
-            if (m && w < len) out[w] = x;
-            at += (uint64_t)__popcll(bm);
+        }
+        for (uint32_t bit = 0; bit < 32u && (uint64_t)bit * lw + w0 < nb; ++bit) {
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                // (bits of hubs at or above a are another walk's)
+                if ((uint64_t)bit * lw + w0 + j >= nb) break;
+                const bool m = (r[j] >> bit) & 1u;
+                const uint64_t bm = __ballot(m);
+                if (bm == 0) continue;
+                const int hl = (int)(bit + 32u * (j & 1u));
+                const uint32_t p = readlane_u32(at[j >> 1], hl);
+                if (m) core_nbr[p + (uint32_t)__popcll(bm & lanemask_lt())] = x;
+                if (lane == hl) at[j >> 1] = p + (uint32_t)__popcll(bm);
+            }
         }
     }
 }
@@ -1327,15 +1425,34 @@ hipError_t launch_core_pick(agis_ctx* ctx, const agis_tables& t, const int32_t* 
     return hipGetLastError();
 }
 
-hipError_t launch_core_pairs(agis_ctx* ctx, const DevGraph& g, const int32_t* hub_slot, const uint32_t* hub_bits,
-                             uint64_t hub_words, const uint32_t* core_vertex, uint64_t C, int32_t* core_slot,
-                             const uint64_t* core_start, const uint32_t* core_len, uint32_t* core_nbr) {
-    hipLaunchKernelGGL(k_core_slots, dim3(grid_for(C, 256)), dim3(256), 0, ctx->stream, core_vertex, C, core_slot);
-    const uint64_t waves = C * C;
-    const uint64_t blocks = std::min<uint64_t>((waves + 3) / 4, (uint64_t)ctx->num_cus * 8);
-    hipLaunchKernelGGL(k_core_fill, dim3((unsigned)blocks), dim3(256), 0, ctx->stream, g, hub_slot, hub_bits,
-                       hub_words, core_vertex, C, core_start, core_len, core_nbr);
+hipError_t launch_core_rows(agis_ctx* ctx, const uint32_t* pair_count, uint64_t H, uint64_t rows,
+                            uint64_t* row_entries) {
+    hipLaunchKernelGGL(k_core_rows, dim3((unsigned)rows), dim3(256), 0, ctx->stream, pair_count, H, row_entries);
     return hipGetLastError();
+}
+
+hipError_t launch_core_pairs(agis_ctx* ctx, const DevGraph& g, const uint32_t* pair_hub, uint64_t H,
+                             const uint32_t* pair_count, const uint32_t* pair_quart, uint64_t C,
+                             const uint64_t* row_start, int32_t* core_slot, uint64_t* core_start, uint32_t* core_len,
+                             uint32_t* core_nbr) {
+    hipStream_t st = ctx->stream;
+    hipLaunchKernelGGL(k_core_index, dim3((unsigned)C), dim3(256), 0, st, pair_count, H, pair_hub, row_start, C,
+                       core_slot, core_start, core_len);
+    uint32_t lw = 0;
+    uint32_t* rows = nullptr;
+    hipError_t e = alloc_rows(g, C, &lw, &rows);
+    const uint64_t panel = 32ull * lw;
+    for (uint64_t base = 0; base + 1 < C && e == hipSuccess; base += panel) {
+        e = fill_rows(g, pair_hub, base, std::min<uint64_t>(panel, C - base), lw, rows, st);
+        if (e != hipSuccess) break;
+        hipLaunchKernelGGL(k_core_fill, dim3((unsigned)(C - base - 1), (lw + 15) / 16, kPairParts), dim3(256), 0, st,
+                           g, rows, lw, pair_hub, H, base, pair_quart, C, core_start, core_nbr);
+        e = hipGetLastError();
+    }
+    const hipError_t es = hipStreamSynchronize(st);  // the rows are freed below
+    if (e == hipSuccess) e = es;
+    if (rows) (void)hipFree(rows);
+    return e;
 }
 
 hipError_t launch_orient_fill(const DevGraph& g, const uint64_t* off_out, uint32_t* nbr_out, hipStream_t stream) {
