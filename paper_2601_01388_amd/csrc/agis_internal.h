@@ -3,14 +3,64 @@
 
 #include <hip/hip_runtime.h>
 
+#include <memory>
+#include <mutex>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "agis.h"
 #include "agis_common.h"
 
+namespace agis {
+
+// Device buffers of destroyed tables, evicted proposal tables and finished
+// calls, kept for the next ones of the context.  The driver wipes memory
+// that is given back before it hands it out again, at about 38 GB/s here
+// once the wiped pages have run out: a program that builds and destroys the
+// tables of R-MAT-20 (7.5 GB a time) is paced by that, 196 ms a build
+// against 18 ms of work.  Kept buffers are bounded (kPoolBudget), none are
+// kept while less than kPoolFreeFloor of device memory is free, an
+// allocation that fails gives them all back first, and so do
+// agis_release_scratch and agis_destroy.  Tables and graphs hold the pool
+// alive (they may outlive their context; it keeps nothing from then on).
+// Buffers come back only after the work that uses them has ended.
+constexpr size_t kPoolBudget = 8ull << 30;
+constexpr size_t kPoolFreeFloor = 128ull << 30;
+constexpr size_t kPoolMin = 1ull << 20;          // smaller buffers are not kept
+constexpr size_t kPoolFloorCheck = 64ull << 20;  // buffers of this size on ask for the free memory
+
+class DevPool {
+  public:
+    ~DevPool() { trim(); }
+    hipError_t alloc(void** p, size_t bytes);
+    template <class T>
+    hipError_t alloc(T** p, size_t bytes) {
+        return alloc((void**)p, bytes);
+    }
+    void free(void* p);
+    void trim();   // gives every kept buffer back
+    void close();  // trim, and keep nothing from now on
+    size_t kept();
+
+  private:
+    struct Buf {
+        void* p;
+        size_t bytes;
+    };
+    std::mutex mu_;
+    std::vector<Buf> idle_;  // oldest first
+    std::unordered_map<void*, size_t> live_;
+    size_t idle_bytes_ = 0;
+    bool open_ = true;
+    void trim_locked();
+};
+
+}  // namespace agis
+
 struct agis_ctx {
     int device = 0;
+    std::shared_ptr<agis::DevPool> pool = std::make_shared<agis::DevPool>();
     hipStream_t stream = nullptr;
     std::string err;
     int num_cus = 256;
@@ -58,6 +108,8 @@ struct agis_ctx {
 
 struct agis_graph {
     agis_ctx* ctx = nullptr;
+    std::shared_ptr<agis::DevPool> pool;  // of an oriented graph's buffers
+    int device = 0;
     agis::DevGraph g{};
     uint32_t max_deg = 0;
     // a degree-oriented graph (agis_orient) owns its CSR and keeps the
@@ -71,6 +123,8 @@ struct TableCache;  // proposal tables of f_approx kept across calls (csrc/api.h
 
 struct agis_tables {
     agis_ctx* ctx = nullptr;
+    std::shared_ptr<agis::DevPool> pool;
+    int device = 0;
     TableCache* cache = nullptr;
     const agis_graph* graph = nullptr;
     uint4* rec = nullptr;      // {deg, LA, LC, 0}
@@ -99,6 +153,10 @@ struct agis_tables {
 };
 
 namespace agis {
+
+// hipMalloc for the context's own buffers: a failed allocation gives the
+// pool's kept buffers back and tries once more.
+hipError_t ctx_malloc(agis_ctx* ctx, void** p, size_t bytes);
 
 int compile_plan(const agis_pattern* p, const uint8_t* order, int mode, int beta_num, int beta_den,
                  agis_plan* out, std::string* err);

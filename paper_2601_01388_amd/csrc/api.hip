@@ -25,7 +25,106 @@ using agis::Partial;
 constexpr uint64_t kNoAllocBytes = 256ull << 20;
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
+namespace agis {
+
+hipError_t DevPool::alloc(void** p, size_t bytes) {
+    std::lock_guard<std::mutex> lk(mu_);
+    *p = nullptr;
+    if (bytes >= kPoolMin) {
+        // the smallest kept buffer that holds it with at most a quarter to spare
+        size_t best = idle_.size();
+        for (size_t i = 0; i < idle_.size(); ++i)
+            if (idle_[i].bytes >= bytes && idle_[i].bytes - bytes <= bytes / 4 &&
+                (best == idle_.size() || idle_[i].bytes < idle_[best].bytes))
+                best = i;
+        if (best < idle_.size()) {
+            const Buf b = idle_[best];
+            idle_.erase(idle_.begin() + (std::ptrdiff_t)best);
+            idle_bytes_ -= b.bytes;
+            live_[b.p] = b.bytes;
+            *p = b.p;
+            return hipSuccess;
+        }
+    }
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory && !idle_.empty()) {
+        (void)hipGetLastError();
+        trim_locked();
+        e = hipMalloc(p, bytes);
+    }
+    if (e == hipSuccess && bytes >= kPoolMin) live_[*p] = bytes;
+    return e;
+}
+
+void DevPool::free(void* p) {
+    if (!p) return;
+    std::lock_guard<std::mutex> lk(mu_);
+    const auto it = live_.find(p);
+    const size_t bytes = it == live_.end() ? 0 : it->second;
+    if (it != live_.end()) live_.erase(it);
+    bool keep = open_ && bytes >= kPoolMin && bytes <= kPoolBudget;
+    if (keep && bytes >= kPoolFloorCheck) {
+        size_t free_b = 0, total_b = 0;
+        keep = hipMemGetInfo(&free_b, &total_b) == hipSuccess && free_b >= kPoolFreeFloor;
+    }
+    if (!keep) {
+        (void)hipFree(p);
+        return;
+    }
+    while (idle_bytes_ + bytes > kPoolBudget) {
+        (void)hipFree(idle_.front().p);
+        idle_bytes_ -= idle_.front().bytes;
+        idle_.erase(idle_.begin());
+    }
+    idle_.push_back(Buf{p, bytes});
+    idle_bytes_ += bytes;
+}
+
+void DevPool::trim_locked() {
+    for (const Buf& b : idle_) (void)hipFree(b.p);
+    idle_.clear();
+    idle_bytes_ = 0;
+}
+
+void DevPool::trim() {
+    std::lock_guard<std::mutex> lk(mu_);
+    trim_locked();
+}
+
+void DevPool::close() {
+    std::lock_guard<std::mutex> lk(mu_);
+    open_ = false;
+    trim_locked();
+}
+
+size_t DevPool::kept() {
+    std::lock_guard<std::mutex> lk(mu_);
+    return idle_bytes_;
+}
+
+hipError_t ctx_malloc(agis_ctx* ctx, void** p, size_t bytes) {
+    *p = nullptr;
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory && ctx->pool->kept()) {
+        (void)hipGetLastError();
+        ctx->pool->trim();
+        e = hipMalloc(p, bytes);
+    }
+    return e;
+}
+
+}  // namespace agis
+
 namespace {
+
+// Ends all work on a device before buffers that it may still read (through
+// pointers a caller exported, on any stream) go back to a pool.
+void sync_device(int device) {
+    int cur = 0;
+    if (hipGetDevice(&cur) != hipSuccess || hipSetDevice(device) != hipSuccess) return;
+    (void)hipDeviceSynchronize();
+    if (cur != device) (void)hipSetDevice(cur);
+}
 
 constexpr int kMaxDevices = 64;
 std::mutex g_noalloc_mutex;
@@ -127,11 +226,13 @@ struct Prepared {
     uint32_t* guide = nullptr;
     double tables_seconds = 0;
     bool owns = true;  // false: the buffers are carved from a fixed workspace
+    agis_ctx* ctx = nullptr;
     ~Prepared() {
-        if (!owns) return;
-        if (q1) (void)hipFree(q1);
-        if (pre) (void)hipFree(pre);
-        if (guide) (void)hipFree(guide);
+        if (!owns || !ctx || (!q1 && !pre && !guide)) return;
+        (void)hipStreamSynchronize(ctx->stream);
+        ctx->pool->free(q1);
+        ctx->pool->free(pre);
+        ctx->pool->free(guide);
     }
 };
 
@@ -167,13 +268,13 @@ struct TableCache {
     std::vector<CacheEntry*> v;
     uint64_t bytes = 0, clock = 0;
     uint32_t* long_rows = nullptr;  // scratch of the row-table builds (2n + 2 entries)
+    std::shared_ptr<agis::DevPool> pool;
     ~TableCache() {
         for (CacheEntry* e : v) {
-            for (void* b : e->buf)
-                if (b) (void)hipFree(b);
+            for (void* b : e->buf) pool->free(b);
             delete e;
         }
-        if (long_rows) (void)hipFree(long_rows);
+        pool->free(long_rows);
     }
     CacheEntry* find(uint32_t kind, uint32_t b, uint32_t f1, uint32_t ie, uint32_t f2, uint32_t blocked) {
         for (CacheEntry* e : v)
@@ -193,8 +294,7 @@ struct TableCache {
             for (CacheEntry* e : v)
                 if (e->users == 0 && (!victim || e->stamp < victim->stamp)) victim = e;
             if (!victim) return;
-            for (void* b : victim->buf)
-                if (b) (void)hipFree(b);
+            for (void* b : victim->buf) pool->free(b);
             bytes -= victim->bytes;
             v.erase(std::find(v.begin(), v.end(), victim));
             delete victim;
@@ -205,10 +305,11 @@ struct TableCache {
     void* alloc(uint64_t nbytes) {
         evict(nbytes);
         void* p = nullptr;
-        if (hipMalloc(&p, nbytes) == hipSuccess) return p;
+        if (pool->alloc(&p, nbytes) == hipSuccess) return p;
         (void)hipGetLastError();
         evict(~0ull);
-        if (hipMalloc(&p, nbytes) == hipSuccess) return p;
+        pool->trim();
+        if (pool->alloc(&p, nbytes) == hipSuccess) return p;
         (void)hipGetLastError();
         return nullptr;
     }
@@ -250,6 +351,7 @@ struct StepTables {
     agis::Arena* arena = nullptr;   // non-null: buffers are carved from it, never allocated or freed
     TableCache* cache = nullptr;    // the graph's cache (set by prepare; none with an arena)
     std::vector<CacheEntry*> held;  // cache entries this call uses
+    agis_ctx* ctx = nullptr;        // set by prepare
     StepTables() = default;
     StepTables(const StepTables&) = delete;
     StepTables& operator=(const StepTables&) = delete;
@@ -258,12 +360,16 @@ struct StepTables {
             std::lock_guard<std::mutex> lk(cache->mu);
             for (CacheEntry* c : held) --c->users;
         }
-        if (arena) return;
+        if (arena || !ctx) return;
+        std::vector<void*> own;  // tables of this call alone
         for (Entry& x : e)
-            if (!x.cached) (void)hipFree(x.buf);
+            if (!x.cached) own.push_back(x.buf);
         for (RowEntry& x : rows)
-            if (!x.cached) (void)hipFree(x.buf);
-        if (long_rows && !cache) (void)hipFree(long_rows);
+            if (!x.cached) own.push_back(x.buf);
+        if (long_rows && !cache) own.push_back(long_rows);
+        if (own.empty()) return;
+        (void)hipStreamSynchronize(ctx->stream);
+        for (void* b : own) ctx->pool->free(b);
     }
 };
 constexpr uint64_t kStepTableBudgetBytes = 16ull << 30;
@@ -308,7 +414,7 @@ hipError_t build_core_pairs(agis_ctx* ctx, const agis_graph* g, agis_tables* t, 
     const uint64_t most = std::min<uint64_t>(H, kCoreMax);
     std::vector<uint64_t> rows(most), start;
     uint64_t* d_rows = nullptr;
-    hipError_t e = hipMalloc(&d_rows, most * sizeof(uint64_t));
+    hipError_t e = ctx->pool->alloc(&d_rows, most * sizeof(uint64_t));
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
         return hipSuccess;
@@ -318,7 +424,7 @@ hipError_t build_core_pairs(agis_ctx* ctx, const agis_graph* g, agis_tables* t, 
         e = hipMemcpyAsync(rows.data(), d_rows, most * sizeof(uint64_t), hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) {
-        if (d_rows) (void)hipFree(d_rows);
+        ctx->pool->free(d_rows);
         return e;
     }
     uint64_t budget = kCorePairBudget;
@@ -335,14 +441,14 @@ hipError_t build_core_pairs(agis_ctx* ctx, const agis_graph* g, agis_tables* t, 
     }
     const uint64_t C = start.size();
     if (C < 2) {
-        (void)hipFree(d_rows);
+        ctx->pool->free(d_rows);
         return hipSuccess;
     }
     t->core_entries = total;
-    e = hipMalloc(&t->core_slot, n * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMalloc(&t->core_start, C * C * sizeof(uint64_t));
-    if (e == hipSuccess) e = hipMalloc(&t->core_len, C * C * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMalloc(&t->core_nbr, std::max<uint64_t>(total, 1) * sizeof(uint32_t));
+    e = ctx->pool->alloc(&t->core_slot, n * sizeof(int32_t));
+    if (e == hipSuccess) e = ctx->pool->alloc(&t->core_start, C * C * sizeof(uint64_t));
+    if (e == hipSuccess) e = ctx->pool->alloc(&t->core_len, C * C * sizeof(uint32_t));
+    if (e == hipSuccess) e = ctx->pool->alloc(&t->core_nbr, std::max<uint64_t>(total, 1) * sizeof(uint32_t));
     if (e == hipSuccess) e = agis::launch_fill_u32((uint32_t*)t->core_slot, n, 0xFFFFFFFFu, ctx->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(d_rows, start.data(), C * sizeof(uint64_t), hipMemcpyHostToDevice, ctx->stream);
@@ -350,14 +456,14 @@ hipError_t build_core_pairs(agis_ctx* ctx, const agis_graph* g, agis_tables* t, 
         e = agis::launch_core_pairs(ctx, g->g, pair_hub, H, t->pair_count, t->pair_quart, C, d_rows, t->core_slot,
                                     t->core_start, t->core_len, t->core_nbr);
     (void)hipStreamSynchronize(ctx->stream);
-    (void)hipFree(d_rows);
+    ctx->pool->free(d_rows);
     if (e == hipSuccess) {
         t->cores = C;
         return hipSuccess;
     }
     // no room (or a failed build): sample without the core lists
     for (void* q : {(void*)t->core_slot, (void*)t->core_start, (void*)t->core_len, (void*)t->core_nbr})
-        if (q) (void)hipFree(q);
+        ctx->pool->free(q);
     t->core_slot = nullptr;
     t->core_start = nullptr;
     t->core_len = nullptr;
@@ -399,7 +505,7 @@ hipError_t build_hub_bitmaps(agis_ctx* ctx, const agis_graph* g, agis_tables* t)
         (void)hipGetLastError();
         for (void* q : {(void*)flags, (void*)prefix, (void*)t->hub_slot, (void*)t->hub_bits, (void*)t->pair_slot,
                         (void*)t->pair_count, (void*)t->pair_quart})
-            if (q) (void)hipFree(q);
+            ctx->pool->free(q);
         t->hub_slot = nullptr;
         t->hub_bits = nullptr;
         t->pair_slot = nullptr;
@@ -408,14 +514,14 @@ hipError_t build_hub_bitmaps(agis_ctx* ctx, const agis_graph* g, agis_tables* t)
         t->hub_words = t->hubs = t->pairs = 0;
         return hipSuccess;
     };
-    e = hipMalloc(&flags, n * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMalloc(&prefix, (n + 1) * sizeof(uint64_t));
-    if (e == hipSuccess) e = hipMalloc(&t->hub_slot, n * sizeof(int32_t));
+    e = ctx->pool->alloc(&flags, n * sizeof(uint32_t));
+    if (e == hipSuccess) e = ctx->pool->alloc(&prefix, (n + 1) * sizeof(uint64_t));
+    if (e == hipSuccess) e = ctx->pool->alloc(&t->hub_slot, n * sizeof(int32_t));
     if (e == hipSuccess) e = agis::launch_hub_slots(ctx, g->g, 1u << b, flags, t->hub_slot, prefix);
     uint64_t hubs = 0;
     if (e == hipSuccess) e = hipMemcpyAsync(&hubs, prefix + n, sizeof(uint64_t), hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    if (e == hipSuccess) e = hipMalloc(&t->hub_bits, hubs * words * sizeof(uint32_t));
+    if (e == hipSuccess) e = ctx->pool->alloc(&t->hub_bits, hubs * words * sizeof(uint32_t));
     if (e == hipErrorOutOfMemory) return drop_out_of_memory();
     if (e == hipSuccess) e = hipMemsetAsync(t->hub_bits, 0, hubs * words * sizeof(uint32_t), ctx->stream);
     if (e == hipSuccess) e = agis::launch_hub_bits(g->g, t->hub_slot, words, t->hub_bits, ctx->stream);
@@ -441,13 +547,13 @@ hipError_t build_hub_bitmaps(agis_ctx* ctx, const agis_graph* g, agis_tables* t)
     uint64_t H = 0;
     uint32_t* pair_hub = nullptr;
     if (e == hipSuccess) {
-        e = hipMalloc(&t->pair_slot, n * sizeof(int32_t));
+        e = ctx->pool->alloc(&t->pair_slot, n * sizeof(int32_t));
         if (e == hipErrorOutOfMemory) {
             (void)hipGetLastError();
             t->pair_slot = nullptr;
             e = hipSuccess;
-            (void)hipFree(flags);
-            (void)hipFree(prefix);
+            ctx->pool->free(flags);
+            ctx->pool->free(prefix);
             return e;  // bitmaps without the pair-hub table
         }
     }
@@ -455,17 +561,17 @@ hipError_t build_hub_bitmaps(agis_ctx* ctx, const agis_graph* g, agis_tables* t)
     if (e == hipSuccess) e = hipMemcpyAsync(&H, prefix + n, sizeof(uint64_t), hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e == hipSuccess && H >= 2) {
-        e = hipMalloc(&pair_hub, H * sizeof(uint32_t));
-        if (e == hipSuccess) e = hipMalloc(&t->pair_count, H * H * sizeof(uint32_t));
-        if (e == hipSuccess) e = hipMalloc(&t->pair_quart, H * H * (agis::kPairParts - 1) * sizeof(uint32_t));
+        e = ctx->pool->alloc(&pair_hub, H * sizeof(uint32_t));
+        if (e == hipSuccess) e = ctx->pool->alloc(&t->pair_count, H * H * sizeof(uint32_t));
+        if (e == hipSuccess) e = ctx->pool->alloc(&t->pair_quart, H * H * (agis::kPairParts - 1) * sizeof(uint32_t));
         if (e == hipSuccess)
             e = agis::launch_pair_counts(ctx, g->g, g->max_deg, t->pair_slot, H, pair_hub, t->pair_count,
                                          t->pair_quart);
         if (e == hipErrorOutOfMemory) {
             // no room for the pair-hub table: keep the bitmaps without it
             (void)hipGetLastError();
-            if (t->pair_count) (void)hipFree(t->pair_count);
-            if (t->pair_quart) (void)hipFree(t->pair_quart);
+            ctx->pool->free(t->pair_count);
+            ctx->pool->free(t->pair_quart);
             t->pair_count = nullptr;
             t->pair_quart = nullptr;
             H = 0;
@@ -477,9 +583,9 @@ hipError_t build_hub_bitmaps(agis_ctx* ctx, const agis_graph* g, agis_tables* t)
         }
         if (e == hipSuccess && t->pair_count) e = build_core_pairs(ctx, g, t, pair_hub, H);
     }
-    if (pair_hub) (void)hipFree(pair_hub);
-    if (flags) (void)hipFree(flags);
-    if (prefix) (void)hipFree(prefix);
+    ctx->pool->free(pair_hub);
+    ctx->pool->free(flags);
+    ctx->pool->free(prefix);
     return e;
 }
 
@@ -504,7 +610,7 @@ void* table_alloc(agis_ctx* ctx, TableCache* cache, bool keep, uint64_t nbytes) 
             p = cache->alloc(nbytes);
             if (p) return p;
         } else {
-            if (hipMalloc(&p, nbytes) == hipSuccess) return p;
+            if (ctx->pool->alloc(&p, nbytes) == hipSuccess) return p;
             (void)hipGetLastError();
         }
         if (attempt > 0 || !ctx->d_scratch) break;
@@ -539,6 +645,7 @@ int prepare(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, const agis
         step1 == (AGIS_RUN_STEP1_BLOCKS | AGIS_RUN_STEP1_FULL))
         return fail(ctx, AGIS_E_INVALID_ARG, "unknown run flag");
     if (params->terms > AGIS_TERMS_F1_I1) return fail(ctx, AGIS_E_INVALID_ARG, "unknown term set");
+    st->ctx = out->ctx = ctx;
     DevPlan& hp = out->hp;
     std::memset(&hp, 0, sizeof(hp));
     hp.k = out->plan.k;
@@ -569,8 +676,11 @@ int prepare(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, const agis
         // the memory of kept tables goes back to this call's tables and the
         // sampler's scratch, whose size sets the number of waves
         size_t free_b = 0, total_b = 0;
-        if (cache->bytes && hipMemGetInfo(&free_b, &total_b) == hipSuccess && free_b < kTableCacheFreeFloor)
+        if ((cache->bytes || ctx->pool->kept()) && hipMemGetInfo(&free_b, &total_b) == hipSuccess &&
+            free_b < kTableCacheFreeFloor) {
             cache->evict(~0ull);
+            ctx->pool->trim();
+        }
     }
     // per-vertex log weights of step i (shared by the call), nullptr beyond
     // the budget
@@ -603,7 +713,7 @@ int prepare(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, const agis
             e = agis::launch_step_log_weights(*t, g->g.n, hp.b[i], hp.f1[i], hp.ie[i], hp.f2[i], hp.lt[i], buf,
                                               ctx->stream);
         if (e != hipSuccess) {
-            if (buf && !st->arena) (void)hipFree(buf);
+            if (buf && !st->arena) ctx->pool->free(buf);
             step_rc = fail(ctx, e == hipErrorOutOfMemory ? AGIS_E_OOM : AGIS_E_HIP,
                            std::string("step weight table: ") + hipGetErrorString(e));
             return nullptr;
@@ -650,17 +760,17 @@ int prepare(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, const agis
                 const uint64_t lbytes = (2 * g->g.n + 2) * sizeof(uint32_t);
                 if (cache) {
                     if (!cache->long_rows)
-                        AGIS_HIP(ctx, hipMalloc(&cache->long_rows, lbytes), "allocate row lists");
+                        AGIS_HIP(ctx, ctx->pool->alloc(&cache->long_rows, lbytes), "allocate row lists");
                     st->long_rows = cache->long_rows;
                 } else if (!st->long_rows) {
-                    AGIS_HIP(ctx, hipMalloc(&st->long_rows, lbytes), "allocate row lists");
+                    AGIS_HIP(ctx, ctx->pool->alloc(&st->long_rows, lbytes), "allocate row lists");
                 }
                 const uint64_t nbytes = g->g.nnz * sizeof(uint64_t);
                 buf = (uint64_t*)table_alloc(ctx, cache, keep, nbytes);
                 if (!buf) return fail(ctx, AGIS_E_OOM, "allocate row pick table: out of device memory");
                 const hipError_t e = agis::launch_rowtab(ctx, g->g, sw, buf, st->long_rows);
                 if (e != hipSuccess) {
-                    (void)hipFree(buf);
+                    ctx->pool->free(buf);
                     return hip_fail(ctx, e, "row pick table");
                 }
                 st->rows.push_back(StepTables::RowEntry{hp.b[i], hp.f1[i], hp.ie[i], hp.f2[i], lt, buf, keep});
@@ -711,8 +821,8 @@ int prepare(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, const agis
                                                                  (uint64_t*)cbp)
                                         : hipErrorOutOfMemory;
             if (e != hipSuccess) {
-                if (clm) (void)hipFree(clm);
-                if (cbp) (void)hipFree(cbp);
+                ctx->pool->free(clm);
+                ctx->pool->free(cbp);
                 if (e != hipErrorOutOfMemory) return hip_fail(ctx, e, "core-pair pick table");
                 (void)hipGetLastError();  // no room: the step walks the lists
                 continue;
@@ -788,7 +898,7 @@ int prepare(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, const agis
             if (!st->arena) {
                 rc = alloc1((void**)&guide, gbytes, "allocate first-step guide");
                 if (rc != AGIS_OK) {
-                    if (keep1) (void)hipFree(blk);
+                    if (keep1) ctx->pool->free(blk);
                     return rc;
                 }
             }
@@ -799,8 +909,8 @@ int prepare(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, const agis
         }
         if (e != hipSuccess) {
             if (keep1) {
-                (void)hipFree(blk);
-                if (guide) (void)hipFree(guide);
+                ctx->pool->free(blk);
+                ctx->pool->free(guide);
             }
             return hip_fail(ctx, e, "first-step block table");
         }
@@ -837,7 +947,7 @@ int prepare(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, const agis
             rc = alloc1((void**)&q1, g->g.n * sizeof(uint32_t), "allocate first-step weights");
             if (rc == AGIS_OK) rc = alloc1((void**)&pre, g->g.n * sizeof(uint64_t), "allocate first-step prefix");
             if (rc != AGIS_OK) {
-                if (q1) (void)hipFree(q1);
+                ctx->pool->free(q1);
                 return rc;
             }
         }
@@ -859,8 +969,8 @@ int prepare(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, const agis
                 rc = alloc1((void**)&guide, gbytes, "allocate first-step guide");
                 if (rc != AGIS_OK) {
                     if (keep1) {
-                        (void)hipFree(q1);
-                        (void)hipFree(pre);
+                        ctx->pool->free(q1);
+                        ctx->pool->free(pre);
                     }
                     return rc;
                 }
@@ -872,9 +982,9 @@ int prepare(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, const agis
         }
         if (e != hipSuccess) {
             if (keep1) {
-                (void)hipFree(q1);
-                (void)hipFree(pre);
-                if (guide) (void)hipFree(guide);
+                ctx->pool->free(q1);
+                ctx->pool->free(pre);
+                ctx->pool->free(guide);
             }
             return hip_fail(ctx, e, "first-step table");
         }
@@ -1131,7 +1241,7 @@ int run_device_eps(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, std
         if (ctx->d_eps) (void)hipFree(ctx->d_eps);
         ctx->d_eps = nullptr;
         ctx->eps_bytes = 0;
-        AGIS_HIP(ctx, hipMalloc(&ctx->d_eps, need), "allocate run-to-eps buffers");
+        AGIS_HIP(ctx, agis::ctx_malloc(ctx, &ctx->d_eps, need), "allocate run-to-eps buffers");
         ctx->eps_bytes = need;
     }
     char* base = (char*)ctx->d_eps;
@@ -1340,6 +1450,7 @@ void agis_destroy(agis_ctx* ctx) {
     if (ctx->d_blocksums) (void)hipFree(ctx->d_blocksums);
     if (ctx->d_eps) (void)hipFree(ctx->d_eps);
     if (ctx->h_cancel) (void)hipHostFree((void*)ctx->h_cancel);
+    ctx->pool->close();
     if (ctx->ev_start) (void)hipEventDestroy(ctx->ev_start);
     if (ctx->ev_stop) (void)hipEventDestroy(ctx->ev_stop);
     delete ctx;
@@ -1363,6 +1474,7 @@ int agis_release_scratch(agis_ctx* ctx) {
     ctx->xout_cap = 0;
     ctx->partials_cap = 0;
     ctx->eps_bytes = 0;
+    ctx->pool->trim();
     return AGIS_OK;
 }
 
@@ -1417,8 +1529,11 @@ int agis_load_csr(agis_ctx* ctx, const uint64_t* off, const uint32_t* nbr, uint6
 
 void agis_graph_destroy(agis_graph* g) {
     if (!g) return;
-    if (g->own_off) (void)hipFree(g->own_off);
-    if (g->own_nbr) (void)hipFree(g->own_nbr);
+    if (g->own_off || g->own_nbr) {
+        sync_device(g->device);
+        g->pool->free(g->own_off);
+        g->pool->free(g->own_nbr);
+    }
     delete g;
 }
 
@@ -1432,14 +1547,16 @@ int agis_orient(agis_ctx* ctx, const agis_graph* g, agis_graph** out) {
     if (!o) return fail(ctx, AGIS_E_OOM, "host allocation");
     o->ctx = ctx;
     o->parent = g;
+    o->pool = ctx->pool;
+    o->device = ctx->device;
     uint32_t* outdeg = nullptr;
-    hipError_t e = hipMalloc(&outdeg, n * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMalloc(&o->own_off, (n + 1) * sizeof(uint64_t));
+    hipError_t e = ctx->pool->alloc(&outdeg, n * sizeof(uint32_t));
+    if (e == hipSuccess) e = ctx->pool->alloc(&o->own_off, (n + 1) * sizeof(uint64_t));
     if (e == hipSuccess) e = agis::launch_orient_offsets(ctx, g->g, outdeg, o->own_off);
     uint64_t nnz = 0;
     if (e == hipSuccess) e = hipMemcpyAsync(&nnz, o->own_off + n, sizeof(uint64_t), hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    if (e == hipSuccess) e = hipMalloc(&o->own_nbr, (nnz ? nnz : 1) * sizeof(uint32_t));
+    if (e == hipSuccess) e = ctx->pool->alloc(&o->own_nbr, (nnz ? nnz : 1) * sizeof(uint32_t));
     if (e == hipSuccess) e = agis::launch_orient_fill(g->g, o->own_off, o->own_nbr, ctx->stream);
     uint32_t* d_max = (uint32_t*)ctx->d_small;
     uint32_t maxd = 0;
@@ -1448,7 +1565,8 @@ int agis_orient(agis_ctx* ctx, const agis_graph* g, agis_graph** out) {
     if (e == hipSuccess) e = agis::launch_max_degree(o->g, d_max, ctx->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(&maxd, d_max, sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    if (outdeg) (void)hipFree(outdeg);
+    if (e != hipSuccess) (void)hipStreamSynchronize(ctx->stream);
+    ctx->pool->free(outdeg);
     if (e != hipSuccess) {
         agis_graph_destroy(o);
         return hip_fail(ctx, e, "orient graph");
@@ -1476,14 +1594,19 @@ int agis_build_proposal_tables(agis_ctx* ctx, const agis_graph* g, uint64_t cv_s
     AGIS_HIP(ctx, hipSetDevice(ctx->device), "set device");
     agis_tables* t = new (std::nothrow) agis_tables();
     if (t) t->cache = new (std::nothrow) TableCache();
-    if (!t) return fail(ctx, AGIS_E_OOM, "host allocation");
+    if (!t || !t->cache) {
+        delete t;
+        return fail(ctx, AGIS_E_OOM, "host allocation");
+    }
     t->ctx = ctx;
+    t->pool = t->cache->pool = ctx->pool;
+    t->device = ctx->device;
     t->graph = g;
     const uint64_t n = g->g.n;
-    hipError_t e = hipMalloc(&t->rec, n * sizeof(uint4));
-    if (e == hipSuccess) e = hipMalloc(&t->s2, n * sizeof(uint64_t));
-    if (e == hipSuccess) e = hipMalloc(&t->hits, n * sizeof(uint64_t));
-    if (e == hipSuccess) e = hipMalloc(&t->trials, n * sizeof(uint64_t));
+    hipError_t e = ctx->pool->alloc(&t->rec, n * sizeof(uint4));
+    if (e == hipSuccess) e = ctx->pool->alloc(&t->s2, n * sizeof(uint64_t));
+    if (e == hipSuccess) e = ctx->pool->alloc(&t->hits, n * sizeof(uint64_t));
+    if (e == hipSuccess) e = ctx->pool->alloc(&t->trials, n * sizeof(uint64_t));
     if (e == hipSuccess)
         e = agis::launch_build_tables(g->g, g->parent ? g->parent->g : g->g, t->rec, t->s2, t->hits, t->trials,
                                       (uint32_t)cv_seed, (uint32_t)(cv_seed >> 32), lc_min_q16, exact_cv ? 1 : 0,
@@ -1500,18 +1623,12 @@ int agis_build_proposal_tables(agis_ctx* ctx, const agis_graph* g, uint64_t cv_s
 
 void agis_tables_destroy(agis_tables* t) {
     if (!t) return;
+    sync_device(t->device);
     delete t->cache;
-    if (t->rec) (void)hipFree(t->rec);
-    if (t->s2) (void)hipFree(t->s2);
-    if (t->hits) (void)hipFree(t->hits);
-    if (t->trials) (void)hipFree(t->trials);
-    if (t->hub_bits) (void)hipFree(t->hub_bits);
-    if (t->hub_slot) (void)hipFree(t->hub_slot);
-    if (t->pair_slot) (void)hipFree(t->pair_slot);
-    if (t->pair_count) (void)hipFree(t->pair_count);
-    if (t->pair_quart) (void)hipFree(t->pair_quart);
-    for (void* q : {(void*)t->core_slot, (void*)t->core_start, (void*)t->core_len, (void*)t->core_nbr})
-        if (q) (void)hipFree(q);
+    for (void* q : {(void*)t->rec, (void*)t->s2, (void*)t->hits, (void*)t->trials, (void*)t->hub_bits,
+                    (void*)t->hub_slot, (void*)t->pair_slot, (void*)t->pair_count, (void*)t->pair_quart,
+                    (void*)t->core_slot, (void*)t->core_start, (void*)t->core_len, (void*)t->core_nbr})
+        t->pool->free(q);
     delete t;
 }
 

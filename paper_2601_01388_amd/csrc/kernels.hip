@@ -932,7 +932,7 @@ hipError_t launch_orient_offsets(agis_ctx* ctx, const DevGraph& g, uint32_t* out
         if (ctx->d_blocksums) (void)hipFree(ctx->d_blocksums);
         ctx->d_blocksums = nullptr;
         ctx->blocksums_cap = 0;
-        hipError_t e = hipMalloc(&ctx->d_blocksums, ntiles * sizeof(uint64_t));
+        hipError_t e = ctx_malloc(ctx, (void**)&ctx->d_blocksums, ntiles * sizeof(uint64_t));
         if (e != hipSuccess) return e;
         ctx->blocksums_cap = ntiles;
     }
@@ -991,7 +991,7 @@ hipError_t launch_hub_slots(agis_ctx* ctx, const DevGraph& g, uint32_t min_deg, 
         if (ctx->d_blocksums) (void)hipFree(ctx->d_blocksums);
         ctx->d_blocksums = nullptr;
         ctx->blocksums_cap = 0;
-        hipError_t e = hipMalloc(&ctx->d_blocksums, ntiles * sizeof(uint64_t));
+        hipError_t e = ctx_malloc(ctx, (void**)&ctx->d_blocksums, ntiles * sizeof(uint64_t));
         if (e != hipSuccess) return e;
         ctx->blocksums_cap = ntiles;
     }
@@ -1188,7 +1188,7 @@ __global__ __launch_bounds__(kPairThreads) void k_pair_counts(DevGraph g, const 
 
 // The row scratch of panels over `hubs` hubs: *lw words per vertex, at most
 // kPairRowWords, fewer for few hubs or little memory.
-static hipError_t alloc_rows(const DevGraph& g, uint64_t hubs, uint32_t* lw, uint32_t** rows) {
+static hipError_t alloc_rows(agis_ctx* ctx, const DevGraph& g, uint64_t hubs, uint32_t* lw, uint32_t** rows) {
     *lw = kPairRowWords;
     while (*lw > 1 && 32ull * (*lw / 2) >= hubs) *lw /= 2;
     size_t free_b = 0, total_b = 0;
@@ -1196,7 +1196,7 @@ static hipError_t alloc_rows(const DevGraph& g, uint64_t hubs, uint32_t* lw, uin
     if (hipMemGetInfo(&free_b, &total_b) == hipSuccess) budget = std::min<uint64_t>(budget, (uint64_t)free_b / 2);
     while (*lw > 1 && g.n * *lw * sizeof(uint32_t) > budget) *lw /= 2;
     for (;; *lw /= 2) {
-        const hipError_t e = hipMalloc(rows, g.n * *lw * sizeof(uint32_t));
+        const hipError_t e = ctx->pool->alloc(rows, g.n * *lw * sizeof(uint32_t));
         if (e != hipErrorOutOfMemory || *lw == 1) return e;
         (void)hipGetLastError();
     }
@@ -1216,9 +1216,9 @@ hipError_t launch_pair_counts(agis_ctx* ctx, const DevGraph& g, uint32_t max_deg
     hipStream_t st = ctx->stream;
     uint32_t lw = 0;
     uint32_t *hub = nullptr, *rows = nullptr;
-    hipError_t e = hipMalloc(&hub, H * sizeof(uint32_t));
+    hipError_t e = ctx->pool->alloc(&hub, H * sizeof(uint32_t));
     if (e != hipSuccess) return e;
-    e = alloc_rows(g, H, &lw, &rows);
+    e = alloc_rows(ctx, g, H, &lw, &rows);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_pair_hubs, dim3(grid_for(g.n, 256)), dim3(256), 0, st, pair_slot, g.n, hub);
         hipLaunchKernelGGL(k_pair_rank, dim3(grid_for(H, 256)), dim3(256), 0, st, g, hub, H, pair_hub, pair_slot);
@@ -1240,8 +1240,8 @@ hipError_t launch_pair_counts(agis_ctx* ctx, const DevGraph& g, uint32_t max_deg
         const hipError_t es = hipStreamSynchronize(st);  // the rows are freed below
         if (e == hipSuccess) e = es;
     }
-    if (rows) (void)hipFree(rows);
-    (void)hipFree(hub);
+    ctx->pool->free(rows);
+    ctx->pool->free(hub);
     return e;
 }
 
@@ -1440,7 +1440,7 @@ hipError_t launch_core_pairs(agis_ctx* ctx, const DevGraph& g, const uint32_t* p
                        core_slot, core_start, core_len);
     uint32_t lw = 0;
     uint32_t* rows = nullptr;
-    hipError_t e = alloc_rows(g, C, &lw, &rows);
+    hipError_t e = alloc_rows(ctx, g, C, &lw, &rows);
     const uint64_t panel = 32ull * lw;
     for (uint64_t base = 0; base + 1 < C && e == hipSuccess; base += panel) {
         e = fill_rows(g, pair_hub, base, std::min<uint64_t>(panel, C - base), lw, rows, st);
@@ -1451,7 +1451,7 @@ hipError_t launch_core_pairs(agis_ctx* ctx, const DevGraph& g, const uint32_t* p
     }
     const hipError_t es = hipStreamSynchronize(st);  // the rows are freed below
     if (e == hipSuccess) e = es;
-    if (rows) (void)hipFree(rows);
+    ctx->pool->free(rows);
     return e;
 }
 
@@ -1502,7 +1502,7 @@ hipError_t build_step1(agis_ctx* ctx, const agis_graph& g, const agis_tables& t,
         if (ctx->blocksums_cap < ntiles) {
             if (ctx->d_blocksums) (void)hipFree(ctx->d_blocksums);
             ctx->d_blocksums = nullptr;
-            e = hipMalloc(&ctx->d_blocksums, ntiles * sizeof(uint64_t));
+            e = ctx_malloc(ctx, (void**)&ctx->d_blocksums, ntiles * sizeof(uint64_t));
             if (e != hipSuccess) return e;
             ctx->blocksums_cap = ntiles;
         }
@@ -3615,7 +3615,7 @@ int plan_sample_launch(agis_ctx* ctx, const agis_graph& g, uint64_t max_slots, u
         if (ctx->d_scratch) (void)hipFree(ctx->d_scratch);
         ctx->d_scratch = nullptr;
         ctx->scratch_bytes = 0;
-        if (hipMalloc(&ctx->d_scratch, bytes) != hipSuccess) {
+        if (ctx_malloc(ctx, &ctx->d_scratch, bytes) != hipSuccess) {
             *err = "could not allocate sampler scratch";
             return AGIS_E_OOM;
         }
@@ -3625,7 +3625,7 @@ int plan_sample_launch(agis_ctx* ctx, const agis_graph& g, uint64_t max_slots, u
         if (ctx->d_partials) (void)hipFree(ctx->d_partials);
         ctx->d_partials = nullptr;
         ctx->partials_cap = 0;
-        if (hipMalloc(&ctx->d_partials, (size_t)L->max_tiles * sizeof(Partial)) != hipSuccess) {
+        if (ctx_malloc(ctx, (void**)&ctx->d_partials, (size_t)L->max_tiles * sizeof(Partial)) != hipSuccess) {
             *err = "could not allocate partials";
             return AGIS_E_OOM;
         }
@@ -3635,7 +3635,7 @@ int plan_sample_launch(agis_ctx* ctx, const agis_graph& g, uint64_t max_slots, u
         if (ctx->d_xout) (void)hipFree(ctx->d_xout);
         ctx->d_xout = nullptr;
         ctx->xout_cap = 0;
-        if (hipMalloc(&ctx->d_xout, (size_t)max_slots * sizeof(double)) != hipSuccess) {
+        if (ctx_malloc(ctx, (void**)&ctx->d_xout, (size_t)max_slots * sizeof(double)) != hipSuccess) {
             *err = "could not allocate the sample-weight buffer";
             return AGIS_E_OOM;
         }

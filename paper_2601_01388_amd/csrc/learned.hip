@@ -522,7 +522,7 @@ int agis_features(agis_ctx* ctx, const agis_tables* t, float* feats) {
     if (g.n > UINT32_MAX) return lfail(ctx, AGIS_E_INVALID_ARG, "features: more than 2^32 - 1 vertices");
     // list of the vertices of degree above the per-lane limit, and its length
     uint32_t* big = nullptr;
-    LHIP(ctx, hipMalloc(&big, (size_t)(g.n + 1) * sizeof(uint32_t)), "allocate feature list");
+    LHIP(ctx, ctx->pool->alloc(&big, (size_t)(g.n + 1) * sizeof(uint32_t)), "allocate feature list");
     uint32_t* nbig = big + g.n;
     hipError_t e = hipMemsetAsync(nbig, 0, sizeof(uint32_t), ctx->stream);
     const uint64_t groups = (g.n + 63) / 64;
@@ -539,7 +539,7 @@ int agis_features(agis_ctx* ctx, const agis_tables* t, float* feats) {
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    (void)hipFree(big);
+    ctx->pool->free(big);
     LHIP(ctx, e, "features");
     return AGIS_OK;
 }
@@ -556,10 +556,10 @@ int agis_learn_targets(agis_ctx* ctx, const agis_graph* g, const agis_tables* t,
     const uint64_t chunk = 1ull << 20;
     uint64_t* d_idx = nullptr;
     agis::Record* d_rec = nullptr;
-    LHIP(ctx, hipMalloc(&d_idx, chunk * sizeof(uint64_t)), "allocate indices");
-    hipError_t e = hipMalloc(&d_rec, chunk * sizeof(agis::Record));
+    LHIP(ctx, ctx->pool->alloc(&d_idx, chunk * sizeof(uint64_t)), "allocate indices");
+    hipError_t e = ctx->pool->alloc(&d_rec, chunk * sizeof(agis::Record));
     if (e != hipSuccess) {
-        (void)hipFree(d_idx);
+        ctx->pool->free(d_idx);
         return lfail(ctx, AGIS_E_OOM, "allocate records");
     }
     std::vector<uint64_t> idx(chunk);
@@ -579,8 +579,8 @@ int agis_learn_targets(agis_ctx* ctx, const agis_graph* g, const agis_tables* t,
         e = hipStreamSynchronize(ctx->stream);
         if (e != hipSuccess) rc = lfail(ctx, AGIS_E_HIP, std::string("targets: ") + hipGetErrorString(e));
     }
-    (void)hipFree(d_idx);
-    (void)hipFree(d_rec);
+    ctx->pool->free(d_idx);
+    ctx->pool->free(d_rec);
     return rc;
 }
 
@@ -656,8 +656,8 @@ int agis_mlp_grad(agis_ctx* ctx, const float* params, const float* feats, const 
     const uint64_t tiles = (rows + agis::kTile - 1) / agis::kTile;
     float* partial = nullptr;
     float* lpart = nullptr;
-    LHIP(ctx, hipMalloc(&partial, tiles * kMlpParams * sizeof(float)), "allocate gradient partials");
-    hipError_t e = hipMalloc(&lpart, tiles * sizeof(float));
+    LHIP(ctx, ctx->pool->alloc(&partial, tiles * kMlpParams * sizeof(float)), "allocate gradient partials");
+    hipError_t e = ctx->pool->alloc(&lpart, tiles * sizeof(float));
     if (e == hipSuccess) {
         hipLaunchKernelGGL(agis::k_mlp_grad, dim3((unsigned)tiles), dim3(agis::kGradThreads), 0, ctx->stream, params,
                            feats, vtx, cls, target, weight, nullptr, rows, 1.0f / weight_sum, partial, lpart);
@@ -666,8 +666,8 @@ int agis_mlp_grad(agis_ctx* ctx, const float* params, const float* feats, const 
         e = hipGetLastError();
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     }
-    (void)hipFree(partial);
-    if (lpart) (void)hipFree(lpart);
+    ctx->pool->free(partial);
+    ctx->pool->free(lpart);
     LHIP(ctx, e, "mlp gradient");
     return AGIS_OK;
 }
@@ -685,12 +685,12 @@ int agis_mlp_train(agis_ctx* ctx, float* params, const float* feats, const uint3
     LHIP(ctx, hipMemcpy(w.data(), weight, rows * sizeof(float), hipMemcpyDeviceToHost), "read weights");
     float *partial = nullptr, *lpart = nullptr, *m1 = nullptr, *m2 = nullptr, *loss = nullptr;
     uint32_t* order = nullptr;
-    hipError_t e = hipMalloc(&partial, tiles * kMlpParams * sizeof(float));
-    if (e == hipSuccess) e = hipMalloc(&lpart, tiles * sizeof(float));
-    if (e == hipSuccess) e = hipMalloc(&m1, kMlpParams * sizeof(float));
-    if (e == hipSuccess) e = hipMalloc(&m2, kMlpParams * sizeof(float));
-    if (e == hipSuccess) e = hipMalloc(&loss, sizeof(float));
-    if (e == hipSuccess) e = hipMalloc(&order, rows * sizeof(uint32_t));
+    hipError_t e = ctx->pool->alloc(&partial, tiles * kMlpParams * sizeof(float));
+    if (e == hipSuccess) e = ctx->pool->alloc(&lpart, tiles * sizeof(float));
+    if (e == hipSuccess) e = ctx->pool->alloc(&m1, kMlpParams * sizeof(float));
+    if (e == hipSuccess) e = ctx->pool->alloc(&m2, kMlpParams * sizeof(float));
+    if (e == hipSuccess) e = ctx->pool->alloc(&loss, sizeof(float));
+    if (e == hipSuccess) e = ctx->pool->alloc(&order, rows * sizeof(uint32_t));
     if (e == hipSuccess) e = hipMemsetAsync(m1, 0, kMlpParams * sizeof(float), ctx->stream);
     if (e == hipSuccess) e = hipMemsetAsync(m2, 0, kMlpParams * sizeof(float), ctx->stream);
     std::vector<uint32_t> perm(rows);
@@ -731,7 +731,7 @@ int agis_mlp_train(agis_ctx* ctx, float* params, const float* feats, const uint3
     }
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     for (void* q : {(void*)partial, (void*)lpart, (void*)m1, (void*)m2, (void*)loss, (void*)order})
-        if (q) (void)hipFree(q);
+        ctx->pool->free(q);
     LHIP(ctx, e, "mlp training");
     return AGIS_OK;
 }

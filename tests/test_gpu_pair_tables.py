@@ -57,3 +57,34 @@ def test_pair_tables_against_oracle(sess, hubs):
             assert abs(r.estimate - st.mean) <= 1e-9 * abs(st.mean), (hubs, name, mode)
     T.close()
     G.close()
+
+
+def test_recycled_buffers_and_handles_that_outlive_their_context():
+    """Tables built from buffers of destroyed ones hold nothing of them, the
+    kept memory goes back on request, and tables destroyed after their
+    context give their memory back."""
+    import torch
+    from paper_2601_01388_amd.session import Session
+    s = Session(0)
+    big, small = _hub_graph(2100, 9000, seed=1), _hub_graph(2050, 8800, seed=2)
+    idx = np.arange(500, dtype=np.uint64)
+    p = synth.named_pattern("house")
+    for g in (big, small, big):
+        G = s.graph(g.off, g.nbr)
+        T = s.tables(G, cv_seed=1)
+        smp = oracle.Sampler(g, oracle.Tables(g, cv_seed=1), compile_pattern(p.k, p.edges, mode="switch"), seed=5)
+        got, ref = s.dump(G, T, p, 5, idx, mode="switch", rowtab="on"), smp.records(idx)
+        for f in ("v", "num", "den", "x", "steps", "fail_step"):
+            assert np.array_equal(got[f], ref[f]), f
+        T.close()
+        G.close()
+    kept = torch.cuda.mem_get_info()[0]
+    s.release_scratch()
+    assert torch.cuda.mem_get_info()[0] > kept
+    G = s.graph(big.off, big.nbr)
+    T = s.tables(G, cv_seed=1)
+    s.close()
+    held = torch.cuda.mem_get_info()[0]
+    T.close()
+    G.close()
+    assert torch.cuda.mem_get_info()[0] > held
