@@ -91,29 +91,63 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
     return ((uint64_t)uniform_u32((uint32_t)(v >> 32)) << 32) | uniform_u32((uint32_t)v);
 }
 
-__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
+// Wave-wide scans and reductions by DPP row moves: a shift within rows of 16
+// lanes costs a vector operation, where a shuffle through the LDS crossbar
+// (ds_bpermute) costs its round trip, some 100 cycles and more under load,
+// at each of the six steps.  The sampler makes several of these per step of
+// a sample, one after the other.  All 64 lanes must be active.
+// Lane i receives lane i - 1, i - 2, i - 4 or i - 8 of its row (row_shr), or
+// rows 1 and 3 (2 and 3) the last lane of row 0 and 2 (of row 1)
+// (row_bcast); the other lanes receive `none`.
+constexpr int kDppShr1 = 0x111, kDppShr2 = 0x112, kDppShr4 = 0x114, kDppShr8 = 0x118;
+constexpr int kDppBcast15 = 0x142, kDppBcast31 = 0x143;
+
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t none, uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, kCtrl, kRows, 0xF, false);
 }
 
-__device__ __forceinline__ int32_t wave_max_i32(int32_t v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        int32_t w = __shfl_xor(v, o, kWave);
-        v = w > v ? w : v;
-    }
-    return v;
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint64_t dpp_u64(uint64_t none, uint64_t v) {
+    const uint32_t lo = dpp_u32<kCtrl, kRows>((uint32_t)none, (uint32_t)v);
+    const uint32_t hi = dpp_u32<kCtrl, kRows>((uint32_t)(none >> 32), (uint32_t)(v >> 32));
+    return ((uint64_t)hi << 32) | lo;
 }
 
 __device__ __forceinline__ uint64_t wave_incl_scan_u64(uint64_t v) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        uint64_t w = __shfl_up(v, d, kWave);
-        if (lane >= d) v += w;
-    }
+    v += dpp_u64<kDppShr1, 0xF>(0ull, v);
+    v += dpp_u64<kDppShr2, 0xF>(0ull, v);
+    v += dpp_u64<kDppShr4, 0xF>(0ull, v);
+    v += dpp_u64<kDppShr8, 0xF>(0ull, v);
+    v += dpp_u64<kDppBcast15, 0xA>(0ull, v);
+    v += dpp_u64<kDppBcast31, 0xC>(0ull, v);
     return v;
+}
+
+// (the sum, maximum and minimum come out wave-uniform)
+__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) { return readlane_u64(wave_incl_scan_u64(v), kWave - 1); }
+
+__device__ __forceinline__ int32_t wave_max_i32(int32_t v) {
+    auto step = [&](uint32_t w) { v = (int32_t)w > v ? (int32_t)w : v; };
+    const uint32_t none = 0x80000000u;
+    step(dpp_u32<kDppShr1, 0xF>(none, (uint32_t)v));
+    step(dpp_u32<kDppShr2, 0xF>(none, (uint32_t)v));
+    step(dpp_u32<kDppShr4, 0xF>(none, (uint32_t)v));
+    step(dpp_u32<kDppShr8, 0xF>(none, (uint32_t)v));
+    step(dpp_u32<kDppBcast15, 0xA>(none, (uint32_t)v));
+    step(dpp_u32<kDppBcast31, 0xC>(none, (uint32_t)v));
+    return (int32_t)readlane_u32((uint32_t)v, kWave - 1);
+}
+
+__device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
+    auto step = [&](uint64_t w) { v = w < v ? w : v; };
+    step(dpp_u64<kDppShr1, 0xF>(~0ull, v));
+    step(dpp_u64<kDppShr2, 0xF>(~0ull, v));
+    step(dpp_u64<kDppShr4, 0xF>(~0ull, v));
+    step(dpp_u64<kDppShr8, 0xF>(~0ull, v));
+    step(dpp_u64<kDppBcast15, 0xA>(~0ull, v));
+    step(dpp_u64<kDppBcast31, 0xC>(~0ull, v));
+    return readlane_u64(v, kWave - 1);
 }
 
 __device__ __forceinline__ uint64_t lanemask_lt() { return (1ull << lane_id()) - 1ull; }
@@ -1667,7 +1701,7 @@ __global__ __launch_bounds__(kRowtabThreads) void k_rowtab_mid(DevGraph g, const
             const uint64_t q = e < d ? (uint64_t)rowtab_q(lmax, l[u]) : 0ull;
             const uint64_t inc = wave_incl_scan_u64(q);
             if (e < d) pre[o + e] = carry + inc;
-            carry += __shfl(inc, kWave - 1, kWave);
+            carry += readlane_u64(inc, kWave - 1);
         }
     }
 }
@@ -2173,12 +2207,8 @@ __device__ __forceinline__ double sample_one(const DevGraph& g, const DevTables&
                 uint64_t left = __ballot(found);
                 uint64_t ans = ~0ull;
                 while (left) {
-                    uint64_t key = (left >> lane & 1ull) ? (((uint64_t)pos << 8) | (uint64_t)lane) : ~0ull;
-#pragma unroll
-                    for (int of = 32; of > 0; of >>= 1) {
-                        const uint64_t k2 = __shfl_xor(key, of, kWave);
-                        key = k2 < key ? k2 : key;
-                    }
+                    const uint64_t key =
+                        wave_min_u64((left >> lane & 1ull) ? (((uint64_t)pos << 8) | (uint64_t)lane) : ~0ull);
                     const int L = (int)(key & 0xFF);
                     const uint32_t e = (uint32_t)(key >> 8);
                     if (e > 0) mt.uni(pre + e - 1, 8);
@@ -2317,12 +2347,8 @@ __device__ __forceinline__ double sample_one(const DevGraph& g, const DevTables&
                 // it, in ascending order of position
                 uint64_t rr = r;
                 for (uint64_t left = __ballot(found); left;) {
-                    uint64_t key = (left >> lane & 1ull) ? (((uint64_t)pos << 8) | (uint64_t)lane) : ~0ull;
-#pragma unroll
-                    for (int of = 32; of > 0; of >>= 1) {
-                        const uint64_t k2 = __shfl_xor(key, of, kWave);
-                        key = k2 < key ? k2 : key;
-                    }
+                    const uint64_t key =
+                        wave_min_u64((left >> lane & 1ull) ? (((uint64_t)pos << 8) | (uint64_t)lane) : ~0ull);
                     const int L = (int)(key & 0xFF);
                     if (rr < readlane_u64(px, L)) break;
                     rr += readlane_u64(qx, L);
@@ -2435,12 +2461,7 @@ __device__ __forceinline__ double sample_one(const DevGraph& g, const DevTables&
                         others = uniform_u32(lists & ~(1u << ja) & ~(1u << jc));
                     } else {
                         // base = smallest degree, ties to the smallest position
-                        uint64_t key = ((uint64_t)my_d << 8) | (uint64_t)lane;
-#pragma unroll
-                        for (int o = 32; o > 0; o >>= 1) {
-                            uint64_t w2 = __shfl_xor(key, o, kWave);
-                            key = w2 < key ? w2 : key;
-                        }
+                        const uint64_t key = wave_min_u64(((uint64_t)my_d << 8) | (uint64_t)lane);
                         const int jb = (int)(key & 0xFF);
                         base = g.nbr + readlane_u64(my_o, jb);
                         db = readlane_u32(my_d, jb);
