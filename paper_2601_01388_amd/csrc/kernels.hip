@@ -3151,13 +3151,14 @@ __global__ __launch_bounds__(256) void k_sample_lanes(const LaunchDesc* __restri
 // Welford over the (up to) kReducePer weights xs[first ..] below lim, as one
 // thread of the fixed reduction tree.
 constexpr int kReducePer = 8;
-__device__ __forceinline__ Partial welford8(const double* __restrict__ xs, uint64_t first, uint64_t lim) {
+template <class Load>
+__device__ __forceinline__ Partial welford8(Load&& x_at, uint64_t first, uint64_t lim) {
 #pragma clang fp contract(off)
     Partial a{0.0, 0.0, 0.0, 0.0};
     for (int j = 0; j < kReducePer; ++j) {
         const uint64_t p = first + j;
         if (p >= lim) break;
-        const double x = xs[p];
+        const double x = x_at(p);
         a.n += 1.0;
         const double d = x - a.mean;
         a.mean += d / a.n;
@@ -3188,7 +3189,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce_x(const LaunchDesc* _
     const uint64_t t0 = (uint64_t)(blockIdx.x - S.tile_base) * kReduceTile;
     const uint64_t lim = S.count;
     const uint64_t first = t0 + (uint64_t)threadIdx.x * kReducePer;
-    Partial a = welford8(xs + S.base, first, lim);
+    Partial a = welford8([&](uint64_t i) { return xs[S.base + i]; }, first, lim);
     const int lane = lane_id();
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
@@ -3230,6 +3231,34 @@ __device__ __forceinline__ void st_dev(AGIS_GMEM unsigned long long* p, unsigned
 __device__ __forceinline__ void st_dev(AGIS_GMEM uint32_t* p, uint32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ double ld_dev_f64(const AGIS_GMEM double* p) {
+    return __longlong_as_double((long long)ld_dev((const AGIS_GMEM unsigned long long*)p));
+}
+__device__ __forceinline__ void st_dev_f64(AGIS_GMEM double* p, double v) {
+    st_dev((AGIS_GMEM unsigned long long*)p, (unsigned long long)__double_as_longlong(v));
+}
+__device__ __forceinline__ Partial ld_dev_partial(const AGIS_GMEM Partial* p) {
+    const AGIS_GMEM double* d = (const AGIS_GMEM double*)p;
+    return Partial{ld_dev_f64(d), ld_dev_f64(d + 1), ld_dev_f64(d + 2), ld_dev_f64(d + 3)};
+}
+__device__ __forceinline__ void st_dev_partial(AGIS_GMEM Partial* p, const Partial& v) {
+    AGIS_GMEM double* d = (AGIS_GMEM double*)p;
+    st_dev_f64(d, v.n);
+    st_dev_f64(d + 1, v.mean);
+    st_dev_f64(d + 2, v.m2);
+    st_dev_f64(d + 3, v.nonzero);
+}
+
+// Waits until this wave's accesses so far have been performed.  Everything
+// the waves of a run to epsilon share (weights, tile counts and partials,
+// pattern states) is written and read with device-scope accesses, which go
+// past the caches of one XCD, so waiting for them orders them: a later
+// device-scope access of this wave is seen by the others after them.  An
+// agent-scope fence would order as well, but also writes back and
+// invalidates the XCD's whole L2, taking the lists and bitmaps of every
+// other wave with it: with a fence per grab and tile the house to +-1% on
+// R-MAT-20 drew 7e7 samples/s, a third of its fixed-size rate.
+__device__ __forceinline__ void drain_dev() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Statistics of one tile (len <= kEpsTile weights from xs) by one wave, in
 // the fixed tree of k_reduce_x: 256 "threads" of 8 consecutive weights
@@ -3240,7 +3269,7 @@ __device__ __forceinline__ Partial reduce_tile_wave(const AGIS_GMEM double* xs, 
     Partial r{0.0, 0.0, 0.0, 0.0};
     for (int w = 0; w < kReduceThreads / kWave; ++w) {
         const uint64_t first = ((uint64_t)w * kWave + (uint64_t)lane) * kReducePer;
-        Partial a = welford8((const double*)xs, first, len);
+        Partial a = welford8([&](uint64_t i) { return ld_dev_f64(xs + i); }, first, len);
 #pragma unroll
         for (int o = 1; o < kWave; o <<= 1) {
             Partial b;
@@ -3281,17 +3310,17 @@ __device__ void merge_ready(const EpsDesc& E, uint32_t p) {
     AGIS_GMEM EpsPattern* P = E.pat + p;
     const uint64_t rtiles = E.ring_samples / kEpsTile;
     for (;;) {
-        // A full fence before looking: the wave that just published a tile
-        // (and fails to take the token) and the holder that just gave the
-        // token up (and looks again) cannot both miss each other.
-        __threadfence();
+        // Everything published before looking: the wave that just published
+        // a tile (and fails to take the token) and the holder that just gave
+        // the token up (and looks again) cannot both miss each other.
+        drain_dev();
         uint64_t m = ld_dev(&P->merged);
         uint64_t tm = m / kEpsTile;
         if (ld_dev(&P->stop)) return;
         if (ld_dev(E.tile_ready + (uint64_t)p * rtiles + (tm & (rtiles - 1))) != tm + 1) return;
         if (atomicCAS(&P->owner, 0u, 1u) != 0u) return;
-        __threadfence();
-        Partial acc = P->acc;
+        drain_dev();
+        Partial acc = ld_dev_partial(&P->acc);
         const uint64_t budget = P->budget, check = P->check;
         bool stopped = false;
         for (;;) {
@@ -3307,27 +3336,27 @@ __device__ void merge_ready(const EpsDesc& E, uint32_t p) {
             tm = m / kEpsTile;
             const uint64_t slot = (uint64_t)p * rtiles + (tm & (rtiles - 1));
             if (m >= budget || ld_dev(E.tile_ready + slot) != tm + 1) break;
-            __threadfence();
-            const Partial b = E.tile_part[slot];
+            drain_dev();
+            const Partial b = ld_dev_partial(E.tile_part + slot);
             acc = chan_merge(acc, b);
             const uint64_t len = (budget - m) < kEpsTile ? (budget - m) : kEpsTile;
             m += len;
-            P->acc = acc;
-            __threadfence();
+            st_dev_partial(&P->acc, acc);
+            drain_dev();
             st_dev(&P->merged, m);
             if (m % check == 0 || m == budget) {
                 const bool conv = m >= P->min_samples && eps_hat_dev(acc, E.z) <= E.eps;
                 if (conv || m == budget) {
                     if (conv) st_dev(&P->converged, 1u);
-                    P->stop_clock = wall_clock64();
-                    __threadfence();
+                    st_dev(&P->stop_clock, (unsigned long long)wall_clock64());
+                    drain_dev();
                     st_dev(&P->stop, 1u);
                     stopped = true;
                     break;
                 }
             }
         }
-        __threadfence();
+        drain_dev();
         atomicExch(&P->owner, 0u);
         if (stopped) return;
     }
@@ -3339,7 +3368,7 @@ __device__ void merge_ready(const EpsDesc& E, uint32_t p) {
 // unfinished slot never waits, so the merge always advances).  A wave stays
 // on its pattern while that pattern hands out samples.  A sample's weight
 // goes to the pattern's ring; a wave counts its finished samples into their
-// tile once per tile it touched in the grab (one release, one atomic), and
+// tile once per tile it touched in the grab (one wait, one atomic), and
 // the wave that completes a tile reduces it and merges what is ready.
 // Samples past a pattern's stopping point are dropped: a wave looks at the
 // stop flag before each sample.  The waves leave once every pattern has
@@ -3475,7 +3504,7 @@ void k_sample_eps(const LaunchDesc* __restrict__ D) {
                 const uint64_t t0 = wall_clock64();
                 const double xv = sample_one<false, kPairs>(g, t, D->plans + P->plan, D->round.k0, D->round.k1,
                                                              P->start + j, sv, sl, nullptr, hub_window, mt);
-                if (lane == 0) E.ring[(uint64_t)p * E.ring_samples + (j & rmask)] = xv;
+                if (lane == 0) st_dev_f64(E.ring + (uint64_t)p * E.ring_samples + (j & rmask), xv);
                 cost = uniform_u64(wall_clock64() - t0);
                 ++cnt;
             }
@@ -3483,27 +3512,22 @@ void k_sample_eps(const LaunchDesc* __restrict__ D) {
             const uint64_t slot = (uint64_t)p * rtiles + (tcur & (rtiles - 1));
             uint32_t last = 0;
             if (lane == 0) {
-                // one release for the weights of this segment: an acquire
-                // here (a cache invalidation) in every wave would cost the
-                // others their cached lists and bitmaps; the wave that
-                // completes the tile acquires once for the whole tile
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                drain_dev();  // the weights of this segment
                 const uint64_t rem = budget - tcur * kEpsTile;
                 const uint32_t len = (uint32_t)(rem < kEpsTile ? rem : kEpsTile);
                 last = atomicAdd(E.tile_done + slot, cnt) + cnt == len ? 1u : 0u;
             }
             if (uniform_u32(last)) {
-                __threadfence();
+                drain_dev();
                 const uint64_t rem = budget - tcur * kEpsTile;
                 const uint64_t len = rem < kEpsTile ? rem : kEpsTile;
                 const Partial part =
                     reduce_tile_wave(E.ring + (uint64_t)p * E.ring_samples + ((tcur * kEpsTile) & rmask), len);
                 if (lane == 0) {
-                    E.tile_done[slot] = 0u;
-                    E.tile_part[slot] = part;
-                    __threadfence();
-                    __hip_atomic_store(E.tile_ready + slot, (unsigned long long)(tcur + 1), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
+                    st_dev(E.tile_done + slot, 0u);
+                    st_dev_partial(E.tile_part + slot, part);
+                    drain_dev();
+                    st_dev(E.tile_ready + slot, (unsigned long long)(tcur + 1));
                 }
                 merge_ready(E, p);
             }
