@@ -82,7 +82,7 @@ struct agis_ctx {
     int tune_blocks_per_cu = 0;
     uint32_t tune_grab = 0;
     int use_graphs = 1;
-    int tune_variant = 0;  // sampling-kernel register budget (see sample_kernel)
+    int tune_variant = 2;  // sampling-kernel register budget (see sample_kernel)
     uint32_t tune_hub_window = 0;  // see LaunchDesc::hub_window
     // captured round (k_zero, k_sample, k_reduce_x) replayed on graph_stream;
     // valid while the key below matches
