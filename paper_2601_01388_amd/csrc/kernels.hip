@@ -91,6 +91,17 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
     return ((uint64_t)uniform_u32((uint32_t)(v >> 32)) << 32) | uniform_u32((uint32_t)v);
 }
 
+// A wave-uniform read of data that no kernel writes while this one runs (the
+// graph and its tables): through the scalar cache.  As a vector load it
+// would take 16 accesses of the first-level cache for its 64 equal
+// addresses, and those accesses are what the sampler runs at: one per cycle
+// (5-clique and 5-cycle on R-MAT-20).
+template <class P>
+__device__ __forceinline__ auto sload(P p) {
+    using T = decltype(p[0] + 0);
+    return *(const AGIS_CMEM T*)uniform_u64((uint64_t)(uintptr_t)p);
+}
+
 // Wave-wide scans and reductions by DPP row moves: a shift within rows of 16
 // lanes costs a vector operation, where a shuffle through the LDS crossbar
 // (ds_bpermute) costs its round trip, some 100 cycles and more under load,
@@ -1825,11 +1836,11 @@ __device__ __forceinline__ bool pair_hub_count(const DevTables& t, uint32_t my_t
     const uint32_t b = readlane_u32(my_tau, 31 - __builtin_clz(bm));
     mt.uni(t.pair_slot + a, 4);
     mt.uni(t.pair_slot + b, 4);
-    const int32_t sa = t.pair_slot[a], sb = t.pair_slot[b];
+    const int32_t sa = sload(t.pair_slot + a), sb = sload(t.pair_slot + b);
     if (sa < 0 || sb < 0) return false;
     const uint64_t pr = (uint64_t)(sa > sb ? sa : sb) * t.pairs + (uint64_t)(sa > sb ? sb : sa);
     mt.uni(t.pair_count + pr, 4);
-    const uint32_t c = t.pair_count[pr];
+    const uint32_t c = sload(t.pair_count + pr);
     bool both = false;
     const bool probe = (uint32_t)lane < i && my_tau != a && my_tau != b;
     if constexpr (MT::kOn) {
@@ -1841,8 +1852,8 @@ __device__ __forceinline__ bool pair_hub_count(const DevTables& t, uint32_t my_t
         }
     }
     if (probe) {
-        const auto ba = t.hub_bits + (uint64_t)t.hub_slot[a] * t.hub_words;
-        const auto bb = t.hub_bits + (uint64_t)t.hub_slot[b] * t.hub_words;
+        const auto ba = t.hub_bits + (uint64_t)sload(t.hub_slot + a) * t.hub_words;
+        const auto bb = t.hub_bits + (uint64_t)sload(t.hub_slot + b) * t.hub_words;
         const uint32_t w = my_tau >> 5, m = 1u << (my_tau & 31u);
         both = (ba[w] & m) != 0 && (bb[w] & m) != 0;
     }
@@ -1866,12 +1877,12 @@ __device__ __forceinline__ uint32_t pair_hub_select(const DevGraph& g, const Dev
     const uint32_t b = readlane_u32(my_tau, 31 - __builtin_clz(bm));
     mt.uni(g.off + a, 16);
     mt.uni(g.off + b, 16);
-    const uint64_t oa = g.off[a], ob = g.off[b];
-    const uint64_t da = g.off[a + 1] - oa, db = g.off[b + 1] - ob;
+    const uint64_t oa = sload(g.off + a), ob = sload(g.off + b);
+    const uint64_t da = sload(g.off + a + 1) - oa, db = sload(g.off + b + 1) - ob;
     const bool walk_a = da < db || (da == db && a < b);
     const uint32_t* list = g.nbr + (walk_a ? oa : ob);
     const uint64_t d = walk_a ? da : db;
-    const auto row = t.hub_bits + (uint64_t)t.hub_slot[walk_a ? b : a] * t.hub_words;
+    const auto row = t.hub_bits + (uint64_t)sload(t.hub_slot + (walk_a ? b : a)) * t.hub_words;
     // matched vertices (other than a and b) that lie in both lists
     bool both = false;
     const bool probe = (uint32_t)lane < i && my_tau != a && my_tau != b;
@@ -1884,15 +1895,15 @@ __device__ __forceinline__ uint32_t pair_hub_select(const DevGraph& g, const Dev
         }
     }
     if (probe) {
-        const auto ra = t.hub_bits + (uint64_t)t.hub_slot[a] * t.hub_words;
-        const auto rb = t.hub_bits + (uint64_t)t.hub_slot[b] * t.hub_words;
+        const auto ra = t.hub_bits + (uint64_t)sload(t.hub_slot + a) * t.hub_words;
+        const auto rb = t.hub_bits + (uint64_t)sload(t.hub_slot + b) * t.hub_words;
         const uint32_t w = my_tau >> 5, mk = 1u << (my_tau & 31u);
         both = (ra[w] & mk) != 0 && (rb[w] & mk) != 0;
     }
     // the cuts j d / P: members of S before each (the part holding rank r
     // lies between the last cut at or below r and the next)
-    const auto q = t.pair_quart + ((uint64_t)t.pair_slot[walk_a ? a : b] * t.pairs +
-                                   (uint64_t)t.pair_slot[walk_a ? b : a]) * (kPairParts - 1);
+    const auto q = t.pair_quart + ((uint64_t)sload(t.pair_slot + (walk_a ? a : b)) * t.pairs +
+                                   (uint64_t)sload(t.pair_slot + (walk_a ? b : a))) * (kPairParts - 1);
     uint32_t cutv[kPairParts - 1], qv[kPairParts - 1];
     mt.uni(t.pair_slot + a, 4);
     mt.uni(t.pair_slot + b, 4);
@@ -1900,8 +1911,8 @@ __device__ __forceinline__ uint32_t pair_hub_select(const DevGraph& g, const Dev
 #pragma unroll
     for (int j = 1; j < kPairParts; ++j) {
         mt.uni(list + (uint64_t)j * d / kPairParts, 4);
-        cutv[j - 1] = list[(uint64_t)j * d / kPairParts];
-        qv[j - 1] = q[j - 1];
+        cutv[j - 1] = sload(list + (uint64_t)j * d / kPairParts);
+        qv[j - 1] = sload(q + j - 1);
     }
     int s = 0;
     uint64_t lo_cnt = 0, hi_cnt = m;
@@ -2029,7 +2040,7 @@ __device__ __forceinline__ CoreMatched core_matched(const uint32_t* list, uint32
         const uint32_t qj = core_block_q(list, len, sw, lm, kj, xj, mt);
         const uint64_t inc = wave_incl_scan_u64((uint64_t)qj);
         if (kj > 0) mt.uni(bp + kj - 1, 8);
-        const uint64_t b0 = kj > 0 ? bp[kj - 1] : 0ull;
+        const uint64_t b0 = kj > 0 ? sload(bp + kj - 1) : 0ull;
         const uint64_t q0 = (uint64_t)readlane_u32(qj, o);
         const uint64_t p0 = b0 + readlane_u64(inc, o) - q0;
         if (lane == j) {
@@ -2083,13 +2094,13 @@ __device__ __forceinline__ double sample_one(const DevGraph& g, const DevTables&
                     if (P->s1_guide) {
                         const uint64_t bkt = r >> P->s1_shift;
                         mt.uni(P->s1_guide + bkt, 8);
-                        const uint32_t lo = P->s1_guide[bkt], hi = P->s1_guide[bkt + 1];
+                        const uint32_t lo = sload(P->s1_guide + bkt), hi = sload(P->s1_guide + bkt + 1);
                         bk = lo + wave_first_greater(blk + lo, (uint64_t)(hi - lo) + 1, r, mt);
                     } else {
                         bk = wave_first_greater(blk, (g.n + kStep1Block - 1) / kStep1Block, r, mt);
                     }
                     mt.uni(blk + bk - 1, 8);
-                    const uint64_t rr = r - blk[(int64_t)bk - 1];
+                    const uint64_t rr = r - sload(blk + (int64_t)bk - 1);
                     const uint64_t v0 = bk * kStep1Block + 4ull * (uint64_t)lane;
                     const AGIS_GMEM int32_t* lt0 = P->lt[0];
                     mt.vec(t.rec + v0, 64, v0 < g.n);
@@ -2126,14 +2137,14 @@ __device__ __forceinline__ double sample_one(const DevGraph& g, const DevTables&
                         // the answer lies between the guides of r's bucket and the next
                         const uint64_t bkt = r >> P->s1_shift;
                         mt.uni(P->s1_guide + bkt, 8);
-                        const uint32_t lo = P->s1_guide[bkt], hi = P->s1_guide[bkt + 1];
+                        const uint32_t lo = sload(P->s1_guide + bkt), hi = sload(P->s1_guide + bkt + 1);
                         v = lo + (uint32_t)wave_first_greater(P->s1_pre + lo, (uint64_t)(hi - lo) + 1, r, mt);
                     } else {
                         v = (uint32_t)wave_first_greater(P->s1_pre, g.n, r, mt);
                     }
                     num = P->s1_total;
                     mt.uni(P->s1_q + v, 4);
-                    den = P->s1_q[v];
+                    den = sload(P->s1_q + v);
                 }
             } else {
                 if (g.nnz == 0) {
@@ -2144,7 +2155,7 @@ __device__ __forceinline__ double sample_one(const DevGraph& g, const DevTables&
                 v = (uint32_t)wave_first_greater(g.off + 1, g.n, r, mt);
                 num = g.nnz;
                 mt.uni(g.off + v, 16);
-                den = g.off[v + 1] - g.off[v];
+                den = sload(g.off + v + 1) - sload(g.off + v);
             }
             x = (double)num / (double)den;
         } else {
@@ -2167,8 +2178,8 @@ __device__ __forceinline__ double sample_one(const DevGraph& g, const DevTables&
                 // prefix segment by segment between their positions.
                 const uint32_t w = readlane_u32(my_tau, __builtin_ctz(bm));
                 mt.uni(g.off + w, 16);
-                const uint64_t o = g.off[w];
-                const uint32_t d = (uint32_t)(g.off[w + 1] - o);
+                const uint64_t o = sload(g.off + w);
+                const uint32_t d = (uint32_t)(sload(g.off + w + 1) - o);
                 const uint32_t* list = g.nbr + o;
                 const uint64_t* pre = P->rowpre[i] + o;  // the row's own inclusive prefix
                 uint32_t pos = 0xFFFFFFFFu;
@@ -2195,7 +2206,7 @@ __device__ __forceinline__ double sample_one(const DevGraph& g, const DevTables&
                     if (d) mt.uni(pre + d - 1, 8);
                 }
                 if (found) qx = pre[pos] - (pos > 0 ? pre[pos - 1] : 0ull);
-                const uint64_t qrow = d ? pre[d - 1] : 0ull;
+                const uint64_t qrow = d ? sload(pre + d - 1) : 0ull;
                 const uint64_t Q = qrow - wave_sum_u64(qx);
                 if (Q == 0) {
                     fail = (int)i;
@@ -2212,7 +2223,7 @@ __device__ __forceinline__ double sample_one(const DevGraph& g, const DevTables&
                     const int L = (int)(key & 0xFF);
                     const uint32_t e = (uint32_t)(key >> 8);
                     if (e > 0) mt.uni(pre + e - 1, 8);
-                    const uint64_t before = e > 0 ? pre[e - 1] : 0ull;
+                    const uint64_t before = e > 0 ? sload(pre + e - 1) : 0ull;
                     if (before - shift > r) {
                         ans = seg + wave_first_greater(pre + seg, e - seg, r + shift, mt);
                         break;
@@ -2226,19 +2237,19 @@ __device__ __forceinline__ double sample_one(const DevGraph& g, const DevTables&
                     mt.uni(list + ans, 4);
                     mt.uni(pre + (ans > 0 ? ans - 1 : ans), ans > 0 ? 16u : 8u);
                 }
-                v = list[ans];
+                v = sload(list + ans);
                 drawn_row = w;
                 drawn_pos = (uint32_t)ans;
                 num = Q;
-                den = pre[ans] - (ans > 0 ? pre[ans - 1] : 0ull);
+                den = sload(pre + ans) - (ans > 0 ? sload(pre + ans - 1) : 0ull);
             } else if (!weighted && __builtin_popcount(bm) == 1) {
                 // Uniform draw from N(w) minus the matched vertices, without
                 // materialising the set: probe each matched vertex in N(w)
                 // and skip the positions found.
                 const uint32_t w = readlane_u32(my_tau, __builtin_ctz(bm));
                 mt.uni(g.off + w, 16);
-                const uint64_t o = g.off[w];
-                const uint32_t d = (uint32_t)(g.off[w + 1] - o);
+                const uint64_t o = sload(g.off + w);
+                const uint32_t d = (uint32_t)(sload(g.off + w + 1) - o);
                 const uint32_t* list = g.nbr + o;
                 uint32_t pos = 0xFFFFFFFFu;
                 bool found = false;
@@ -2272,7 +2283,7 @@ __device__ __forceinline__ double sample_one(const DevGraph& g, const DevTables&
                         idx = r + c;
                     }
                     mt.uni(list + idx, 4);
-                    v = list[idx];
+                    v = sload(list + idx);
                     drawn_row = w;
                     drawn_pos = (uint32_t)idx;
                 }
@@ -2317,15 +2328,15 @@ __device__ __forceinline__ double sample_one(const DevGraph& g, const DevTables&
                 mt.uni(t.core_start + cpr, 8);
                 mt.uni(t.core_len + cpr, 4);
                 mt.uni(P->clm[i] + cpr, 4);
-                const uint64_t st = t.core_start[cpr];
-                const uint32_t len = t.core_len[cpr];
-                const int32_t lm = P->clm[i][cpr];
+                const uint64_t st = sload(t.core_start + cpr);
+                const uint32_t len = sload(t.core_len + cpr);
+                const int32_t lm = sload(P->clm[i] + cpr);
                 const uint32_t* list = t.core_nbr + st;
                 const AGIS_GMEM int32_t* swi = P->sw[i];
                 const uint64_t nb = ((uint64_t)len + kCoreBlock - 1) / kCoreBlock;
                 const AGIS_GMEM uint64_t* bp = P->cbp[i] + st / kCoreBlock;
                 if (nb) mt.uni(bp + nb - 1, 8);
-                const uint64_t qi = nb ? bp[nb - 1] : 0ull;
+                const uint64_t qi = nb ? sload(bp + nb - 1) : 0ull;
                 if (qi == 0) {
                     fail = (int)i;
                     break;
@@ -2356,7 +2367,7 @@ __device__ __forceinline__ double sample_one(const DevGraph& g, const DevTables&
                 }
                 const uint64_t kb = wave_first_greater(bp, nb, rr, mt);
                 if (kb > 0) mt.uni(bp + kb - 1, 8);
-                const uint64_t before = kb > 0 ? bp[kb - 1] : 0ull;
+                const uint64_t before = kb > 0 ? sload(bp + kb - 1) : 0ull;
                 uint32_t xv;
                 const uint32_t qv = core_block_q(list, len, swi, lm, kb, xv, mt);
                 const uint64_t incl = wave_incl_scan_u64((uint64_t)qv);
@@ -2430,7 +2441,7 @@ __device__ __forceinline__ double sample_one(const DevGraph& g, const DevTables&
                             if (lmin < db) {
                                 const uint64_t prm = readlane_u64(pr, jk);
                                 mt.uni(t.core_start + prm, 8);
-                                base = t.core_nbr + t.core_start[prm];
+                                base = t.core_nbr + sload(t.core_start + prm);
                                 db = lmin;
                                 others = 1u << (1 - jk);
                                 walk_reuse = false;
@@ -2456,8 +2467,8 @@ __device__ __forceinline__ double sample_one(const DevGraph& g, const DevTables&
                                             (uint64_t)readlane_u32((uint32_t)my_core, jc);
                         mt.uni(t.core_start + pr, 8);
                         mt.uni(t.core_len + pr, 4);
-                        base = t.core_nbr + t.core_start[pr];
-                        db = t.core_len[pr];
+                        base = t.core_nbr + sload(t.core_start + pr);
+                        db = sload(t.core_len + pr);
                         others = uniform_u32(lists & ~(1u << ja) & ~(1u << jc));
                     } else {
                         // base = smallest degree, ties to the smallest position
