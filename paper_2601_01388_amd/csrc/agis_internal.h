@@ -203,10 +203,16 @@ hipError_t launch_pair_counts(agis_ctx* ctx, const DevGraph& g, uint32_t max_deg
                               uint32_t* pair_hub, uint32_t* pair_count, uint32_t* pair_quart);
 hipError_t launch_hub_bits(const DevGraph& g, const int32_t* hub_slot, uint64_t words, uint32_t* bits,
                            hipStream_t stream);
-// Degree orientation: out-degrees into outdeg (n entries of scratch), the
-// offsets into off_out (n + 1), then the neighbours into nbr_out.
-hipError_t launch_orient_offsets(agis_ctx* ctx, const DevGraph& g, uint32_t* outdeg, uint64_t* off_out);
-hipError_t launch_orient_fill(const DevGraph& g, const uint64_t* off_out, uint32_t* nbr_out, hipStream_t stream);
+// Degree orientation: the kept slots (mask, one bit each, orient_words of
+// them) and their counts per run of slots, scanned (run_kept, orient_runs + 1
+// entries), the offsets into off_out (n + 1); then the neighbours into
+// nbr_out.  deg: n entries of scratch, or nullptr.
+uint64_t orient_words(uint64_t nnz);
+uint64_t orient_runs(uint64_t nnz);
+hipError_t launch_orient_offsets(agis_ctx* ctx, const DevGraph& g, uint32_t* deg, uint64_t* mask, uint64_t* run_kept,
+                                 uint64_t* off_out);
+hipError_t launch_orient_fill(agis_ctx* ctx, const DevGraph& g, const uint64_t* mask, const uint64_t* run_kept,
+                              uint32_t* nbr_out);
 // out[v] = certain-zero marker if d(v) < b + f1, else lt[v] (lt given) or the
 // f_approx log weight of signature (b, f1, ie, f2).
 hipError_t launch_step_log_weights(const agis_tables& t, uint64_t n, uint32_t b, uint32_t f1, uint32_t ie, uint32_t f2,

@@ -1549,15 +1549,23 @@ int agis_orient(agis_ctx* ctx, const agis_graph* g, agis_graph** out) {
     o->parent = g;
     o->pool = ctx->pool;
     o->device = ctx->device;
-    uint32_t* outdeg = nullptr;
-    hipError_t e = ctx->pool->alloc(&outdeg, n * sizeof(uint32_t));
-    if (e == hipSuccess) e = ctx->pool->alloc(&o->own_off, (n + 1) * sizeof(uint64_t));
-    if (e == hipSuccess) e = agis::launch_orient_offsets(ctx, g->g, outdeg, o->own_off);
+    uint64_t *mask = nullptr, *run_kept = nullptr;
+    uint32_t* deg = nullptr;
+    hipError_t e = ctx->pool->alloc(&o->own_off, (n + 1) * sizeof(uint64_t));
+    if (e == hipSuccess)
+        e = ctx->pool->alloc(&mask, std::max<uint64_t>(agis::orient_words(g->g.nnz), 1) * sizeof(uint64_t));
+    if (e == hipSuccess) e = ctx->pool->alloc(&run_kept, (agis::orient_runs(g->g.nnz) + 1) * sizeof(uint64_t));
+    if (e == hipSuccess && ctx->pool->alloc(&deg, n * sizeof(uint32_t)) != hipSuccess) {
+        (void)hipGetLastError();  // no room: the degrees come from the offsets
+        deg = nullptr;
+    }
+    if (e == hipSuccess) e = agis::launch_orient_offsets(ctx, g->g, deg, mask, run_kept, o->own_off);
     uint64_t nnz = 0;
     if (e == hipSuccess) e = hipMemcpyAsync(&nnz, o->own_off + n, sizeof(uint64_t), hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+    ctx->pool->free(deg);
     if (e == hipSuccess) e = ctx->pool->alloc(&o->own_nbr, (nnz ? nnz : 1) * sizeof(uint32_t));
-    if (e == hipSuccess) e = agis::launch_orient_fill(g->g, o->own_off, o->own_nbr, ctx->stream);
+    if (e == hipSuccess) e = agis::launch_orient_fill(ctx, g->g, mask, run_kept, o->own_nbr);
     uint32_t* d_max = (uint32_t*)ctx->d_small;
     uint32_t maxd = 0;
     o->g = agis::DevGraph{agis::gmem((const uint64_t*)o->own_off), agis::gmem((const uint32_t*)o->own_nbr), n, nnz};
@@ -1566,7 +1574,8 @@ int agis_orient(agis_ctx* ctx, const agis_graph* g, agis_graph** out) {
     if (e == hipSuccess) e = hipMemcpyAsync(&maxd, d_max, sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) (void)hipStreamSynchronize(ctx->stream);
-    ctx->pool->free(outdeg);
+    ctx->pool->free(mask);
+    ctx->pool->free(run_kept);
     if (e != hipSuccess) {
         agis_graph_destroy(o);
         return hip_fail(ctx, e, "orient graph");

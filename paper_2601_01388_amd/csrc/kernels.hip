@@ -333,6 +333,49 @@ __device__ __forceinline__ uint64_t wave_first_greater(const uint64_t* __restric
     return lo + (uint64_t)(__ffsll((unsigned long long)m) - 1);
 }
 
+// Rows of consecutive slots.  Per-slot kernels give a wave kSlotRun slots in
+// a row: the row of the first is found by a wave search of the offsets, each
+// further 64 slots start from the row of the last slot before them, and the
+// lanes find theirs among the ends of the next 64 rows by shuffles.  (A
+// binary search of the offsets per slot is some 20 dependent loads.)
+constexpr uint64_t kSlotRun = 1024;
+
+// The row of slot e (wave-uniform, e < nnz).
+__device__ __forceinline__ uint64_t wave_row_of_slot(const DevGraph& g, uint64_t e) {
+    return wave_first_greater((const uint64_t*)g.off + 1, g.n, e);
+}
+
+// This lane's row for the 64 slots from e on (slots past the end: the row of
+// the last slot), v0 being the row of slot e or an earlier one.  All lanes
+// must call it.
+__device__ __forceinline__ uint64_t lane_row(const DevGraph& g, uint64_t e, uint64_t v0) {
+    const uint32_t lane = (uint32_t)lane_id();
+    const uint32_t mine = e + lane < g.nnz ? lane : (uint32_t)(g.nnz - 1 - e);
+    uint64_t row = v0;
+    bool open = true;
+    for (;;) {
+        // ends of the rows v0 .. v0 + 63, in slots from e on (at most 64)
+        const uint64_t v = v0 + lane;
+        const uint64_t end = v < g.n ? g.off[v + 1] : ~0ull;
+        const uint32_t rel = end <= e ? 0u : (end - e > 64u ? 64u : (uint32_t)(end - e));
+        // the first of them above this lane's slot
+        uint32_t k = 0;
+#pragma unroll
+        for (uint32_t s = 32; s > 0; s >>= 1) k += (uint32_t)__shfl((int)rel, (int)(k + s - 1), kWave) <= mine ? s : 0u;
+        const bool here = (uint32_t)__shfl((int)rel, (int)k, kWave) > mine;
+        if (open && here) {
+            row = v0 + k;
+            open = false;
+        }
+        const uint64_t left = __ballot(open);
+        if (left == 0) return row;
+        // the rows of the other lanes lie further on, behind empty rows
+        const uint64_t from = v0 + kWave;
+        const uint64_t slot = e + readlane_u32(mine, __builtin_ctzll(left));
+        v0 = from + wave_first_greater((const uint64_t*)g.off + 1 + from, g.n - from, slot);
+    }
+}
+
 // Wave-cooperative: first position p in [lo, hi) with list[p] > key, or hi
 // when there is none (list ascending).
 template <class MT = NoMeter>
@@ -897,17 +940,58 @@ __global__ __launch_bounds__(256) void k_step1_blocksum(const uint4* rec, DevPla
 // {v, w} is kept as v -> w iff (d(v), v) < (d(w), w), i.e. edges from the
 // higher-degree end are dropped.  Rows stay in ascending id order.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ uint64_t orient_key(const DevGraph& g, uint32_t v) {
-    return ((g.off[v + 1] - g.off[v]) << 32) | (uint64_t)v;
+// One bit per slot: kept or not (64 slots a word), and the kept slots of
+// every run of kSlotRun.  The kept slots of the whole graph in slot order are
+// the oriented neighbours, and the number of them before a row's first slot
+// is the row's offset, so a scan of the run counts gives both.  (One thread
+// per row, walking it twice, took 41 ms on R-MAT-20, whose longest row has
+// 64,710 slots.)
+__global__ void k_degrees(DevGraph g, uint32_t* __restrict__ deg) {
+    const uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (v < g.n) deg[v] = (uint32_t)(g.off[v + 1] - g.off[v]);
 }
 
-__global__ void k_orient_count(DevGraph g, uint32_t* outdeg) {
+constexpr uint64_t kRunWords = kSlotRun / kWave;
+
+// deg: the degrees, or nullptr (read from the offsets)
+__global__ __launch_bounds__(256) void k_orient_mask(DevGraph g, const uint32_t* __restrict__ deg,
+                                                     uint64_t* __restrict__ mask, uint64_t* __restrict__ run_kept) {
+    const uint64_t nw = (uint64_t)gridDim.x * (blockDim.x / kWave);
+    auto key_of = [&](uint64_t v) -> uint64_t {
+        const uint64_t d = deg ? (uint64_t)deg[v] : g.off[v + 1] - g.off[v];
+        return (d << 32) | v;
+    };
+    for (uint64_t r = (uint64_t)blockIdx.x * (blockDim.x / kWave) + uniform_u32(threadIdx.x / kWave);
+         r * kSlotRun < g.nnz; r += nw) {
+        uint64_t v0 = wave_row_of_slot(g, r * kSlotRun);
+        uint64_t kept = 0;
+        for (uint64_t w = r * kRunWords; w < (r + 1) * kRunWords && w * kWave < g.nnz; ++w) {
+            const uint64_t e = w * kWave + (uint64_t)lane_id();
+            const uint64_t v = lane_row(g, w * kWave, v0);
+            const uint32_t x = e < g.nnz ? g.nbr[e] : 0u;
+            const uint64_t m = __ballot(e < g.nnz && key_of(x) > key_of(v));
+            if (lane_id() == 0) mask[w] = m;
+            kept += (uint64_t)__popcll(m);
+            v0 = readlane_u64(v, kWave - 1);
+        }
+        if (lane_id() == 0) run_kept[r] = kept;
+    }
+}
+
+// run_kept: exclusive prefix over the runs, the total last
+__global__ void k_orient_off(DevGraph g, const uint64_t* __restrict__ mask, const uint64_t* __restrict__ run_kept,
+                             uint64_t runs, uint64_t* __restrict__ off_out) {
     const uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= g.n) return;
-    const uint64_t kv = orient_key(g, (uint32_t)v);
-    uint32_t c = 0;
-    for (uint64_t e = g.off[v]; e < g.off[v + 1]; ++e) c += orient_key(g, g.nbr[e]) > kv ? 1u : 0u;
-    outdeg[v] = c;
+    if (v > g.n) return;
+    const uint64_t e = v < g.n ? g.off[v] : g.nnz;
+    if (e >= g.nnz) {
+        off_out[v] = run_kept[runs];
+        return;
+    }
+    const uint64_t r = e / kSlotRun, w = e / kWave;
+    uint64_t c = run_kept[r];
+    for (uint64_t k = r * kRunWords; k < w; ++k) c += (uint64_t)__popcll(mask[k]);
+    off_out[v] = c + (uint64_t)__popcll(mask[w] & ((1ull << (e % kWave)) - 1ull));
 }
 
 __global__ __launch_bounds__(kScanThreads) void k_u32_tilesum(const uint32_t* in, uint64_t n, uint64_t* tile_sums) {
@@ -958,36 +1042,48 @@ __global__ __launch_bounds__(kScanThreads) void k_u32_final(const uint32_t* in, 
     }
 }
 
-__global__ void k_orient_fill(DevGraph g, const uint64_t* off_out, uint32_t* nbr_out) {
-    const uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= g.n) return;
-    const uint64_t kv = orient_key(g, (uint32_t)v);
-    uint64_t p = off_out[v];
-    for (uint64_t e = g.off[v]; e < g.off[v + 1]; ++e) {
-        const uint32_t w = g.nbr[e];
-        if (orient_key(g, w) > kv) nbr_out[p++] = w;
+__global__ __launch_bounds__(256) void k_orient_fill(DevGraph g, const uint64_t* __restrict__ mask,
+                                                     const uint64_t* __restrict__ run_kept,
+                                                     uint32_t* __restrict__ nbr_out) {
+    const uint64_t nw = (uint64_t)gridDim.x * (blockDim.x / kWave);
+    for (uint64_t r = (uint64_t)blockIdx.x * (blockDim.x / kWave) + uniform_u32(threadIdx.x / kWave);
+         r * kSlotRun < g.nnz; r += nw) {
+        uint64_t at = run_kept[r];
+        for (uint64_t w = r * kRunWords; w < (r + 1) * kRunWords && w * kWave < g.nnz; ++w) {
+            const uint64_t m = mask[w];
+            const uint64_t e = w * kWave + (uint64_t)lane_id();
+            if (m >> lane_id() & 1ull) nbr_out[at + (uint64_t)__popcll(m & lanemask_lt())] = g.nbr[e];
+            at += (uint64_t)__popcll(m);
+        }
     }
 }
 
-hipError_t launch_orient_offsets(agis_ctx* ctx, const DevGraph& g, uint32_t* outdeg, uint64_t* off_out) {
+uint64_t orient_words(uint64_t nnz) { return (nnz + kWave - 1) / kWave; }
+uint64_t orient_runs(uint64_t nnz) { return (nnz + kSlotRun - 1) / kSlotRun; }
+
+static unsigned run_grid(const agis_ctx* ctx, uint64_t nnz) {
+    return (unsigned)std::min<uint64_t>((orient_runs(nnz) + 3) / 4, (uint64_t)ctx->num_cus * 8);
+}
+
+hipError_t launch_orient_offsets(agis_ctx* ctx, const DevGraph& g, uint32_t* deg, uint64_t* mask, uint64_t* run_kept,
+                                 uint64_t* off_out) {
     hipStream_t st = ctx->stream;
-    const uint64_t n = g.n;
-    const uint64_t ntiles = (n + kScanTile - 1) / kScanTile;
-    if (ctx->blocksums_cap < ntiles) {
-        if (ctx->d_blocksums) (void)hipFree(ctx->d_blocksums);
-        ctx->d_blocksums = nullptr;
-        ctx->blocksums_cap = 0;
-        hipError_t e = ctx_malloc(ctx, (void**)&ctx->d_blocksums, ntiles * sizeof(uint64_t));
-        if (e != hipSuccess) return e;
-        ctx->blocksums_cap = ntiles;
-    }
-    hipError_t e = hipMemsetAsync(off_out, 0, sizeof(uint64_t), st);
+    const uint64_t runs = orient_runs(g.nnz);
+    if (deg) hipLaunchKernelGGL(k_degrees, dim3(grid_for(g.n, 256)), dim3(256), 0, st, g, deg);
+    const hipError_t e = hipMemsetAsync(run_kept + runs, 0, sizeof(uint64_t), st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_orient_count, dim3(grid_for(n, 256)), dim3(256), 0, st, g, outdeg);
-    hipLaunchKernelGGL(k_u32_tilesum, dim3((unsigned)ntiles), dim3(kScanThreads), 0, st, outdeg, n, ctx->d_blocksums);
-    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(1024), 0, st, ctx->d_blocksums, ntiles);
-    hipLaunchKernelGGL(k_u32_final, dim3((unsigned)ntiles), dim3(kScanThreads), 0, st, outdeg, n, ctx->d_blocksums,
-                       off_out);
+    if (g.nnz)
+        hipLaunchKernelGGL(k_orient_mask, dim3(run_grid(ctx, g.nnz)), dim3(256), 0, st, g, deg, mask, run_kept);
+    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(1024), 0, st, run_kept, runs + 1);
+    hipLaunchKernelGGL(k_orient_off, dim3(grid_for(g.n + 1, 256)), dim3(256), 0, st, g, mask, run_kept, runs, off_out);
+    return hipGetLastError();
+}
+
+hipError_t launch_orient_fill(agis_ctx* ctx, const DevGraph& g, const uint64_t* mask, const uint64_t* run_kept,
+                              uint32_t* nbr_out) {
+    if (g.nnz)
+        hipLaunchKernelGGL(k_orient_fill, dim3(run_grid(ctx, g.nnz)), dim3(256), 0, ctx->stream, g, mask, run_kept,
+                           nbr_out);
     return hipGetLastError();
 }
 
@@ -1498,11 +1594,6 @@ hipError_t launch_core_pairs(agis_ctx* ctx, const DevGraph& g, const uint32_t* p
     if (e == hipSuccess) e = es;
     ctx->pool->free(rows);
     return e;
-}
-
-hipError_t launch_orient_fill(const DevGraph& g, const uint64_t* off_out, uint32_t* nbr_out, hipStream_t stream) {
-    hipLaunchKernelGGL(k_orient_fill, dim3(grid_for(g.n, 256)), dim3(256), 0, stream, g, off_out, nbr_out);
-    return hipGetLastError();
 }
 
 uint64_t step1_scan_tiles(uint64_t n) { return (n + kScanTile - 1) / kScanTile; }
