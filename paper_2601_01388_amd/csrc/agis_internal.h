@@ -180,13 +180,15 @@ hipError_t upload_fixed_point_tables(hipStream_t stream);
 // Row checks (offsets monotone and within nnz) must pass before the edge
 // checks run: the edge checks index rows through the offsets.
 hipError_t launch_validate_rows(const DevGraph& g, uint32_t* d_flags, hipStream_t stream);
-hipError_t launch_validate_edges(const DevGraph& g, uint32_t* d_flags, hipStream_t stream);
+// *d_lower: the slots whose neighbour is below their row's vertex by (degree,
+// id); without faults the graph is symmetric iff they are half of the slots.
+hipError_t launch_validate_edges(agis_ctx* ctx, const DevGraph& g, uint32_t* d_flags, uint64_t* d_lower);
 hipError_t launch_max_degree(const DevGraph& g, uint32_t* d_max, hipStream_t stream);
 // adj: the graph whose lists decide whether two neighbours are adjacent (g
-// itself, or the undirected graph of an oriented g)
-hipError_t launch_build_tables(const DevGraph& g, const DevGraph& adj, uint4* rec, uint64_t* s2, uint64_t* hits,
-                               uint64_t* trials, uint32_t k0, uint32_t k1, int32_t lc_min, int exact,
-                               hipStream_t stream);
+// itself, or the undirected graph of an oriented g).  Fills t.rec, t.s2,
+// t.hits and t.trials; t's hub bitmaps are used where they are built.
+hipError_t launch_build_tables(agis_ctx* ctx, const DevGraph& g, const DevGraph& adj, const agis_tables& t, uint32_t k0,
+                               uint32_t k1, int32_t lc_min, int exact);
 // Hub bitmaps: log2-degree histogram (64 buckets) of g; then, for vertices
 // of degree >= min_deg, their slots (hub_slot, -1 elsewhere; flags is n
 // entries of scratch), the count into *hubs; then the bits.
@@ -201,8 +203,9 @@ hipError_t launch_hub_slots(agis_ctx* ctx, const DevGraph& g, uint32_t min_deg, 
 // Entries with a <= b are not written.  Synchronises the stream.
 hipError_t launch_pair_counts(agis_ctx* ctx, const DevGraph& g, uint32_t max_deg, int32_t* pair_slot, uint64_t H,
                               uint32_t* pair_hub, uint32_t* pair_count, uint32_t* pair_quart);
-hipError_t launch_hub_bits(const DevGraph& g, const int32_t* hub_slot, uint64_t words, uint32_t* bits,
-                           hipStream_t stream);
+// hub: scratch of `hubs` entries, the vertices by slot.
+hipError_t launch_hub_bits(const DevGraph& g, const int32_t* hub_slot, uint64_t hubs, uint32_t* hub, uint64_t words,
+                           uint32_t* bits, hipStream_t stream);
 // Degree orientation: the kept slots (mask, one bit each, orient_words of
 // them) and their counts per run of slots, scanned (run_kept, orient_runs + 1
 // entries), the offsets into off_out (n + 1); then the neighbours into

@@ -524,7 +524,8 @@ hipError_t build_hub_bitmaps(agis_ctx* ctx, const agis_graph* g, agis_tables* t)
     if (e == hipSuccess) e = ctx->pool->alloc(&t->hub_bits, hubs * words * sizeof(uint32_t));
     if (e == hipErrorOutOfMemory) return drop_out_of_memory();
     if (e == hipSuccess) e = hipMemsetAsync(t->hub_bits, 0, hubs * words * sizeof(uint32_t), ctx->stream);
-    if (e == hipSuccess) e = agis::launch_hub_bits(g->g, t->hub_slot, words, t->hub_bits, ctx->stream);
+    // (flags is free again: it takes the hubs by slot)
+    if (e == hipSuccess) e = agis::launch_hub_bits(g->g, t->hub_slot, hubs, flags, words, t->hub_bits, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e == hipSuccess) {
         t->hub_words = words;
@@ -1497,18 +1498,25 @@ int agis_load_csr(agis_ctx* ctx, const uint64_t* off, const uint32_t* nbr, uint6
     if (nnz & 1ull) return fail(ctx, AGIS_E_INVALID_CSR, "nnz of a symmetric graph must be even");
     agis::DevGraph dg{agis::gmem(off), agis::gmem(nbr), n, nnz};
     uint32_t* d_cells = (uint32_t*)ctx->d_small;
-    uint32_t cells[2] = {0, 0};
-    AGIS_HIP(ctx, hipMemsetAsync(d_cells, 0, 2 * sizeof(uint32_t), ctx->stream), "clear flags");
+    // fault flags, largest degree, and (64 bits) the slots that point down
+    uint32_t cells[4] = {0, 0, 0, 0};
+    AGIS_HIP(ctx, hipMemsetAsync(d_cells, 0, sizeof(cells), ctx->stream), "clear flags");
     if (flags & AGIS_CSR_VALIDATE) {
         AGIS_HIP(ctx, agis::launch_validate_rows(dg, d_cells, ctx->stream), "validate CSR rows");
         AGIS_HIP(ctx, hipMemcpyAsync(cells, d_cells, sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream),
                  "read flags");
         AGIS_HIP(ctx, hipStreamSynchronize(ctx->stream), "validate CSR rows");
-        if (cells[0] == 0) AGIS_HIP(ctx, agis::launch_validate_edges(dg, d_cells, ctx->stream), "validate CSR edges");
+        if (cells[0] == 0)
+            AGIS_HIP(ctx, agis::launch_validate_edges(ctx, dg, d_cells, (uint64_t*)(d_cells + 2)), "validate CSR edges");
     }
     if (cells[0] == 0) AGIS_HIP(ctx, agis::launch_max_degree(dg, d_cells + 1, ctx->stream), "max degree");
     AGIS_HIP(ctx, hipMemcpyAsync(cells, d_cells, sizeof(cells), hipMemcpyDeviceToHost, ctx->stream), "read flags");
     AGIS_HIP(ctx, hipStreamSynchronize(ctx->stream), "validate CSR");
+    if ((flags & AGIS_CSR_VALIDATE) && cells[0] == 0) {
+        uint64_t lower = 0;
+        std::memcpy(&lower, &cells[2], sizeof(lower));
+        if (2 * lower != nnz) cells[0] |= 16u;
+    }
     if (cells[0]) {
         std::string m = "invalid CSR:";
         if (cells[0] & 1u) m += " offsets not non-decreasing or beyond nnz;";
@@ -1616,12 +1624,12 @@ int agis_build_proposal_tables(agis_ctx* ctx, const agis_graph* g, uint64_t cv_s
     if (e == hipSuccess) e = ctx->pool->alloc(&t->s2, n * sizeof(uint64_t));
     if (e == hipSuccess) e = ctx->pool->alloc(&t->hits, n * sizeof(uint64_t));
     if (e == hipSuccess) e = ctx->pool->alloc(&t->trials, n * sizeof(uint64_t));
-    if (e == hipSuccess)
-        e = agis::launch_build_tables(g->g, g->parent ? g->parent->g : g->g, t->rec, t->s2, t->hits, t->trials,
-                                      (uint32_t)cv_seed, (uint32_t)(cv_seed >> 32), lc_min_q16, exact_cv ? 1 : 0,
-                                      ctx->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+    // the bitmaps first: they decide most of the clustering trials
     if (e == hipSuccess) e = build_hub_bitmaps(ctx, g, t);
+    if (e == hipSuccess)
+        e = agis::launch_build_tables(ctx, g->g, g->parent ? g->parent->g : g->g, *t, (uint32_t)cv_seed,
+                                      (uint32_t)(cv_seed >> 32), lc_min_q16, exact_cv ? 1 : 0);
+    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) {
         agis_tables_destroy(t);
         return hip_fail(ctx, e, "build proposal tables");

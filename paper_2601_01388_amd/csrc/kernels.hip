@@ -288,19 +288,6 @@ __device__ __forceinline__ bool contains_u32_counted(const uint32_t* __restrict_
     return lo < len && list[lo] == x;
 }
 
-// Row of edge slot e: the vertex v with off[v] <= e < off[v + 1].
-__device__ __forceinline__ uint32_t row_of_slot(const uint64_t* __restrict__ off, uint64_t n, uint64_t e) {
-    uint64_t lo = 0, hi = n;  // first v with off[v + 1] > e
-    while (lo < hi) {
-        uint64_t mid = (lo + hi) >> 1;
-        if (off[mid + 1] > e)
-            hi = mid;
-        else
-            lo = mid + 1;
-    }
-    return (uint32_t)lo;
-}
-
 // Wave-cooperative 64-ary search: first index p in [0, n) with a[p] > r,
 // given a non-decreasing and a[n - 1] > r.  Every lane returns the answer.
 template <class MT = NoMeter>
@@ -613,28 +600,46 @@ __global__ void k_validate_rows(DevGraph g, uint32_t* flags) {
 // Per-slot kernels run a grid-stride loop over 64-bit slot indices on a
 // capped grid (a dispatch holds at most 2^32 work-items, fewer than the
 // slots of the largest graphs).
-__global__ void k_validate_edges(DevGraph g, uint32_t* flags) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < g.nnz; e += stride) {
-        const uint32_t v = row_of_slot(g.off, g.n, e);
-        if (v >= g.n) {
-            atomicOr(flags, 1u);
-            continue;
-        }
+//
+// Symmetry: each slot (v, x) whose x is below v by (degree, id) is looked up
+// in x's row, the shorter of the two, and counted in *lower.  In a graph
+// without the other faults these slots' mirrors are distinct slots of the
+// other direction, so if all are found and they are half of the slots, every
+// slot has its mirror.  (Looking every slot up in its neighbour's row took
+// 2.2 ms on R-MAT-20.)
+__global__ __launch_bounds__(256) void k_validate_edges(DevGraph g, uint32_t* flags, unsigned long long* lower) {
+    const uint64_t nw = (uint64_t)gridDim.x * (blockDim.x / kWave);
+    uint64_t low = 0;
+    uint32_t faults = 0;
+    for (uint64_t r = (uint64_t)blockIdx.x * (blockDim.x / kWave) + uniform_u32(threadIdx.x / kWave);
+         r * kSlotRun < g.nnz; r += nw) {
         // offsets were checked (monotone, within nnz) by k_validate_rows first
-        const uint32_t x = g.nbr[e];
-        uint32_t f = 0;
-        if ((uint64_t)x >= g.n) {
-            atomicOr(flags, 2u);
-            continue;
+        const uint64_t end = (r + 1) * kSlotRun < g.nnz ? (r + 1) * kSlotRun : g.nnz;
+        uint64_t v0 = wave_row_of_slot(g, r * kSlotRun);
+        for (uint64_t e0 = r * kSlotRun; e0 < end; e0 += kWave) {
+            const uint64_t e = e0 + (uint64_t)lane_id();
+            const uint64_t v = lane_row(g, e0, v0);
+            v0 = readlane_u64(v, kWave - 1);
+            bool is_low = false;
+            if (e < g.nnz) {
+                const uint32_t x = g.nbr[e];
+                if ((uint64_t)x >= g.n) {
+                    faults |= 2u;
+                } else {
+                    const uint64_t ov = g.off[v], ev = g.off[v + 1], ox = g.off[x];
+                    const uint64_t dv = ev - ov, dx = g.off[x + 1] - ox;
+                    if (x == v) faults |= 4u;
+                    if (e + 1 < ev && g.nbr[e + 1] <= x) faults |= 8u;
+                    is_low = dx < dv || (dx == dv && x < v);
+                    if (is_low && (dx > 0xFFFFFFFFull || !contains_u32(g.nbr + ox, (uint32_t)dx, (uint32_t)v)))
+                        faults |= 16u;
+                }
+            }
+            low += (uint64_t)__popcll(__ballot(is_low));
         }
-        if (x == v) f |= 4u;
-        if (e + 1 < g.off[v + 1] && g.nbr[e + 1] <= x) f |= 8u;
-        const uint64_t o = g.off[x];
-        const uint64_t d = g.off[x + 1] - o;
-        if (d > 0xFFFFFFFFull || !contains_u32(g.nbr + o, (uint32_t)d, v)) f |= 16u;
-        if (f) atomicOr(flags, f);
     }
+    if (faults) atomicOr(flags, faults);
+    if (lane_id() == 0 && low) atomicAdd(lower, (unsigned long long)low);
 }
 
 __global__ void k_max_degree(DevGraph g, uint32_t* out) {
@@ -663,8 +668,15 @@ hipError_t launch_validate_rows(const DevGraph& g, uint32_t* d_flags, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_validate_edges(const DevGraph& g, uint32_t* d_flags, hipStream_t stream) {
-    if (g.nnz) hipLaunchKernelGGL(k_validate_edges, dim3(stride_grid(g.nnz, 256)), dim3(256), 0, stream, g, d_flags);
+// Workgroups of four waves for a kernel over runs of kSlotRun slots.
+static unsigned run_grid(const agis_ctx* ctx, uint64_t nnz) {
+    return (unsigned)std::min<uint64_t>(((nnz + kSlotRun - 1) / kSlotRun + 3) / 4, (uint64_t)ctx->num_cus * 8);
+}
+
+hipError_t launch_validate_edges(agis_ctx* ctx, const DevGraph& g, uint32_t* d_flags, uint64_t* d_lower) {
+    if (g.nnz)
+        hipLaunchKernelGGL(k_validate_edges, dim3(run_grid(ctx, g.nnz)), dim3(256), 0, ctx->stream, g, d_flags,
+                           (unsigned long long*)d_lower);
     return hipGetLastError();
 }
 
@@ -684,54 +696,72 @@ __global__ void k_tables_init(DevGraph g, uint4* rec, uint64_t* s2, uint64_t* hi
     hits[v] = 0;
 }
 
-// One thread per edge slot (v, x): adds d(x) to S2(v) and, for the sampled
+// One lane per edge slot (v, x): adds d(x) to S2(v) and, for the sampled
 // clustering coefficient, runs trial t = slot - off[v] of vertex v: an
 // ordered pair (a, b) of distinct neighbour positions from Philox key
 // cv_seed, counter (v, t, 0, tag 0 / tag 1), a hit when the two neighbours
-// are adjacent.  For the exact coefficient, counts the neighbours z > x of v
-// that are adjacent to x (each edge among N(v) once).
+// are adjacent: a bit probe when either has a neighbourhood bitmap (hub_slot
+// given), else a search of the shorter of their lists.  For the exact
+// coefficient, counts the neighbours z > x of v that are adjacent to x (each
+// edge among N(v) once).  (With a search of the offsets per slot and of the
+// first neighbour's list per trial: 3.1 ms on R-MAT-20.)
 __global__ __launch_bounds__(256) void k_tables_edges(DevGraph g, DevGraph adj, const uint4* rec, uint64_t* s2,
-                                                       uint64_t* hits, uint32_t k0, uint32_t k1, int exact) {
-    // grid-stride over slots; the loop bound is uniform in a workgroup, so
-    // every lane of a wave takes part in the wave-wide sums below
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t base = (uint64_t)blockIdx.x * blockDim.x; base < g.nnz; base += stride) {
-    const uint64_t e = base + threadIdx.x;
-    const bool active = e < g.nnz;
-    uint32_t v = 0xFFFFFFFFu;
-    uint64_t dx = 0, h = 0;
-    if (active) {
-        v = row_of_slot(g.off, g.n, e);
-        const uint32_t x = g.nbr[e];
-        const uint64_t ov = g.off[v];
-        const uint32_t d = rec[v].x;
-        dx = rec[x].x;
-        const uint32_t* row = g.nbr + ov;
-        if (d >= 2 && !exact) {
-            const uint32_t t = (uint32_t)(e - ov);
-            const uint64_t a = bounded_draw(k0, k1, v, t, 0, 0, d);
-            uint64_t b = bounded_draw(k0, k1, v, t, 0, 1, d - 1);
-            if (b >= a) ++b;
-            const uint32_t y = row[a], z = row[b];
-            const uint64_t oy = adj.off[y];
-            h = contains_u32(adj.nbr + oy, (uint32_t)(adj.off[y + 1] - oy), z) ? 1u : 0u;
-        } else if (d >= 2) {
-            const uint64_t ox = adj.off[x];
-            const uint32_t dxx = (uint32_t)(adj.off[x + 1] - ox);
-            for (uint32_t p = lower_bound_u32(row, d, x + 1); p < d; ++p)
-                if (contains_u32(adj.nbr + ox, dxx, row[p])) ++h;
+                                                       uint64_t* hits, const int32_t* __restrict__ hub_slot,
+                                                       const uint32_t* __restrict__ hub_bits, uint64_t hub_words,
+                                                       uint32_t k0, uint32_t k1, int exact, uint64_t run) {
+    const uint64_t nw = (uint64_t)gridDim.x * (blockDim.x / kWave);
+    for (uint64_t r = (uint64_t)blockIdx.x * (blockDim.x / kWave) + uniform_u32(threadIdx.x / kWave);
+         r * run < g.nnz; r += nw) {
+        const uint64_t end = (r + 1) * run < g.nnz ? (r + 1) * run : g.nnz;
+        uint64_t v0 = wave_row_of_slot(g, r * run);
+        for (uint64_t e0 = r * run; e0 < end; e0 += kWave) {
+            const uint64_t e = e0 + (uint64_t)lane_id();
+            const bool active = e < g.nnz;
+            const uint64_t row_v = lane_row(g, e0, v0);
+            v0 = readlane_u64(row_v, kWave - 1);
+            const uint32_t v = active ? (uint32_t)row_v : 0xFFFFFFFFu;
+            uint64_t dx = 0, h = 0;
+            if (active) {
+                const uint32_t x = g.nbr[e];
+                const uint64_t ov = g.off[v];
+                const uint32_t d = rec[v].x;
+                dx = rec[x].x;
+                const uint32_t* row = g.nbr + ov;
+                if (d >= 2 && !exact) {
+                    const uint32_t t = (uint32_t)(e - ov);
+                    const uint64_t a = bounded_draw(k0, k1, v, t, 0, 0, d);
+                    uint64_t b = bounded_draw(k0, k1, v, t, 0, 1, d - 1);
+                    if (b >= a) ++b;
+                    const uint32_t y = row[a], z = row[b];
+                    const int32_t sy = hub_slot ? hub_slot[y] : -1, sz = hub_slot ? hub_slot[z] : -1;
+                    if (sy >= 0 || sz >= 0) {
+                        const uint32_t w = sy >= 0 ? z : y;
+                        h = hub_bits[(uint64_t)(sy >= 0 ? sy : sz) * hub_words + (w >> 5)] >> (w & 31u) & 1u;
+                    } else {
+                        const uint64_t oy = adj.off[y], oz = adj.off[z];
+                        const uint64_t dy = adj.off[y + 1] - oy, dz = adj.off[z + 1] - oz;
+                        const bool first = dy <= dz;
+                        h = contains_u32(adj.nbr + (first ? oy : oz), (uint32_t)(first ? dy : dz), first ? z : y) ? 1u
+                                                                                                                  : 0u;
+                    }
+                } else if (d >= 2) {
+                    const uint64_t ox = adj.off[x];
+                    const uint32_t dxx = (uint32_t)(adj.off[x + 1] - ox);
+                    for (uint32_t p = lower_bound_u32(row, d, x + 1); p < d; ++p)
+                        if (contains_u32(adj.nbr + ox, dxx, row[p])) ++h;
+                }
+            }
+            // consecutive slots mostly share a row: one atomic per row segment of the wave
+            int head;
+            bool tail;
+            wave_segments(v, head, tail);
+            const uint64_t sdx = wave_segmented_sum_u64(dx, head);
+            const uint64_t sh = wave_segmented_sum_u64(h, head);
+            if (active && tail) {
+                atomicAdd((unsigned long long*)&s2[v], (unsigned long long)sdx);
+                if (sh) atomicAdd((unsigned long long*)&hits[v], (unsigned long long)sh);
+            }
         }
-    }
-    // consecutive slots mostly share a row: one atomic per row segment of the wave
-    int head;
-    bool tail;
-    wave_segments(v, head, tail);
-    const uint64_t sdx = wave_segmented_sum_u64(dx, head);
-    const uint64_t sh = wave_segmented_sum_u64(h, head);
-    if (active && tail) {
-        atomicAdd((unsigned long long*)&s2[v], (unsigned long long)sdx);
-        if (sh) atomicAdd((unsigned long long*)&hits[v], (unsigned long long)sh);
-    }
     }
 }
 
@@ -757,16 +787,21 @@ __global__ void k_tables_finalize(DevGraph g, uint4* rec, const uint64_t* s2, co
     rec[v] = r;
 }
 
-hipError_t launch_build_tables(const DevGraph& g, const DevGraph& adj, uint4* rec, uint64_t* s2, uint64_t* hits,
-                               uint64_t* trials, uint32_t k0, uint32_t k1, int32_t lc_min, int exact,
-                               hipStream_t stream) {
+hipError_t launch_build_tables(agis_ctx* ctx, const DevGraph& g, const DevGraph& adj, const agis_tables& t, uint32_t k0,
+                               uint32_t k1, int32_t lc_min, int exact) {
     if (!g.n) return hipSuccess;
-    hipLaunchKernelGGL(k_tables_init, dim3(grid_for(g.n, 256)), dim3(256), 0, stream, g, rec, s2, hits);
+    hipStream_t stream = ctx->stream;
+    // (the bitmaps are of g's rows: of an oriented graph they do not decide adjacency)
+    const int32_t* hub_slot = adj.nbr == g.nbr && t.hub_bits ? t.hub_slot : nullptr;
+    hipLaunchKernelGGL(k_tables_init, dim3(grid_for(g.n, 256)), dim3(256), 0, stream, g, t.rec, t.s2, t.hits);
+    // (the exact count costs a slot of a long row thousands of searches: a
+    // wave takes 64 of them at a time)
     if (g.nnz)
-        hipLaunchKernelGGL(k_tables_edges, dim3(stride_grid(g.nnz, 256)), dim3(256), 0, stream, g, adj, rec, s2, hits,
-                           k0, k1, exact);
-    hipLaunchKernelGGL(k_tables_finalize, dim3(grid_for(g.n, 256)), dim3(256), 0, stream, g, rec, s2, hits, trials,
-                       lc_min, exact);
+        hipLaunchKernelGGL(k_tables_edges, dim3(exact ? stride_grid(g.nnz, 256) : run_grid(ctx, g.nnz)), dim3(256), 0,
+                           stream, g, adj, t.rec, t.s2, t.hits, hub_slot, t.hub_bits, t.hub_words, k0, k1, exact,
+                           exact ? (uint64_t)kWave : kSlotRun);
+    hipLaunchKernelGGL(k_tables_finalize, dim3(grid_for(g.n, 256)), dim3(256), 0, stream, g, t.rec, t.s2, t.hits,
+                       t.trials, lc_min, exact);
     return hipGetLastError();
 }
 
@@ -1061,10 +1096,6 @@ __global__ __launch_bounds__(256) void k_orient_fill(DevGraph g, const uint64_t*
 uint64_t orient_words(uint64_t nnz) { return (nnz + kWave - 1) / kWave; }
 uint64_t orient_runs(uint64_t nnz) { return (nnz + kSlotRun - 1) / kSlotRun; }
 
-static unsigned run_grid(const agis_ctx* ctx, uint64_t nnz) {
-    return (unsigned)std::min<uint64_t>((orient_runs(nnz) + 3) / 4, (uint64_t)ctx->num_cus * 8);
-}
-
 hipError_t launch_orient_offsets(agis_ctx* ctx, const DevGraph& g, uint32_t* deg, uint64_t* mask, uint64_t* run_kept,
                                  uint64_t* off_out) {
     hipStream_t st = ctx->stream;
@@ -1148,20 +1179,25 @@ hipError_t launch_hub_slots(agis_ctx* ctx, const DevGraph& g, uint32_t min_deg, 
     return hipGetLastError();
 }
 
-__global__ void k_hub_bits(DevGraph g, const int32_t* hub_slot, uint64_t words, uint32_t* bits) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < g.nnz; e += stride) {
-        const uint32_t v = row_of_slot(g.off, g.n, e);
-        const int32_t slot = hub_slot[v];
-        if (slot < 0) continue;
-        const uint32_t x = g.nbr[e];
-        atomicOr(&bits[(uint64_t)slot * words + (x >> 5)], 1u << (x & 31u));
+// Grid: (hubs, slices of a row).
+__global__ __launch_bounds__(256) void k_hub_bits(DevGraph g, const uint32_t* __restrict__ hub, uint64_t words,
+                                                  uint32_t* __restrict__ bits) {
+    const uint32_t v = hub[blockIdx.x];
+    const uint64_t o = g.off[v], d = g.off[v + 1] - o;
+    uint32_t* row = bits + (uint64_t)blockIdx.x * words;
+    const uint64_t step = (uint64_t)gridDim.y * blockDim.x;
+    for (uint64_t e = (uint64_t)blockIdx.y * blockDim.x + threadIdx.x; e < d; e += step) {
+        const uint32_t x = g.nbr[o + e];
+        atomicOr(row + (x >> 5), 1u << (x & 31u));
     }
 }
 
-hipError_t launch_hub_bits(const DevGraph& g, const int32_t* hub_slot, uint64_t words, uint32_t* bits,
-                           hipStream_t stream) {
-    if (g.nnz) hipLaunchKernelGGL(k_hub_bits, dim3(stride_grid(g.nnz, 256)), dim3(256), 0, stream, g, hub_slot, words, bits);
+__global__ void k_pair_hubs(const int32_t* __restrict__ pair_slot, uint64_t n, uint32_t* __restrict__ hub);
+
+hipError_t launch_hub_bits(const DevGraph& g, const int32_t* hub_slot, uint64_t hubs, uint32_t* hub, uint64_t words,
+                           uint32_t* bits, hipStream_t stream) {
+    hipLaunchKernelGGL(k_pair_hubs, dim3(grid_for(g.n, 256)), dim3(256), 0, stream, hub_slot, g.n, hub);
+    if (hubs) hipLaunchKernelGGL(k_hub_bits, dim3((unsigned)hubs, 4), dim3(256), 0, stream, g, hub, words, bits);
     return hipGetLastError();
 }
 
