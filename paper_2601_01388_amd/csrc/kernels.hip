@@ -642,15 +642,25 @@ __global__ __launch_bounds__(256) void k_validate_edges(DevGraph g, uint32_t* fl
     if (lane_id() == 0 && low) atomicAdd(lower, (unsigned long long)low);
 }
 
-__global__ void k_max_degree(DevGraph g, uint32_t* out) {
-    const uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    uint32_t d = v < g.n ? (uint32_t)(g.off[v + 1] - g.off[v]) : 0u;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        uint32_t w = __shfl_xor(d, o, kWave);
-        d = w > d ? w : d;
+// (a grid-stride loop and one atomic per workgroup: with one per wave, the
+// atomics on the one address took 0.19 ms on R-MAT-20)
+__global__ __launch_bounds__(256) void k_max_degree(DevGraph g, uint32_t* out) {
+    __shared__ int32_t wm[4];
+    int32_t d = 0;  // compared as signed with the top bit flipped
+    uint32_t m = 0;
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < g.n; v += stride) {
+        const uint32_t x = (uint32_t)(g.off[v + 1] - g.off[v]);
+        m = x > m ? x : m;
     }
-    if (lane_id() == 0 && d) atomicMax(out, d);
+    d = wave_max_i32((int32_t)(m ^ 0x80000000u));
+    if (lane_id() == 0) wm[threadIdx.x / kWave] = d;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 4; ++w) d = wm[w] > d ? wm[w] : d;
+        m = (uint32_t)d ^ 0x80000000u;
+        if (m) atomicMax(out, m);
+    }
 }
 
 static unsigned grid_for(uint64_t n, unsigned threads) { return (unsigned)((n + threads - 1) / threads); }
@@ -681,7 +691,8 @@ hipError_t launch_validate_edges(agis_ctx* ctx, const DevGraph& g, uint32_t* d_f
 }
 
 hipError_t launch_max_degree(const DevGraph& g, uint32_t* d_max, hipStream_t stream) {
-    if (g.n) hipLaunchKernelGGL(k_max_degree, dim3(grid_for(g.n, 256)), dim3(256), 0, stream, g, d_max);
+    if (g.n)
+        hipLaunchKernelGGL(k_max_degree, dim3(std::min(grid_for(g.n, 256), 1024u)), dim3(256), 0, stream, g, d_max);
     return hipGetLastError();
 }
 
@@ -858,12 +869,22 @@ __device__ __forceinline__ int32_t step0_log(const uint4* rec, const DevPlan& P,
 }
 }  // namespace
 
-__global__ void k_step1_max(const uint4* rec, DevPlan P, uint64_t n, int32_t* lmax) {
-    const uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// (one atomic per workgroup of a capped grid, as k_max_degree)
+__global__ __launch_bounds__(256) void k_step1_max(const uint4* rec, DevPlan P, uint64_t n, int32_t* lmax) {
+    __shared__ int32_t wm[4];
     int32_t l = kCertainZero;
-    if (v < n) l = step0_log(rec, P, v);
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
+        const int32_t x = step0_log(rec, P, v);
+        l = x > l ? x : l;
+    }
     l = wave_max_i32(l);
-    if (lane_id() == 0 && l != kCertainZero) atomicMax(lmax, l);
+    if (lane_id() == 0) wm[threadIdx.x / kWave] = l;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 4; ++w) l = wm[w] > l ? wm[w] : l;
+        if (l != kCertainZero) atomicMax(lmax, l);
+    }
 }
 
 __device__ __forceinline__ uint32_t step0_weight(const uint4* rec, const DevPlan& P, uint64_t v, int32_t lmax) {
@@ -1557,39 +1578,64 @@ __global__ __launch_bounds__(256) void k_core_fill(DevGraph g, const uint32_t* _
 // the inclusive prefix within the list of the entries' integer weights
 // against it (0 for certain zeros).  The weights themselves are not kept:
 // a draw recomputes the 64 of its block from the step's weight table.
+//
+// The gathers bound it, so an entry costs one: the log weights of a list of
+// up to 64 kCorePickRegs entries stay in registers between the maximum and
+// the sums (longer lists gather twice), and the exponent table is in the
+// LDS.  With two gathers and the exponents through the vector cache it took
+// 6.9 ms on the lists of the oriented R-MAT-20.
+constexpr int kCorePickRegs = 16;
+
 __global__ __launch_bounds__(256) void k_core_pick(const uint32_t* __restrict__ core_nbr,
                                                     const uint64_t* __restrict__ core_start,
                                                     const uint32_t* __restrict__ core_len, uint64_t C,
                                                     const int32_t* __restrict__ sw, int32_t* __restrict__ clm,
                                                     uint64_t* __restrict__ cbp) {
     const int lane = lane_id();
+    for (uint32_t e = threadIdx.x; e < 4096u; e += blockDim.x) s_exp2tab[e] = c_exp2tab[e];
+    __syncthreads();
     const uint64_t nw = (uint64_t)gridDim.x * (blockDim.x / kWave);
-    for (uint64_t pr = (uint64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave; pr < C * C; pr += nw) {
+    for (uint64_t pr = (uint64_t)blockIdx.x * (blockDim.x / kWave) + uniform_u32(threadIdx.x / kWave); pr < C * C;
+         pr += nw) {
         const uint64_t a = pr / C, b = pr % C;
         if (a > b) continue;  // wave-uniform; (b, a) shares the list
-        const uint64_t st = core_start[pr];
-        const uint64_t len = core_len[pr];
+        const uint64_t st = sload(core_start + pr);
+        const uint32_t len = sload(core_len + pr);
+        const uint32_t* list = core_nbr + st;
+        auto log_at = [&](uint32_t e) -> int32_t { return e < len ? sw[list[e]] : kCertainZero; };
+        int32_t l[kCorePickRegs];
         int32_t lm = kCertainZero;
-        for (uint64_t e = (uint64_t)lane; e < len; e += kWave) {
-            const int32_t l = sw[core_nbr[st + e]];
-            lm = l > lm ? l : lm;
+#pragma unroll
+        for (uint32_t u = 0; u < kCorePickRegs; ++u) {
+            l[u] = kCertainZero;
+            if (u * kWave < len) l[u] = log_at(u * kWave + (uint32_t)lane);
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kCorePickRegs; ++u) lm = l[u] > lm ? l[u] : lm;
+        for (uint32_t e0 = kCorePickRegs * kWave; e0 < len; e0 += kWave) {
+            const int32_t x = log_at(e0 + (uint32_t)lane);
+            lm = x > lm ? x : lm;
         }
         lm = wave_max_i32(lm);
         if (lane == 0) {
             clm[pr] = lm;
             clm[b * C + a] = lm;
         }
-        uint64_t run = 0;
-        for (uint64_t e0 = 0; e0 < len; e0 += kWave) {
-            const uint64_t e = e0 + (uint64_t)lane;
-            uint32_t q = 0;
-            if (e < len) {
-                const int32_t l = sw[core_nbr[st + e]];
-                q = l == kCertainZero ? 0u : weight_from_log(lm, l, c_exp2tab);
-            }
-            run += wave_sum_u64(q);
-            if (lane == 0) cbp[(st + e0) / kCoreBlock] = run;
-        }
+        // lane u takes the prefix of block u of each 64 (stored together)
+        uint64_t run = 0, mine = 0;
+        uint64_t* out = cbp + st / kCoreBlock;
+        auto block = [&](uint32_t u, int32_t x) {
+            const uint32_t w = weight_from_log(lm, x, s_exp2tab);
+            run += wave_sum_u64(x == kCertainZero ? 0ull : (uint64_t)w);
+            if ((uint32_t)lane == (u & 63u)) mine = run;
+            if ((u & 63u) == 63u) out[u - 63u + (uint32_t)lane] = mine;
+        };
+#pragma unroll
+        for (uint32_t u = 0; u < kCorePickRegs; ++u)
+            if (u * kWave < len) block(u, l[u]);
+        for (uint32_t u = kCorePickRegs; u * kWave < len; ++u) block(u, log_at(u * kWave + (uint32_t)lane));
+        const uint32_t nb = (len + kWave - 1) / kWave;
+        if ((uint32_t)lane < (nb & 63u)) out[(nb & ~63u) + (uint32_t)lane] = mine;
     }
 }
 
@@ -1646,7 +1692,7 @@ hipError_t build_step1_blocks(agis_ctx* ctx, const agis_graph& g, const agis_tab
     hipError_t e = hipMemcpyAsync(d_lmax, &init, sizeof(init), hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return e;
     const uint64_t nblk = (n + kStep1Block - 1) / kStep1Block;
-    hipLaunchKernelGGL(k_step1_max, dim3(grid_for(n, 256)), dim3(256), 0, st, t.rec, hp, n, d_lmax);
+    hipLaunchKernelGGL(k_step1_max, dim3(std::min(grid_for(n, 256), 1024u)), dim3(256), 0, st, t.rec, hp, n, d_lmax);
     const uint64_t wg = (nblk + 3) / 4;
     hipLaunchKernelGGL(k_step1_blocksum, dim3((unsigned)(wg < kStrideBlocks ? wg : kStrideBlocks)), dim3(256), 0, st,
                        t.rec, hp, n, d_lmax, blk);
@@ -1680,7 +1726,7 @@ hipError_t build_step1(agis_ctx* ctx, const agis_graph& g, const agis_tables& t,
         }
         blocksums = ctx->d_blocksums;
     }
-    hipLaunchKernelGGL(k_step1_max, dim3(grid_for(n, 256)), dim3(256), 0, st, t.rec, hp, n, d_lmax);
+    hipLaunchKernelGGL(k_step1_max, dim3(std::min(grid_for(n, 256), 1024u)), dim3(256), 0, st, t.rec, hp, n, d_lmax);
     hipLaunchKernelGGL(k_step1_tilesum, dim3((unsigned)ntiles), dim3(kScanThreads), 0, st, t.rec, hp, n, d_lmax,
                        blocksums);
     hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(1024), 0, st, blocksums, ntiles);
@@ -1695,16 +1741,27 @@ hipError_t build_step1(agis_ctx* ctx, const agis_graph& g, const agis_tables& t,
 
 // Entry v owns the buckets b with pre[v - 1] <= b << shift < pre[v]
 // (pre[-1] = 0): it is the first entry above each of their lower bounds.
+// One thread per bucket searches the prefix (a thread per vertex, writing
+// the buckets its weight spans, left one thread 36,000 of them for the
+// R-MAT-20 4-star's heaviest vertex: 0.84 ms).
 __global__ void k_prefix_guide(const uint64_t* __restrict__ pre, uint64_t n, uint64_t buckets, uint32_t shift,
                                uint32_t* __restrict__ guide) {
-    const uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= n) return;
-    const uint64_t lo = v ? pre[v - 1] : 0ull, hi = pre[v];
-    const uint64_t unit = 1ull << shift;
-    uint64_t b = (lo + unit - 1) >> shift;      // first b with b << shift >= lo
-    const uint64_t e = (hi + unit - 1) >> shift;  // first b with b << shift >= hi
-    for (; b < e && b < buckets; ++b) guide[b] = (uint32_t)v;
-    if (v == n - 1) guide[buckets] = (uint32_t)v;
+    const uint64_t b = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (b > buckets) return;
+    if (b == buckets) {
+        guide[b] = (uint32_t)(n - 1);
+        return;
+    }
+    const uint64_t r = b << shift;
+    uint64_t lo = 0, hi = n - 1;  // pre[n - 1] > r
+    while (lo < hi) {
+        const uint64_t mid = (lo + hi) >> 1;
+        if (pre[mid] > r)
+            hi = mid;
+        else
+            lo = mid + 1;
+    }
+    guide[b] = (uint32_t)lo;
 }
 
 uint32_t guide_shift(uint64_t total) {
@@ -1715,7 +1772,8 @@ uint32_t guide_shift(uint64_t total) {
 hipError_t launch_prefix_guide(const uint64_t* pre, uint64_t n, uint64_t total, uint32_t shift, uint32_t* guide,
                                hipStream_t stream) {
     const uint64_t buckets = ((total - 1) >> shift) + 1;
-    hipLaunchKernelGGL(k_prefix_guide, dim3(grid_for(n, 256)), dim3(256), 0, stream, pre, n, buckets, shift, guide);
+    hipLaunchKernelGGL(k_prefix_guide, dim3(grid_for(buckets + 1, 256)), dim3(256), 0, stream, pre, n, buckets, shift,
+                       guide);
     return hipGetLastError();
 }
 
