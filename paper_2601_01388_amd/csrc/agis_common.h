@@ -305,6 +305,11 @@ static_assert(sizeof(EpsPattern) == 256, "two 128-byte lines per pattern");
 // ring_samples weights and ring_samples / kEpsTile tiles (completed-sample
 // counter, partial statistics, and the index + 1 of the tile whose partial
 // is ready); slots are handed out only below merged + window.
+//
+// Ranks: workgroup b has rank b / rank_blocks (rank_blocks: one per compute
+// unit).  Ranks below kEpsFirst sample from the start; the others look now
+// and then whether samples are worth more waves, and join or leave.
+constexpr uint32_t kEpsFirst = 2;
 struct EpsDesc {
     AGIS_GMEM EpsPattern* pat;
     AGIS_GMEM double* ring;
@@ -318,6 +323,12 @@ struct EpsDesc {
     uint64_t window;
     uint32_t npat;
     uint32_t grab;          // slots per take from a pattern's counter
+    AGIS_GMEM uint32_t* ranks;  // ranks past kEpsFirst that sample, as far as known
+    AGIS_GMEM uint32_t* costs;  // wall-clock ticks of a sample of each workgroup of rank 0, 0: none yet
+    uint32_t rank_blocks;
+    uint32_t look_ticks;        // wall-clock ticks between two looks of a waiting workgroup
+    uint32_t join_ticks;        // mean ticks of a sample from which the others join
+    uint32_t pad0;
     double z;
     double eps;
 };

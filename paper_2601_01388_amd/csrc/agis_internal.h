@@ -82,7 +82,7 @@ struct agis_ctx {
     int tune_blocks_per_cu = 0;
     uint32_t tune_grab = 0;
     int use_graphs = 1;
-    int tune_variant = 2;  // sampling-kernel register budget (see sample_kernel)
+    int tune_variant = -1;  // sampling-kernel register budget (see sample_kernel; -1: the launch's own)
     uint32_t tune_hub_window = 0;  // see LaunchDesc::hub_window
     // captured round (k_zero, k_sample, k_reduce_x) replayed on graph_stream;
     // valid while the key below matches
@@ -285,6 +285,7 @@ struct SampleLaunch {
     uint64_t max_tiles = 0;  // reduction tiles of the largest round
     bool dump = false;       // launch the record-writing variant
     bool meter = false;      // launch the request-metering variant (needs idx)
+    bool eps = false;        // a run to epsilon (set by the caller before plan_sample_launch)
     int variant = 0;         // register-budget variant
     uint32_t hub_window = 0; // see LaunchDesc::hub_window
     // the kernel with the pair-hub paths (set by the caller before

@@ -1195,6 +1195,10 @@ int run_rounds(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, std::ve
 // Offsets in the context's small device buffer of the launch's start clock
 // and of the fault flag of a run to epsilon in one launch.
 constexpr uint32_t kClockOffset = 520;
+// A run to epsilon's later workgroups: time between two looks, and the mean
+// time of a sample from which they join (see eps_joins).
+constexpr int kEpsLookMicroseconds = 40;
+constexpr int kEpsJoinMicroseconds = 16;
 constexpr uint32_t kFaultOffset = 528;
 
 // Runs every pattern to epsilon (or its budget) in one persistent launch
@@ -1219,6 +1223,7 @@ int run_device_eps(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, std
              "upload plans");
     if (total == 0) return AGIS_OK;
     agis::SampleLaunch L;
+    L.eps = true;
     for (const PatternRun& r : runs) L.pairs = L.pairs || uses_pair_hubs(r.prep.hp, t);
     int rc = agis::plan_sample_launch(ctx, *g, std::min<uint64_t>(total, kMaxRoundSlots), npat, &L, &ctx->err);
     if (rc != AGIS_OK) return rc;
@@ -1237,7 +1242,9 @@ int run_device_eps(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, std
     const size_t ready_bytes = (size_t)npat * rtiles * sizeof(unsigned long long);
     const size_t done_bytes = (size_t)npat * rtiles * sizeof(uint32_t);
     auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-    const size_t need = up(pat_bytes) + up(ring_bytes) + up(part_bytes) + up(ready_bytes) + up(done_bytes);
+    const uint32_t rank_blocks = (uint32_t)std::max(1, ctx->num_cus);
+    const size_t rank_bytes = (1 + (size_t)rank_blocks) * sizeof(uint32_t);
+    const size_t need = up(rank_bytes) + up(pat_bytes) + up(ring_bytes) + up(part_bytes) + up(ready_bytes) + up(done_bytes);
     if (ctx->eps_bytes < need) {
         if (ctx->d_eps) (void)hipFree(ctx->d_eps);
         ctx->d_eps = nullptr;
@@ -1251,6 +1258,7 @@ int run_device_eps(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, std
     Partial* d_part = (Partial*)((char*)d_ring + up(ring_bytes));
     unsigned long long* d_ready = (unsigned long long*)((char*)d_part + up(part_bytes));
     uint32_t* d_done = (uint32_t*)((char*)d_ready + up(ready_bytes));
+    uint32_t* d_ranks = (uint32_t*)((char*)d_done + up(done_bytes));
     std::vector<agis::EpsPattern> hp(npat);
     std::memset(hp.data(), 0, pat_bytes);
     for (uint32_t p = 0; p < npat; ++p) {
@@ -1262,10 +1270,10 @@ int run_device_eps(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, std
         hp[p].stop = runs[p].budget == 0 ? 1u : 0u;
     }
     AGIS_HIP(ctx, hipMemcpyAsync(d_pat, hp.data(), pat_bytes, hipMemcpyHostToDevice, ctx->stream), "upload states");
-    // counters and ready marks start at zero (fill kernels, not memsets: the
-    // sequence could be captured)
-    AGIS_HIP(ctx, agis::launch_fill_u32(d_done, npat * rtiles, 0u, ctx->stream), "clear tile counters");
-    AGIS_HIP(ctx, agis::launch_fill_u32((uint32_t*)d_ready, 2 * npat * rtiles, 0u, ctx->stream), "clear tile marks");
+    // ready marks, tile counters, ranks and sample times start at zero (a fill
+    // kernel, not a memset: the sequence could be captured)
+    const size_t clear_bytes = up(ready_bytes) + up(done_bytes) + up(rank_bytes);
+    AGIS_HIP(ctx, agis::launch_fill_u32((uint32_t*)d_ready, clear_bytes / 4, 0u, ctx->stream), "clear run-to-eps state");
     *ctx->h_cancel = 0;
     unsigned long long* d_clock = (unsigned long long*)((char*)ctx->d_small + kClockOffset);
     uint32_t* d_fault = (uint32_t*)((char*)ctx->d_small + kFaultOffset);
@@ -1290,6 +1298,11 @@ int run_device_eps(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, std
     // the largest grab of a wave (grabs grow with the merged count, see
     // k_sample_eps): 16 slots per atomic on the pattern's counter
     E.grab = std::max<uint32_t>(L.grab, 16u);
+    E.ranks = agis::gmem(d_ranks);
+    E.costs = agis::gmem(d_ranks + 1);
+    E.rank_blocks = rank_blocks;
+    E.look_ticks = (uint32_t)((int64_t)kEpsLookMicroseconds * ctx->wall_clock_khz / 1000);
+    E.join_ticks = (uint32_t)((int64_t)kEpsJoinMicroseconds * ctx->wall_clock_khz / 1000);
     E.z = z;
     E.eps = pp->eps;
     AGIS_HIP(ctx, hipMemcpyAsync(ctx->d_launch, &ld, sizeof(ld), hipMemcpyHostToDevice, ctx->stream), "upload launch");

@@ -3571,6 +3571,53 @@ __device__ void merge_ready(const EpsDesc& E, uint32_t p) {
 // stopped or handed out its budget; the host's cancel flag stops every
 // pattern at its merged prefix.
 constexpr uint32_t kWindowSpins = 1u << 22;
+constexpr uint32_t kJoinLooks = 1u << 20;  // bound of a workgroup's looks before it joins
+
+// Whether a workgroup of a later rank samples: waits until the samples of
+// rank 0 prove to be long (true), or every pattern has stopped (false).
+// Every wave takes its slots from the pattern's counter and counts them into
+// their tile, and atomics on one address are served one at a time, about 7.5
+// million per second: with 6144 waves at once, the first slot of each alone
+// takes 0.8 ms, which is many times what a run of a few thousand short samples
+// needs.  2048 waves serve those (R-MAT-15 3-star to 1%, 4096 samples: 0.79
+// ms with all waves, 0.28 with 2 workgroups per CU; triangles at 188K samples
+// 2.7 and 1.0), all of them samples of 20 us and more (R-MAT-20 house: 5.2
+// and 8.9).  Costs of runs that want all waves lie above 16 us a sample and
+// those of runs that do not below 12 (joining from 8 us on gave the latter
+// 2.0 ms instead of 1.0).
+__device__ __forceinline__ bool eps_joins(const EpsDesc& E, uint32_t rank) {
+    __shared__ uint32_t joins;
+    if (threadIdx.x < kWave) {
+        const uint32_t lane = threadIdx.x;
+        uint32_t in = 2u;
+        uint64_t since = wall_clock64();
+        for (uint32_t look = 0; look < kJoinLooks && in == 2u; ++look) {
+            while (wall_clock64() - since < E.look_ticks) __builtin_amdgcn_s_sleep(32);
+            since = wall_clock64();
+            const bool runs = lane < E.npat && ld_dev(&E.pat[lane].stop) == 0u;
+            double sum = 0.0, num = 0.0;
+            for (uint32_t b = lane; b < E.rank_blocks; b += kWave) {
+                const uint32_t c = ld_dev(E.costs + b);
+                sum += (double)c;
+                num += c ? 1.0 : 0.0;
+            }
+            for (int o = 1; o < kWave; o <<= 1) {
+                sum += __shfl_xor(sum, o, kWave);
+                num += __shfl_xor(num, o, kWave);
+            }
+            if (!__ballot(runs))
+                in = 0u;
+            else if (sum >= num * (double)E.join_ticks)  // (none has finished one: long)
+                in = 1u;
+        }
+        if (lane == 0) {
+            joins = in;
+            if (in && blockIdx.x % E.rank_blocks == 0) atomicMax(E.ranks, rank + 1u - kEpsFirst);
+        }
+    }
+    __syncthreads();
+    return joins != 0u;
+}
 
 template <int kWavesPerEU, bool kPairs>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU)))
@@ -3579,6 +3626,8 @@ void k_sample_eps(const LaunchDesc* __restrict__ D) {
     for (uint32_t e = threadIdx.x; e < 4096u; e += blockDim.x) s_exp2tab[e] = c_exp2tab[e];
     __syncthreads();
     if (blockIdx.x == 0 && threadIdx.x == 0) *D->eps.clock0 = wall_clock64();
+    const uint32_t rank = blockIdx.x / D->eps.rank_blocks;
+    if (rank >= kEpsFirst && !eps_joins(D->eps, rank)) return;
     const uint64_t gw = (uint64_t)blockIdx.x * (blockDim.x / kWave) + uniform_u32(threadIdx.x / kWave);
     const uint64_t cap = D->cap;
     uint32_t* sv = D->scratch + gw * cap * 2;
@@ -3605,7 +3654,10 @@ void k_sample_eps(const LaunchDesc* __restrict__ D) {
     // check point / waves)), so the samples in flight stay about a quarter
     // of those merged (few drawn past an early stop) and a slow sample
     // holds few slots behind it (the merge is in index order).
-    const uint64_t nwaves = (uint64_t)gridDim.x * (blockDim.x / kWave);
+    // (waves: those that sample, as far as known)
+    const uint64_t awaves = (uint64_t)gridDim.x * (blockDim.x / kWave);
+    const uint64_t rwaves = (uint64_t)E.rank_blocks * (blockDim.x / kWave);
+    const bool tells = blockIdx.x < E.rank_blocks && threadIdx.x < kWave;
     uint64_t seen = 0;  // the current pattern's merged count, as last read
     uint64_t cost = 0;  // wall-clock ticks (10 ns) of this wave's last sample
     for (;;) {
@@ -3631,6 +3683,8 @@ void k_sample_eps(const LaunchDesc* __restrict__ D) {
         }
         AGIS_GMEM EpsPattern* P = E.pat + p;
         const uint64_t budget = P->budget;
+        uint64_t nwaves = (kEpsFirst + uniform_u32(ld_dev(E.ranks))) * rwaves;
+        nwaves = nwaves < awaves ? nwaves : awaves;
         // (no stop comes before the first check point, so the samples up to
         // it are spread over all waves at once)
         const uint64_t chk = P->check;
@@ -3705,6 +3759,7 @@ void k_sample_eps(const LaunchDesc* __restrict__ D) {
                 ++cnt;
             }
             if (cnt == 0) break;
+            if (tells && lane == 0) st_dev(E.costs + blockIdx.x, (uint32_t)(cost < 1000000000ull ? cost + 1 : cost));
             const uint64_t slot = (uint64_t)p * rtiles + (tcur & (rtiles - 1));
             uint32_t last = 0;
             if (lane == 0) {
@@ -3799,7 +3854,11 @@ int plan_sample_launch(agis_ctx* ctx, const agis_graph& g, uint64_t max_slots, u
         const uint64_t q = (uint64_t)free_b / 2 + ctx->scratch_bytes / 2;
         budget = q < (8ull << 30) ? (8ull << 30) : (q > (64ull << 30) ? (64ull << 30) : q);
     }
-    L->variant = ctx->tune_variant;
+    // register budget: 8 waves per SIMD for fixed-size runs, 6 for runs to
+    // epsilon (a pass of 4M 5-cycle samples takes 11.7 ms at 8 and 13.7 at 6;
+    // a house to 1% takes 5.45 at 8 and 5.22 at 6, short runs 10 to 25% less
+    // at 6, the 5-vertex concentrations 53.3 at 8 and 54.3 at 6)
+    L->variant = ctx->tune_variant >= 0 ? ctx->tune_variant : (L->eps ? 0 : 2);
     L->hub_window = ctx->tune_hub_window;
     int& cached = L->lanes ? ctx->lanes_blocks_per_cu : ctx->sample_blocks_per_cu[L->variant * 2 + (L->pairs ? 1 : 0)];
     if (cached == 0) {
