@@ -235,12 +235,13 @@ constexpr uint32_t kMaxSegs = 64;
 // Slot-queue counters of a round: kQueues of them, kQueueStride 64-bit
 // entries (256 bytes) apart, from byte kQueueOffset of the context's small
 // device buffer; kNoSlot marks an empty part.
-constexpr uint32_t kQueues = 8;
+constexpr uint32_t kQueues = 32;
 // XCDs of the device (MI355X: 8, each with its own L2); workgroups are dealt
 // to them round robin by workgroup index
 constexpr uint32_t kXcds = 8;
 constexpr uint32_t kQueueStride = 32;
 constexpr uint32_t kQueueOffset = 2048;
+constexpr uint32_t kSmallBytes = kQueueOffset + kQueues * kQueueStride * 8;  // of that buffer
 constexpr uint64_t kNoSlot = ~0ull;
 
 struct Segment {

@@ -69,7 +69,7 @@ struct agis_ctx {
     size_t partials_cap = 0;
     void* d_scratch = nullptr;
     size_t scratch_bytes = 0;
-    void* d_small = nullptr;  // 4 KiB of flags / reduction cells
+    void* d_small = nullptr;  // kSmallBytes of flags, reduction cells and slot counters
     uint64_t* d_blocksums = nullptr;
     size_t blocksums_cap = 0;
     double* d_xout = nullptr;  // per-sample weights of the current round

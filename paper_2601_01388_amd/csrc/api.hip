@@ -1407,7 +1407,7 @@ int agis_create(agis_ctx** out, int device, void* hip_stream) {
     }
     if (e == hipSuccess) e = hipMalloc(&ctx->d_plans, agis::kMaxSegs * sizeof(DevPlan));
     if (e == hipSuccess) e = hipMalloc(&ctx->d_launch, sizeof(agis::LaunchDesc));
-    if (e == hipSuccess) e = hipMalloc(&ctx->d_small, 4096);
+    if (e == hipSuccess) e = hipMalloc(&ctx->d_small, agis::kSmallBytes);
     if (e == hipSuccess) {
         // the fixed workspace of agis_estimate_noalloc; a failed lookup only
         // disables that entry point (it reports the failure)
