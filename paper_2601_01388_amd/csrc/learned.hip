@@ -47,18 +47,6 @@ __device__ __forceinline__ float gelu_grad(float a) {
     return 0.5f * (1.0f + erff(a * 0.70710678118654752f)) + a * 0.39894228040143268f * expf(-0.5f * a * a);
 }
 
-__device__ __forceinline__ uint32_t lower_bound_u32(const uint32_t* __restrict__ list, uint32_t len, uint32_t x) {
-    uint32_t lo = 0, hi = len;
-    while (lo < hi) {
-        uint32_t mid = (lo + hi) >> 1;
-        if (list[mid] < x)
-            lo = mid + 1;
-        else
-            hi = mid;
-    }
-    return lo;
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -71,18 +59,33 @@ __device__ __forceinline__ uint32_t lower_bound_u32(const uint32_t* __restrict__
 // of those with d <= kLaneDeg are gathered by the whole wave as one
 // concatenated list (element e belongs to the lane whose exclusive prefix
 // of degrees is the last one <= e), so the loads are independent; each such
-// lane then scans its histogram column from h = d down.  Vertices of larger
-// degree go to a list for k_features_big.
+// lane then scans its histogram column from h = d down.  Vertices of degree
+// up to kWaveDeg go to the front of a list for k_features_wave, the others to
+// its back for k_features_big.
+//
+// k_features_wave: one wave per listed vertex holds the neighbour degrees in
+// registers (each is gathered once) and finds the h-index by bisection, a
+// count being one compare and one scalar bit count per 64 neighbours.
+// R-MAT-22 (4M vertices): 0.74 ms; with every vertex past kLaneDeg in
+// k_features_big, whose barriers then were most of the work, 3.9 ms.
 //
 // k_features_big: one workgroup per listed vertex narrows [lo, hi] (lo
-// always feasible) by 256-bucket histograms of the degrees >= lo: bucket b
+// always feasible) by histograms (a bucket a thread) of the degrees >= lo: bucket b
 // holds degrees in [lo + b w, lo + (b + 1) w) with w a power of two, the
 // last bucket also everything above; suffix sums give the count of degrees
 // >= lo + b w, and the feasible thresholds form a prefix of the buckets.
-// Three passes cover any degree below 2^24.
+// Three passes cover any degree below 2^24.  Workgroups of 256 take the rows
+// up to kHubDeg, of 1024 the others (one hub at a time holds up the kernel:
+// 1.58 ms with 256 threads for all, 0.25 + 0.44 so); kHeldPer neighbours per
+// thread stay in registers from one pass to the next, and longer rows are
+// read that many per thread at a time, so their loads overlap.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kLaneDeg = 32;
+constexpr uint32_t kWaveDeg = 1024;
 constexpr int kFeatThreads = 256;
+constexpr int kHubThreads = 1024;   // of k_features_big for rows past kHubDeg
+constexpr uint32_t kHeldPer = 16;   // neighbours a thread of k_features_big holds
+constexpr uint32_t kHubDeg = kHeldPer * kFeatThreads;
 constexpr int kFeatWaves = kFeatThreads / kWave;
 
 __device__ __forceinline__ void write_features(float* __restrict__ feats, uint64_t v, uint32_t d, uint64_t s2,
@@ -99,8 +102,8 @@ __global__ __launch_bounds__(kFeatThreads) void k_features(DevGraph g, const uin
                                                            const uint64_t* __restrict__ s2,
                                                            const uint64_t* __restrict__ hits,
                                                            const uint64_t* __restrict__ trials,
-                                                           float* __restrict__ feats, uint32_t* __restrict__ big,
-                                                           uint32_t* __restrict__ nbig) {
+                                                           float* __restrict__ feats, uint32_t* __restrict__ list,
+                                                           uint32_t* __restrict__ nlist) {
     // histogram bin b of lane l of wave w: hist[w][b][l], bins 0..kLaneDeg
     __shared__ uint32_t hist[kFeatWaves][kLaneDeg + 1][kWave];
     __shared__ uint32_t s_excl[kFeatWaves][kWave];
@@ -152,62 +155,174 @@ __global__ __launch_bounds__(kFeatThreads) void k_features(DevGraph g, const uin
             }
             write_features(feats, v, d, s2[v], hits[v], trials[v], h);
         }
-        const uint64_t bm = __ballot(have && !small);
+        const uint64_t below = (1ull << lane) - 1ull;
+        const uint64_t mm = __ballot(have && !small && d <= kWaveDeg);
+        const uint64_t bm = __ballot(have && d > kWaveDeg);
+        if (mm) {
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(nlist, (uint32_t)__popcll(mm));
+            at = (uint32_t)__shfl((int)at, 0, kWave);
+            if (mm >> lane & 1ull) list[at + (uint32_t)__popcll(mm & below)] = (uint32_t)v;
+        }
         if (bm) {
-            uint32_t base = 0;
-            if (lane == 0) base = atomicAdd(nbig, (uint32_t)__popcll(bm));
-            base = (uint32_t)__shfl((int)base, 0, kWave);
-            if (have && !small) big[base + (uint32_t)__popcll(bm & ((1ull << lane) - 1ull))] = (uint32_t)v;
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(nlist + 1, (uint32_t)__popcll(bm));
+            at = (uint32_t)__shfl((int)at, 0, kWave);
+            if (bm >> lane & 1ull) list[g.n - 1 - (at + (uint32_t)__popcll(bm & below))] = (uint32_t)v;
         }
         __syncthreads();  // the LDS of this iteration is rewritten by the next
     }
 }
 
-__global__ __launch_bounds__(kFeatThreads) void k_features_big(DevGraph g, const uint4* __restrict__ rec,
-                                                               const uint64_t* __restrict__ s2,
-                                                               const uint64_t* __restrict__ hits,
-                                                               const uint64_t* __restrict__ trials,
-                                                               float* __restrict__ feats,
-                                                               const uint32_t* __restrict__ big,
-                                                               const uint32_t* __restrict__ nbig) {
-    __shared__ uint32_t cnt[kFeatThreads];
-    const uint32_t m = *nbig;
-    const int t = (int)threadIdx.x;
-    for (uint32_t i = blockIdx.x; i < m; i += gridDim.x) {
-        const uint64_t v = big[i];
+// h-index of the d <= 64 R neighbour degrees of the row at o, by one wave.
+template <int R>
+__device__ __forceinline__ uint32_t wave_hindex(const uint4* __restrict__ rec, const uint32_t* __restrict__ row,
+                                                uint32_t d) {
+    uint32_t x[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t e = (uint32_t)(r * kWave + lane_id());
+        x[r] = e < d ? row[e] : 0u;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t e = (uint32_t)(r * kWave + lane_id());
+        x[r] = e < d ? rec[x[r]].x : 0u;  // (0 is below every threshold)
+    }
+    uint32_t lo = 0, hi = d;
+    while (lo < hi) {
+        const uint32_t mid = lo + (hi - lo + 1) / 2;
+        uint32_t c = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) c += (uint32_t)__popcll(__ballot(x[r] >= mid));
+        if (c >= mid)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    return lo;
+}
+
+__global__ __launch_bounds__(kFeatThreads) void k_features_wave(DevGraph g, const uint4* __restrict__ rec,
+                                                                const uint64_t* __restrict__ s2,
+                                                                const uint64_t* __restrict__ hits,
+                                                                const uint64_t* __restrict__ trials,
+                                                                float* __restrict__ feats,
+                                                                const uint32_t* __restrict__ list,
+                                                                const uint32_t* __restrict__ nlist) {
+    const uint32_t m = nlist[0];
+    const uint32_t wave = blockIdx.x * kFeatWaves + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    for (uint32_t i = wave; i < m; i += gridDim.x * kFeatWaves) {
+        const uint64_t v = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)list[i]);
         const uint64_t o = g.off[v];
         const uint32_t d = (uint32_t)(g.off[v + 1] - o);
+        const uint32_t* row = g.nbr + o;
+        uint32_t h;
+        if (d <= 1 * kWave)
+            h = wave_hindex<1>(rec, row, d);
+        else if (d <= 2 * kWave)
+            h = wave_hindex<2>(rec, row, d);
+        else if (d <= 4 * kWave)
+            h = wave_hindex<4>(rec, row, d);
+        else if (d <= 8 * kWave)
+            h = wave_hindex<8>(rec, row, d);
+        else
+            h = wave_hindex<16>(rec, row, d);
+        if (lane_id() == 0) write_features(feats, v, d, s2[v], hits[v], trials[v], h);
+    }
+}
+static_assert(kWaveDeg == 16 * kWave, "the widest row of k_features_wave");
+
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void k_features_big(DevGraph g, const uint4* __restrict__ rec,
+                                                           const uint64_t* __restrict__ s2,
+                                                           const uint64_t* __restrict__ hits,
+                                                           const uint64_t* __restrict__ trials,
+                                                           float* __restrict__ feats,
+                                                           const uint32_t* __restrict__ list,
+                                                           const uint32_t* __restrict__ nlist, uint32_t dmin,
+                                                           uint32_t dmax) {
+    constexpr int kWaves = kThreads / kWave;
+    constexpr uint32_t kHold = kHeldPer * kThreads;
+    __shared__ uint32_t cnt[kThreads];
+    __shared__ uint32_t wsum[kWaves];
+    const uint32_t m = nlist[1];
+    const int t = (int)threadIdx.x;
+    const int lane = lane_id(), wave = t / kWave;
+    for (uint32_t i = blockIdx.x; i < m; i += gridDim.x) {
+        const uint64_t v = list[g.n - 1 - i];
+        const uint64_t o = g.off[v];
+        const uint32_t d = (uint32_t)(g.off[v + 1] - o);
+        if (d < dmin || d > dmax) continue;
+        const uint32_t* __restrict__ row = g.nbr + o;
+        uint32_t held[kHeldPer];
+        if (d <= kHold) {
+#pragma unroll
+            for (uint32_t r = 0; r < kHeldPer; ++r) {
+                const uint32_t e = r * kThreads + (uint32_t)t;
+                held[r] = e < d ? row[e] : 0u;
+            }
+#pragma unroll
+            for (uint32_t r = 0; r < kHeldPer; ++r) {
+                const uint32_t e = r * kThreads + (uint32_t)t;
+                held[r] = e < d ? rec[held[r]].x : 0u;
+            }
+        }
         uint32_t lo = 0, hi = d;  // the h-index is in [lo, hi]; lo is feasible
         while (lo < hi) {
             const uint64_t span = (uint64_t)hi - lo + 1;
             uint32_t sh = 0;
-            while (((uint64_t)kFeatThreads << sh) < (uint64_t)span) ++sh;
+            while (((uint64_t)kThreads << sh) < (uint64_t)span) ++sh;
             cnt[t] = 0;
             __syncthreads();
-            for (uint32_t e = (uint32_t)t; e < d; e += kFeatThreads) {
-                const uint32_t x = rec[g.nbr[o + e]].x;
+            auto count = [&](uint32_t x) {
                 if (x >= lo) {
                     const uint32_t b = (x - lo) >> sh;
-                    atomicAdd(&cnt[b < (uint32_t)kFeatThreads ? b : (uint32_t)kFeatThreads - 1u], 1u);
+                    atomicAdd(&cnt[b < (uint32_t)kThreads ? b : (uint32_t)kThreads - 1u], 1u);
+                }
+            };
+            if (d <= kHold) {
+#pragma unroll
+                for (uint32_t r = 0; r < kHeldPer; ++r)
+                    if (r * kThreads + (uint32_t)t < d) count(held[r]);
+            } else {
+                for (uint32_t e0 = 0; e0 < d; e0 += kHold) {
+                    uint32_t x[kHeldPer];
+#pragma unroll
+                    for (uint32_t r = 0; r < kHeldPer; ++r) {
+                        const uint64_t e = (uint64_t)e0 + r * kThreads + (uint32_t)t;
+                        x[r] = e < d ? row[e] : 0u;
+                    }
+#pragma unroll
+                    for (uint32_t r = 0; r < kHeldPer; ++r) {
+                        const uint64_t e = (uint64_t)e0 + r * kThreads + (uint32_t)t;
+                        x[r] = e < d ? rec[x[r]].x : 0u;
+                    }
+#pragma unroll
+                    for (uint32_t r = 0; r < kHeldPer; ++r)
+                        if ((uint64_t)e0 + r * kThreads + (uint32_t)t < d) count(x[r]);
+                    if (d - e0 <= kHold) break;
                 }
             }
             __syncthreads();
-            // suffix sums: cnt[b] becomes the number of degrees >= lo + b w
-            for (int step = 1; step < kFeatThreads; step <<= 1) {
-                const uint32_t add = t + step < kFeatThreads ? cnt[t + step] : 0u;
-                __syncthreads();
-                cnt[t] += add;
-                __syncthreads();
+            // suffix sums: c becomes the number of degrees >= lo + t w
+            uint32_t c = cnt[t];
+#pragma unroll
+            for (int step = 1; step < kWave; step <<= 1) {
+                const uint32_t add = (uint32_t)__shfl_down((int)c, step, kWave);
+                if (lane + step < kWave) c += add;
             }
+            if (lane == 0) wsum[wave] = c;
+            __syncthreads();
+            for (int w = wave + 1; w < kWaves; ++w) c += wsum[w];
             const uint64_t thr = (uint64_t)lo + ((uint64_t)t << sh);
-            const int ok = thr <= hi && (uint64_t)cnt[t] >= thr;
+            const int ok = thr <= hi && (uint64_t)c >= thr;
             const int nok = __syncthreads_count(ok);
             const uint32_t nlo = lo + ((uint32_t)(nok - 1) << sh);
             hi = (uint32_t)min<uint64_t>((uint64_t)hi, (uint64_t)nlo + (1ull << sh) - 1ull);
             lo = nlo;
         }
         if (t == 0) write_features(feats, v, d, s2[v], hits[v], trials[v], lo);
-        __syncthreads();
     }
 }
 
@@ -642,26 +757,39 @@ int agis_features(agis_ctx* ctx, const agis_tables* t, float* feats) {
     const agis::DevGraph& g = t->graph->g;
     if (g.n == 0) return AGIS_OK;
     if (g.n > UINT32_MAX) return lfail(ctx, AGIS_E_INVALID_ARG, "features: more than 2^32 - 1 vertices");
-    // list of the vertices of degree above the per-lane limit, and its length
-    uint32_t* big = nullptr;
-    LHIP(ctx, ctx->pool->alloc(&big, (size_t)(g.n + 1) * sizeof(uint32_t)), "allocate feature list");
-    uint32_t* nbig = big + g.n;
-    hipError_t e = hipMemsetAsync(nbig, 0, sizeof(uint32_t), ctx->stream);
+    // list of the vertices of degree above the per-lane limit (see
+    // k_features), and the lengths of its front and back parts
+    uint32_t* list = nullptr;
+    LHIP(ctx, ctx->pool->alloc(&list, (size_t)(g.n + 2) * sizeof(uint32_t)), "allocate feature list");
+    uint32_t* nlist = list + g.n;
+    hipError_t e = hipMemsetAsync(nlist, 0, 2 * sizeof(uint32_t), ctx->stream);
     const uint64_t groups = (g.n + 63) / 64;
     const uint64_t blocks = std::min<uint64_t>((groups + agis::kFeatWaves - 1) / agis::kFeatWaves,
                                                (uint64_t)ctx->num_cus * 8);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(agis::k_features, dim3((unsigned)blocks), dim3(agis::kFeatThreads), 0, ctx->stream, g,
-                           t->rec, t->s2, t->hits, t->trials, feats, big, nbig);
+                           t->rec, t->s2, t->hits, t->trials, feats, list, nlist);
         e = hipGetLastError();
     }
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(agis::k_features_big, dim3((unsigned)ctx->num_cus * 4), dim3(agis::kFeatThreads), 0,
-                           ctx->stream, g, t->rec, t->s2, t->hits, t->trials, feats, big, nbig);
+        hipLaunchKernelGGL(agis::k_features_big<agis::kHubThreads>, dim3((unsigned)ctx->num_cus * 2),
+                           dim3(agis::kHubThreads), 0, ctx->stream, g, t->rec, t->s2, t->hits, t->trials, feats, list,
+                           nlist, agis::kHubDeg + 1, UINT32_MAX);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(agis::k_features_big<agis::kFeatThreads>, dim3((unsigned)ctx->num_cus * 8),
+                           dim3(agis::kFeatThreads), 0, ctx->stream, g, t->rec, t->s2, t->hits, t->trials, feats, list,
+                           nlist, 0u, agis::kHubDeg);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(agis::k_features_wave, dim3((unsigned)ctx->num_cus * 8), dim3(agis::kFeatThreads), 0,
+                           ctx->stream, g, t->rec, t->s2, t->hits, t->trials, feats, list, nlist);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    ctx->pool->free(big);
+    ctx->pool->free(list);
     LHIP(ctx, e, "features");
     return AGIS_OK;
 }
