@@ -47,6 +47,12 @@ __device__ __forceinline__ float gelu_grad(float a) {
     return 0.5f * (1.0f + erff(a * 0.70710678118654752f)) + a * 0.39894228040143268f * expf(-0.5f * a * a);
 }
 
+// x of lane (l - kBy) mod 16 of this lane's row of 16.
+template <int kBy>
+__device__ __forceinline__ float row_rotated(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 | kBy, 0xf, 0xf, true));
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -624,10 +630,15 @@ __global__ __launch_bounds__(kReduceWaves* kWave) void k_mlp_reduce(
 // A[m = l % 32][k = 8 (l / 32) + j] and B[k = 8 (l / 32) + j][n = l % 32],
 // j = 0..7, and receives D[m = 8 (j / 4) + 4 (l / 32) + j % 4][n = l % 32],
 // j = 0..15.  Output: y (optional) and the Q16 table round(2^16 y).
+// The error function of the 64 GELUs per row and layer bounds it (vector
+// units); 4 waves per SIMD (128 registers) hide the rest: R-MAT-22, 4M rows,
+// 0.53 ms with 16 x 5 lane exchanges for layer 3's sums, 0.495 with 8 row
+// exchanges and rotations within rows, 0.45 with 4 waves instead of 3 as well
+// (6 waves spill: 0.9).
 // ---------------------------------------------------------------------------
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 
-__global__ __launch_bounds__(256) void k_mlp_infer(const float* __restrict__ params, const float* __restrict__ feats,
+__global__ __launch_bounds__(256, 4) void k_mlp_infer(const float* __restrict__ params, const float* __restrict__ feats,
                                                    uint64_t n, uint32_t cls, const int32_t* __restrict__ base,
                                                    float y_min, float y_max, int32_t* __restrict__ lt,
                                                    float* __restrict__ yout) {
@@ -688,16 +699,30 @@ __global__ __launch_bounds__(256) void k_mlp_infer(const float* __restrict__ par
         float part[16];
         for (int j = 0; j < 16; ++j)
             part[j] = w3n[0] * gelu(acc0[j] + b2n[0]) + w3n[1] * gelu(acc1[j] + b2n[1]);
-        for (int j = 0; j < 16; ++j) {
+        // The sum over the 32 lanes adds lane l ^ 16 first, then l ^ 8, 4, 2
+        // and 1.  The first step exchanges rows of 16 lanes between part[j]
+        // and part[j + 8], which leaves 8 values a lane: those of j < 8 in the
+        // even rows, the others in the odd ones.  From then on lane l's value
+        // depends on l mod 8, 4, ... only, so rotations within the row bring
+        // the same operands as the exchanges.
+        float y = 0.0f;
 #pragma unroll
-            for (int s = 16; s > 0; s >>= 1) part[j] += __shfl_xor(part[j], s, kWave);
+        for (int j = 0; j < 8; ++j) {
+            const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(part[j]), __float_as_uint(part[j + 8]),
+                                                             false, false);
+            float r = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+            r += row_rotated<8>(r);
+            r += row_rotated<4>(r);
+            r += row_rotated<2>(r);
+            r += row_rotated<1>(r);
+            y = (col & 15) == j ? r : y;
         }
-        // lane with col j < 16 of each half writes row m = 8 (j / 4) + 4 half + j % 4
-        if (col < 16) {
-            float y = b3;
-            for (int j = 0; j < 16; ++j)
-                if (j == col) y += part[j];
-            const int m = 8 * (col / 4) + 4 * half + (col % 4);
+        // lane with col % 16 < 8 of each row of 16 writes the sum of j =
+        // 8 (col / 16) + col % 16, row m = 8 (j / 4) + 4 half + j % 4
+        if ((col & 15) < 8) {
+            y = b3 + y;
+            const int j = 8 * (col >> 4) + (col & 15);
+            const int m = 8 * (j / 4) + 4 * half + (j % 4);
             const uint64_t r = tile * 32 + (uint64_t)m;
             if (r < n) {
                 // clamped to [y_min, y_max] and to +-2^13 (also maps NaN to a
@@ -771,19 +796,22 @@ int agis_features(agis_ctx* ctx, const agis_tables* t, float* feats) {
                            t->rec, t->s2, t->hits, t->trials, feats, list, nlist);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) {
+    // (a launch costs a small graph more than its work: only what the largest
+    // degree calls for)
+    const uint64_t dmax = t->graph->max_deg;
+    if (e == hipSuccess && dmax > agis::kHubDeg) {
         hipLaunchKernelGGL(agis::k_features_big<agis::kHubThreads>, dim3((unsigned)ctx->num_cus * 2),
                            dim3(agis::kHubThreads), 0, ctx->stream, g, t->rec, t->s2, t->hits, t->trials, feats, list,
                            nlist, agis::kHubDeg + 1, UINT32_MAX);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) {
+    if (e == hipSuccess && dmax > agis::kWaveDeg) {
         hipLaunchKernelGGL(agis::k_features_big<agis::kFeatThreads>, dim3((unsigned)ctx->num_cus * 8),
                            dim3(agis::kFeatThreads), 0, ctx->stream, g, t->rec, t->s2, t->hits, t->trials, feats, list,
                            nlist, 0u, agis::kHubDeg);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) {
+    if (e == hipSuccess && dmax > agis::kLaneDeg) {
         hipLaunchKernelGGL(agis::k_features_wave, dim3((unsigned)ctx->num_cus * 8), dim3(agis::kFeatThreads), 0,
                            ctx->stream, g, t->rec, t->s2, t->hits, t->trials, feats, list, nlist);
         e = hipGetLastError();
