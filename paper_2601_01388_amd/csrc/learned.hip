@@ -339,21 +339,62 @@ __global__ __launch_bounds__(kThreads) void k_features_big(DevGraph g, const uin
 // extensions of the prefix v_1..v_i without bias; a sample that failed
 // after step i contributes R_i = 0.  Sums and counts per (step, vertex).
 // ---------------------------------------------------------------------------
-__global__ void k_targets(const Record* __restrict__ recs, uint64_t m, uint32_t k, uint64_t n,
-                          double* __restrict__ sums, uint32_t* __restrict__ counts) {
-    const uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= m) return;
-    const Record& r = recs[j];
-    const int steps = r.steps;
-    const bool ok = r.fail_step < 0;
-    double prod = 1.0;
-    for (int i = (int)k - 1; i >= 0; --i) {
-        if (i < steps) {
-            const double R = ok ? prod : 0.0;
-            atomicAdd(&sums[(uint64_t)i * n + r.v[i]], R);
-            atomicAdd(&counts[(uint64_t)i * n + r.v[i]], 1u);
+//
+// Samples meet at hubs, and atomics on one address are served one at a time,
+// about 7.5 million per second.  A workgroup adds up kTargetRecords records
+// in LDS first: a table of kTargetCells cells, each claimed by the first
+// (step, vertex) that hashes there, receives what is added to its key, the
+// others go to memory directly; a hub is claimed within a few records, and
+// reaches memory once per workgroup.
+// 5-cliques on R-MAT-18, 1M records: 1.55 ms with every addition in memory,
+// 0.70 so (0.48 with 4096 records and 8192 cells, which take all of the LDS and
+// cost small calls 0.02 ms).
+constexpr int kTargetThreads = 512;
+constexpr uint32_t kTargetRecords = 2048;
+constexpr uint32_t kTargetCells = 4096;
+
+__global__ __launch_bounds__(kTargetThreads) void k_targets(const Record* __restrict__ recs, uint64_t m, uint32_t k,
+                                                            uint64_t n, double* __restrict__ sums,
+                                                            uint32_t* __restrict__ counts) {
+    __shared__ double c_sum[kTargetCells];
+    __shared__ unsigned long long c_key[kTargetCells];  // step * n + vertex + 1, 0: free
+    __shared__ uint32_t c_count[kTargetCells];
+    for (uint32_t c = threadIdx.x; c < kTargetCells; c += kTargetThreads) {
+        c_sum[c] = 0.0;
+        c_key[c] = 0ull;
+        c_count[c] = 0u;
+    }
+    __syncthreads();
+    const uint64_t j0 = (uint64_t)blockIdx.x * kTargetRecords;
+    const uint64_t j1 = j0 + kTargetRecords < m ? j0 + kTargetRecords : m;
+    for (uint64_t j = j0 + threadIdx.x; j < j1; j += kTargetThreads) {
+        const Record& r = recs[j];
+        const int steps = r.steps;
+        const bool ok = r.fail_step < 0;
+        double prod = 1.0;
+        for (int i = (int)k - 1; i >= 0; --i) {
+            if (i < steps) {
+                const double R = ok ? prod : 0.0;
+                const uint64_t at = (uint64_t)i * n + r.v[i];
+                const uint32_t c = (uint32_t)((at * 0x9E3779B97F4A7C15ull) >> 32) % kTargetCells;
+                const unsigned long long was = atomicCAS(&c_key[c], 0ull, (unsigned long long)at + 1);
+                if (was == 0ull || was == at + 1) {
+                    if (ok) atomicAdd(&c_sum[c], R);
+                    atomicAdd(&c_count[c], 1u);
+                } else {
+                    if (ok) atomicAdd(&sums[at], R);
+                    atomicAdd(&counts[at], 1u);
+                }
+            }
+            if (ok && i > 0) prod = prod * ((double)r.num[i] / (double)r.den[i]);
         }
-        if (ok && i > 0) prod = prod * ((double)r.num[i] / (double)r.den[i]);
+    }
+    __syncthreads();
+    for (uint32_t c = threadIdx.x; c < kTargetCells; c += kTargetThreads) {
+        const uint64_t key = c_key[c];
+        if (key == 0) continue;
+        if (c_sum[c] != 0.0) atomicAdd(&sums[key - 1], c_sum[c]);
+        atomicAdd(&counts[key - 1], c_count[c]);
     }
 }
 
@@ -852,8 +893,8 @@ int agis_learn_targets(agis_ctx* ctx, const agis_graph* g, const agis_tables* t,
         }
         rc = agis_dump_samples(ctx, g, t, p, order, seed, params, d_idx, m, (agis_record*)d_rec);
         if (rc != AGIS_OK) break;
-        hipLaunchKernelGGL(agis::k_targets, dim3(grid1(m, 256)), dim3(256), 0, ctx->stream, d_rec, m, p->k, n, sums,
-                           counts);
+        hipLaunchKernelGGL(agis::k_targets, dim3(grid1(m, agis::kTargetRecords)), dim3(agis::kTargetThreads), 0,
+                           ctx->stream, d_rec, m, p->k, n, sums, counts);
         e = hipStreamSynchronize(ctx->stream);
         if (e != hipSuccess) rc = lfail(ctx, AGIS_E_HIP, std::string("targets: ") + hipGetErrorString(e));
     }
