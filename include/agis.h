@@ -287,9 +287,8 @@ int agis_graph_export(agis_ctx* ctx, const agis_graph* g, uint64_t* n, uint64_t*
  * (up to 1 GiB); the common-neighbour counts of every pair among the hubs
  * of highest degree (up to H = 8,192 of them, within a bounded build work),
  * which make a uniform step over the common neighbours of two such hubs a
- * table read plus a partial walk (8 counts per ordered pair, the total and
- * 7 running counts at eighths of the shorter list, H^2 x 8 x 4 B: at most
- * 2 GiB); and the common-neighbour lists themselves of every pair among
+ * table read plus a partial walk (8 counts per pair, the total and 7 running
+ * counts at eighths of the shorter list, H^2 x 8 x 4 B: at most 2 GiB); and the common-neighbour lists themselves of every pair among
  * the C highest-degree of those hubs (the core; C <= 4,096, the lists
  * within 4 GiB and an eighth of the free memory), from which a step over
  * two core vertices starts.

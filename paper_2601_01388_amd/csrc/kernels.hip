@@ -3082,9 +3082,14 @@ struct SlotQueue {
 // 64-byte segments, wave-level requests), compiled apart so the production
 // kernel carries none of that state.  kWavesPerEU:
 // register budget of the variant -- at least that many waves per SIMD must
-// fit (4 leaves the compiler its own choice, 80 registers and 6 waves here;
-// 7 and 8 trade spills for more resident waves); the autotuner picks the
-// fastest.
+// fit (6, 7 and 8 waves: 80, 72 and 64 registers, none of them spilled to
+// memory); the autotuner picks the fastest.  The chains of dependent loads of
+// a sample bound it, and the access rate of the first-level cache (one
+// 64-byte access a cycle and compute unit; 16 for a coalesced or uniform
+// 4-byte load, 64 for a gather), of which it uses 0.98 (R-MAT-20 5-cycle) and
+// 1.05 (5-clique): so wave-uniform reads go through the scalar cache, scans
+// through lane rotations, and 8 waves beat 6 (4M samples: 5-cycle 13.7 ->
+// 11.7 ms, 5-clique 45.3 -> 42.3).
 template <int kMode, int kWavesPerEU, bool kPairs>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU)))
 void k_sample(const LaunchDesc* __restrict__ D) {
