@@ -3009,11 +3009,13 @@ __device__ __forceinline__ void st_dev_partial(AGIS_GMEM Partial* p, const Parti
     st_dev_f64(d + 3, v.nonzero);
 }
 
-// The slots of a round as a wave takes them: kQueues contiguous parts, each
-// with a counter of its own (atomics on one address are served one at a
+// The slots of a round as a wave takes them: up to kQueues contiguous parts,
+// each with a counter of its own (atomics on one address are served one at a
 // time, about 7.5 million per second).  Workgroup b belongs to part
-// b % kQueues, whose first slots are dealt to its waves without an atomic;
-// the counter hands out what is left, span slots at a time.  A wave whose
+// b % parts; a part has share slots per workgroup, so that a launch whose
+// waves all have slots at once deals them all.  A part's first slots are
+// dealt to its waves without an atomic; the counter hands out what is left,
+// span slots at a time.  A wave whose
 // part has run out looks at all counters at once and goes on with the next
 // part that is not empty, so an empty part costs a load and not an atomic.
 // 4096 triangles on a small graph took 104 us in the sampler when each wave
@@ -3023,23 +3025,37 @@ __device__ __forceinline__ void st_dev_partial(AGIS_GMEM Partial* p, const Parti
 struct SlotQueue {
     AGIS_GMEM unsigned long long* counters;
     uint64_t total, span;
-    uint64_t lo, hi, dealt;  // the current part; its slots dealt without the counter
-    uint32_t q;
+    uint64_t share;          // slots per workgroup
+    uint32_t parts, q;       // parts, and the current one
+    uint64_t lo, hi, dealt;  // its slots, and how many are dealt without the counter
+    __device__ __forceinline__ SlotQueue(AGIS_GMEM unsigned long long* c, uint64_t slots, uint64_t each)
+        : counters(c), total(slots), span(each) {
+        share = (total + gridDim.x - 1) / gridDim.x;
+        parts = gridDim.x < kQueues ? gridDim.x : kQueues;
+    }
+    // Workgroups of the parts before p, p <= parts.
+    __device__ __forceinline__ uint64_t groups_before(uint32_t p) const {
+        const uint32_t rest = gridDim.x % parts;
+        return (uint64_t)p * (gridDim.x / parts) + (p < rest ? p : rest);
+    }
+    __device__ __forceinline__ uint64_t first_of(uint32_t p) const {
+        const uint64_t f = groups_before(p) * share;
+        return f < total ? f : total;
+    }
     // Slots of part p dealt without an atomic.
     __device__ __forceinline__ uint64_t dealt_of(uint32_t p) const {
-        const uint64_t blocks = gridDim.x > p ? (gridDim.x - p - 1) / kQueues + 1 : 0;
-        return blocks * (blockDim.x / kWave) * span;
+        return (groups_before(p + 1) - groups_before(p)) * (blockDim.x / kWave) * span;
     }
     __device__ __forceinline__ void enter(uint32_t p) {
         q = p;
-        lo = total * p / kQueues;
-        hi = total * (p + 1) / kQueues;
+        lo = first_of(p);
+        hi = first_of(p + 1);
         dealt = dealt_of(p);
     }
     // The wave's dealt slots.
     __device__ __forceinline__ uint64_t first() {
-        enter(blockIdx.x % kQueues);
-        const uint64_t o = ((uint64_t)(blockIdx.x / kQueues) * (blockDim.x / kWave) + uniform_u32(threadIdx.x / kWave)) * span;
+        enter(blockIdx.x % parts);
+        const uint64_t o = ((uint64_t)(blockIdx.x / parts) * (blockDim.x / kWave) + uniform_u32(threadIdx.x / kWave)) * span;
         return o < hi - lo ? lo + o : kNoSlot;
     }
     // The part's next slots, kNoSlot if it has run out.
@@ -3055,14 +3071,14 @@ struct SlotQueue {
         for (;;) {
             const uint32_t p = (uint32_t)lane_id();
             bool left = false;
-            if (p < kQueues) {
-                const uint64_t len = total * (p + 1) / kQueues - total * p / kQueues, d = dealt_of(p);
+            if (p < parts) {
+                const uint64_t len = first_of(p + 1) - first_of(p), d = dealt_of(p);
                 left = d < len && ld_dev(counters + (uint64_t)p * kQueueStride) < len - d;
             }
-            const uint64_t parts = __ballot(left);
-            if (parts == 0) return kNoSlot;
-            const uint64_t after = parts & ~((2ull << q) - 1ull);
-            enter((uint32_t)__builtin_ctzll(after ? after : parts));
+            const uint64_t some = __ballot(left);
+            if (some == 0) return kNoSlot;
+            const uint64_t after = some & ~((2ull << q) - 1ull);
+            enter((uint32_t)__builtin_ctzll(after ? after : some));
             const uint64_t s = take();
             if (s != kNoSlot) return s;
         }
@@ -3109,7 +3125,7 @@ void k_sample(const LaunchDesc* __restrict__ D) {
     const DevTables t = D->t;
     const uint32_t hub_window = D->hub_window;
     AGIS_GMEM double* xout = D->xout;
-    SlotQueue queue{D->queue, total, grab};
+    SlotQueue queue(D->queue, total, grab);
     uint32_t sg = 0;  // segment of the current slot (within a part, slots only increase)
     uint64_t cur = queue.first();
     for (;;) {
@@ -3378,7 +3394,7 @@ __global__ __launch_bounds__(256) void k_sample_lanes(const LaunchDesc* __restri
     const uint64_t span = (uint64_t)D->grab * kWave;
     const DevGraph g = D->g;
     AGIS_GMEM double* xout = D->xout;
-    SlotQueue queue{D->queue, total, span};
+    SlotQueue queue(D->queue, total, span);
     uint32_t sg = 0;  // this lane's segment (within a part, a lane's slots only increase)
     uint64_t cur = queue.first();
     for (;;) {
