@@ -520,15 +520,12 @@ hipError_t build_hub_bitmaps(agis_ctx* ctx, const agis_graph* g, agis_tables* t)
     if (e == hipSuccess) e = ctx->pool->alloc(&prefix, (n + 1) * sizeof(uint64_t));
     if (e == hipSuccess) e = ctx->pool->alloc(&t->hub_slot, n * sizeof(int32_t));
     if (e == hipSuccess) e = agis::launch_hub_slots(ctx, g->g, 1u << b, flags, t->hub_slot, prefix);
-    uint64_t hubs = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&hubs, prefix + n, sizeof(uint64_t), hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+    const uint64_t hubs = above;
     if (e == hipSuccess) e = ctx->pool->alloc(&t->hub_bits, hubs * words * sizeof(uint32_t));
     if (e == hipErrorOutOfMemory) return drop_out_of_memory();
     if (e == hipSuccess) e = hipMemsetAsync(t->hub_bits, 0, hubs * words * sizeof(uint32_t), ctx->stream);
     // (flags is free again: it takes the hubs by slot)
     if (e == hipSuccess) e = agis::launch_hub_bits(g->g, t->hub_slot, hubs, flags, words, t->hub_bits, ctx->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e == hipSuccess) {
         t->hub_words = words;
         t->hubs = hubs;
@@ -561,8 +558,7 @@ hipError_t build_hub_bitmaps(agis_ctx* ctx, const agis_graph* g, agis_tables* t)
         }
     }
     if (e == hipSuccess) e = agis::launch_hub_slots(ctx, g->g, 1u << pb, flags, t->pair_slot, prefix);
-    if (e == hipSuccess) e = hipMemcpyAsync(&H, prefix + n, sizeof(uint64_t), hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+    for (int j = pb; j < 64; ++j) H += hist[j];
     if (e == hipSuccess && H >= 2) {
         e = ctx->pool->alloc(&pair_hub, H * sizeof(uint32_t));
         if (e == hipSuccess) e = ctx->pool->alloc(&t->pair_count, H * H * sizeof(uint32_t));
@@ -1513,8 +1509,9 @@ int agis_load_csr(agis_ctx* ctx, const uint64_t* off, const uint32_t* nbr, uint6
     if (nnz & 1ull) return fail(ctx, AGIS_E_INVALID_CSR, "nnz of a symmetric graph must be even");
     agis::DevGraph dg{agis::gmem(off), agis::gmem(nbr), n, nnz};
     uint32_t* d_cells = (uint32_t*)ctx->d_small;
-    // fault flags, largest degree, and (64 bits) the slots that point down
-    uint32_t cells[4] = {0, 0, 0, 0};
+    // fault flags, largest degree, and where a round's slot counters are the
+    // counts of the slots that point down
+    uint32_t cells[agis::kSmallBytes / 4] = {0};
     AGIS_HIP(ctx, hipMemsetAsync(d_cells, 0, sizeof(cells), ctx->stream), "clear flags");
     if (flags & AGIS_CSR_VALIDATE) {
         AGIS_HIP(ctx, agis::launch_validate_rows(dg, d_cells, ctx->stream), "validate CSR rows");
@@ -1522,14 +1519,18 @@ int agis_load_csr(agis_ctx* ctx, const uint64_t* off, const uint32_t* nbr, uint6
                  "read flags");
         AGIS_HIP(ctx, hipStreamSynchronize(ctx->stream), "validate CSR rows");
         if (cells[0] == 0)
-            AGIS_HIP(ctx, agis::launch_validate_edges(ctx, dg, d_cells, (uint64_t*)(d_cells + 2)), "validate CSR edges");
+            AGIS_HIP(ctx, agis::launch_validate_edges(ctx, dg, d_cells, (uint64_t*)(d_cells + agis::kQueueOffset / 4)), "validate CSR edges");
     }
     if (cells[0] == 0) AGIS_HIP(ctx, agis::launch_max_degree(dg, d_cells + 1, ctx->stream), "max degree");
     AGIS_HIP(ctx, hipMemcpyAsync(cells, d_cells, sizeof(cells), hipMemcpyDeviceToHost, ctx->stream), "read flags");
     AGIS_HIP(ctx, hipStreamSynchronize(ctx->stream), "validate CSR");
     if ((flags & AGIS_CSR_VALIDATE) && cells[0] == 0) {
         uint64_t lower = 0;
-        std::memcpy(&lower, &cells[2], sizeof(lower));
+        for (uint32_t q = 0; q < agis::kQueues; ++q) {
+            uint64_t c = 0;
+            std::memcpy(&c, (const char*)cells + agis::kQueueOffset + (size_t)q * agis::kQueueStride * 8, sizeof(c));
+            lower += c;
+        }
         if (2 * lower != nnz) cells[0] |= 16u;
     }
     if (cells[0]) {

@@ -602,21 +602,26 @@ __global__ void k_validate_rows(DevGraph g, uint32_t* flags) {
 // slots of the largest graphs).
 //
 // Symmetry: each slot (v, x) whose x is below v by (degree, id) is looked up
-// in x's row, the shorter of the two, and counted in *lower.  In a graph
+// in x's row, the shorter of the two, and counted (a workgroup's count goes
+// to one of kQueues counters: on one address 8192 waves took a millisecond,
+// which a large graph hides and a small one does not).  In a graph
 // without the other faults these slots' mirrors are distinct slots of the
 // other direction, so if all are found and they are half of the slots, every
 // slot has its mirror.  (Looking every slot up in its neighbour's row took
 // 2.2 ms on R-MAT-20.)
-__global__ __launch_bounds__(256) void k_validate_edges(DevGraph g, uint32_t* flags, unsigned long long* lower) {
+__global__ __launch_bounds__(256) void k_validate_edges(DevGraph g, uint32_t* flags, unsigned long long* lower, uint64_t run) {
+    __shared__ unsigned long long group_low;
+    if (threadIdx.x == 0) group_low = 0;
+    __syncthreads();
     const uint64_t nw = (uint64_t)gridDim.x * (blockDim.x / kWave);
     uint64_t low = 0;
     uint32_t faults = 0;
     for (uint64_t r = (uint64_t)blockIdx.x * (blockDim.x / kWave) + uniform_u32(threadIdx.x / kWave);
-         r * kSlotRun < g.nnz; r += nw) {
+         r * run < g.nnz; r += nw) {
         // offsets were checked (monotone, within nnz) by k_validate_rows first
-        const uint64_t end = (r + 1) * kSlotRun < g.nnz ? (r + 1) * kSlotRun : g.nnz;
-        uint64_t v0 = wave_row_of_slot(g, r * kSlotRun);
-        for (uint64_t e0 = r * kSlotRun; e0 < end; e0 += kWave) {
+        const uint64_t end = (r + 1) * run < g.nnz ? (r + 1) * run : g.nnz;
+        uint64_t v0 = wave_row_of_slot(g, r * run);
+        for (uint64_t e0 = r * run; e0 < end; e0 += kWave) {
             const uint64_t e = e0 + (uint64_t)lane_id();
             const uint64_t v = lane_row(g, e0, v0);
             v0 = readlane_u64(v, kWave - 1);
@@ -639,7 +644,9 @@ __global__ __launch_bounds__(256) void k_validate_edges(DevGraph g, uint32_t* fl
         }
     }
     if (faults) atomicOr(flags, faults);
-    if (lane_id() == 0 && low) atomicAdd(lower, (unsigned long long)low);
+    if (lane_id() == 0) atomicAdd(&group_low, (unsigned long long)low);
+    __syncthreads();
+    if (threadIdx.x == 0 && group_low) atomicAdd(lower + (uint64_t)(blockIdx.x % kQueues) * kQueueStride, group_low);
 }
 
 // (a grid-stride loop and one atomic per workgroup: with one per wave, the
@@ -678,15 +685,24 @@ hipError_t launch_validate_rows(const DevGraph& g, uint32_t* d_flags, hipStream_
     return hipGetLastError();
 }
 
-// Workgroups of four waves for a kernel over runs of kSlotRun slots.
-static unsigned run_grid(const agis_ctx* ctx, uint64_t nnz) {
-    return (unsigned)std::min<uint64_t>(((nnz + kSlotRun - 1) / kSlotRun + 3) / 4, (uint64_t)ctx->num_cus * 8);
+// Workgroups of four waves for a kernel over runs of `run` slots.
+static unsigned run_grid(const agis_ctx* ctx, uint64_t nnz, uint64_t run = kSlotRun) {
+    return (unsigned)std::min<uint64_t>(((nnz + run - 1) / run + 3) / 4, (uint64_t)ctx->num_cus * 8);
+}
+
+// Slots in a wave's run: kSlotRun, and on graphs that do not fill the chip
+// with such runs less, down to 64 (a run's 16 steps follow one another: on
+// R-MAT-10 the symmetry check took 34 us with runs of 1024 and C_v 58).
+static uint64_t slot_run(const agis_ctx* ctx, uint64_t nnz) {
+    uint64_t run = kSlotRun;
+    while (run > (uint64_t)kWave && nnz / run < (uint64_t)ctx->num_cus * 16) run /= 2;
+    return run;
 }
 
 hipError_t launch_validate_edges(agis_ctx* ctx, const DevGraph& g, uint32_t* d_flags, uint64_t* d_lower) {
     if (g.nnz)
-        hipLaunchKernelGGL(k_validate_edges, dim3(run_grid(ctx, g.nnz)), dim3(256), 0, ctx->stream, g, d_flags,
-                           (unsigned long long*)d_lower);
+        hipLaunchKernelGGL(k_validate_edges, dim3(run_grid(ctx, g.nnz, slot_run(ctx, g.nnz))), dim3(256), 0,
+                           ctx->stream, g, d_flags, (unsigned long long*)d_lower, slot_run(ctx, g.nnz));
     return hipGetLastError();
 }
 
@@ -807,10 +823,11 @@ hipError_t launch_build_tables(agis_ctx* ctx, const DevGraph& g, const DevGraph&
     hipLaunchKernelGGL(k_tables_init, dim3(grid_for(g.n, 256)), dim3(256), 0, stream, g, t.rec, t.s2, t.hits);
     // (the exact count costs a slot of a long row thousands of searches: a
     // wave takes 64 of them at a time)
+    const uint64_t run = exact ? (uint64_t)kWave : slot_run(ctx, g.nnz);
     if (g.nnz)
-        hipLaunchKernelGGL(k_tables_edges, dim3(exact ? stride_grid(g.nnz, 256) : run_grid(ctx, g.nnz)), dim3(256), 0,
+        hipLaunchKernelGGL(k_tables_edges, dim3(exact ? stride_grid(g.nnz, 256) : run_grid(ctx, g.nnz, run)), dim3(256), 0,
                            stream, g, adj, t.rec, t.s2, t.hits, hub_slot, t.hub_bits, t.hub_words, k0, k1, exact,
-                           exact ? (uint64_t)kWave : kSlotRun);
+                           run);
     hipLaunchKernelGGL(k_tables_finalize, dim3(grid_for(g.n, 256)), dim3(256), 0, stream, g, t.rec, t.s2, t.hits,
                        t.trials, lc_min, exact);
     return hipGetLastError();
