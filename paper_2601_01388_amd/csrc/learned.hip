@@ -660,8 +660,12 @@ __global__ __launch_bounds__(kGradThreads, 2) void k_mlp_grad(
             for (int c = 0; c < 4; ++c) X[(4 + c) * kGradLd + row] = c == cur.c ? 1.0f : 0.0f;
             X[kIn * kGradLd + row] = 1.0f;
         }
-        // layer 1: this lane's 16 units of its row
-        float g1[16];
+        // layer 1: this lane's 16 units of its row.  The one-hot inputs are
+        // multiplied like the others (a weight that is not finite reaches the
+        // rows of every class)
+        float g1[16], hot[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) hot[c] = c == cur.c ? 1.0f : 0.0f;
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             const int m = unit(j);
@@ -671,7 +675,8 @@ __global__ __launch_bounds__(kGradThreads, 2) void k_mlp_grad(
             a += w[1] * cur.x.y;
             a += w[2] * cur.x.z;
             a += w[3] * cur.x.w;
-            if (cur.c >= 0) a += w[4 + cur.c];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) a += w[4 + c] * hot[c];
             H1[m * kGradLd + row] = gelu(a);
             g1[j] = gelu_grad(a);
         }
