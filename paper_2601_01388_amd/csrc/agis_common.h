@@ -234,7 +234,7 @@ constexpr uint32_t kMaxSegs = 64;
 
 // Slot-queue counters of a round: kQueues of them, kQueueStride 64-bit
 // entries (256 bytes) apart, from byte kQueueOffset of the context's small
-// device buffer; kNoSlot marks an empty part.
+// device buffer; kNoSlot: no slots left.
 constexpr uint32_t kQueues = 32;
 // XCDs of the device (MI355X: 8, each with its own L2); workgroups are dealt
 // to them round robin by workgroup index
@@ -329,7 +329,8 @@ struct EpsDesc {
     uint32_t rank_blocks;
     uint32_t look_ticks;        // wall-clock ticks between two looks of a waiting workgroup
     uint32_t join_ticks;        // mean ticks of a sample from which the others join
-    uint32_t pad0;
+    uint32_t late_ticks;        // the same once late_merged samples are merged
+    uint64_t late_merged;
     double z;
     double eps;
 };

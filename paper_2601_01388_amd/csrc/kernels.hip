@@ -3026,76 +3026,68 @@ __device__ __forceinline__ void st_dev_partial(AGIS_GMEM Partial* p, const Parti
     st_dev_f64(d + 3, v.nonzero);
 }
 
-// The slots of a round as a wave takes them: up to kQueues contiguous parts,
-// each with a counter of its own (atomics on one address are served one at a
-// time, about 7.5 million per second).  Workgroup b belongs to part
-// b % parts; a part has share slots per workgroup, so that a launch whose
-// waves all have slots at once deals them all.  A part's first slots are
-// dealt to its waves without an atomic; the counter hands out what is left,
-// span slots at a time.  A wave whose
-// part has run out looks at all counters at once and goes on with the next
-// part that is not empty, so an empty part costs a load and not an atomic.
+// The slots of a round as a wave takes them: grabs of `span` consecutive
+// slots, in index order.  The first grabs are dealt, one to each wave,
+// without an atomic; the others are handed out by up to kQueues counters in
+// turn, the t-th grab of counter p being number dealt + t parts + p (atomics
+// on one address are served one at a time, about 7.5 million per second).
+// Workgroup b takes from counter b % parts.  So the counters run through the
+// patterns of a round side by side and run out together, whatever the
+// patterns cost; a wave whose counter has run out looks at all of them at
+// once and goes on with one that has not, each wave with another, so an
+// exhausted counter costs a load and not an atomic.
 // 4096 triangles on a small graph took 104 us in the sampler when each wave
-// took its first slot and asked every empty part by an atomic (8 parts), 46
-// us now; 36K 4-cliques 0.335 ms, 0.31 with the dealt slots, 0.28 with 32
-// parts instead of 8 (0.275 with 64); 4M 5-cycles 11.1 -> 10.95.
+// took its first slot and asked every empty counter by an atomic (8
+// counters), 46 us now; 36K 4-cliques 0.335 ms, 0.31 with the dealt slots,
+// 0.28 with 32 counters instead of 8; 4M 5-cycles 11.1 -> 10.81.  Batches
+// need the turns: with a contiguous part of the slots per counter, the waves
+// of the cheap patterns came to the dear ones' counters all at once (4
+// patterns x 50,000 samples on R-MAT-16 2.79 ms in the sampler, now 1.64; the
+// six 4-vertex patterns x 100,000 on R-MAT-20 5.67 ms, now 2.60).
 struct SlotQueue {
     AGIS_GMEM unsigned long long* counters;
     uint64_t total, span;
-    uint64_t share;          // slots per workgroup
-    uint32_t parts, q;       // parts, and the current one
-    uint64_t lo, hi, dealt;  // its slots, and how many are dealt without the counter
+    uint64_t grabs, dealt;  // in all, and those dealt without a counter
+    uint32_t parts, q;      // counters, and the current one
     __device__ __forceinline__ SlotQueue(AGIS_GMEM unsigned long long* c, uint64_t slots, uint64_t each)
         : counters(c), total(slots), span(each) {
-        share = (total + gridDim.x - 1) / gridDim.x;
+        grabs = (total + span - 1) / span;
+        dealt = (uint64_t)gridDim.x * (blockDim.x / kWave);
         parts = gridDim.x < kQueues ? gridDim.x : kQueues;
+        q = blockIdx.x % parts;
     }
-    // Workgroups of the parts before p, p <= parts.
-    __device__ __forceinline__ uint64_t groups_before(uint32_t p) const {
-        const uint32_t rest = gridDim.x % parts;
-        return (uint64_t)p * (gridDim.x / parts) + (p < rest ? p : rest);
-    }
-    __device__ __forceinline__ uint64_t first_of(uint32_t p) const {
-        const uint64_t f = groups_before(p) * share;
-        return f < total ? f : total;
-    }
-    // Slots of part p dealt without an atomic.
-    __device__ __forceinline__ uint64_t dealt_of(uint32_t p) const {
-        return (groups_before(p + 1) - groups_before(p)) * (blockDim.x / kWave) * span;
-    }
-    __device__ __forceinline__ void enter(uint32_t p) {
-        q = p;
-        lo = first_of(p);
-        hi = first_of(p + 1);
-        dealt = dealt_of(p);
+    // First slot of grab t of counter p, kNoSlot past its last.
+    __device__ __forceinline__ uint64_t slot_of(uint32_t p, uint64_t t) const {
+        const uint64_t i = dealt + t * parts + p;
+        return i < grabs ? i * span : kNoSlot;
     }
     // The wave's dealt slots.
-    __device__ __forceinline__ uint64_t first() {
-        enter(blockIdx.x % parts);
-        const uint64_t o = ((uint64_t)(blockIdx.x / parts) * (blockDim.x / kWave) + uniform_u32(threadIdx.x / kWave)) * span;
-        return o < hi - lo ? lo + o : kNoSlot;
+    __device__ __forceinline__ uint64_t first() const {
+        const uint64_t i = (uint64_t)blockIdx.x * (blockDim.x / kWave) + uniform_u32(threadIdx.x / kWave);
+        return i < grabs ? i * span : kNoSlot;
     }
-    // The part's next slots, kNoSlot if it has run out.
+    // The end of the grab that starts at a slot.
+    __device__ __forceinline__ uint64_t end(uint64_t slot) const {
+        return total - slot < span ? total : slot + span;
+    }
+    // The next slots of the wave's counter, kNoSlot if it has run out.
     __device__ __forceinline__ uint64_t take() const {
-        if (dealt >= hi - lo) return kNoSlot;
-        unsigned long long o = 0;
-        if (lane_id() == 0) o = atomicAdd(counters + (uint64_t)q * kQueueStride, (unsigned long long)span);
-        o = uniform_u64(o) + dealt;
-        return o < hi - lo ? lo + o : kNoSlot;
+        if (slot_of(q, 0) == kNoSlot) return kNoSlot;
+        unsigned long long t = 0;
+        if (lane_id() == 0) t = atomicAdd(counters + (uint64_t)q * kQueueStride, 1ull);
+        return slot_of(q, uniform_u64(t));
     }
-    // Slots of another part once this one has run out, kNoSlot once all have.
+    // Slots of another counter once this one has run out, kNoSlot once all
+    // have.
     __device__ __forceinline__ uint64_t take_elsewhere() {
         for (;;) {
             const uint32_t p = (uint32_t)lane_id();
-            bool left = false;
-            if (p < parts) {
-                const uint64_t len = first_of(p + 1) - first_of(p), d = dealt_of(p);
-                left = d < len && ld_dev(counters + (uint64_t)p * kQueueStride) < len - d;
-            }
+            const bool left = p < parts && slot_of(p, 0) != kNoSlot &&
+                              slot_of(p, ld_dev(counters + (uint64_t)p * kQueueStride)) != kNoSlot;
             const uint64_t some = __ballot(left);
             if (some == 0) return kNoSlot;
-            const uint64_t after = some & ~((2ull << q) - 1ull);
-            enter((uint32_t)__builtin_ctzll(after ? after : some));
+            const uint32_t pick = (q + blockIdx.x / parts + uniform_u32(threadIdx.x / kWave)) % (uint32_t)__popcll(some);
+            q = (uint32_t)__builtin_ctzll(__ballot(left && (uint32_t)__popcll(some & lanemask_lt()) == pick));
             const uint64_t s = take();
             if (s != kNoSlot) return s;
         }
@@ -3143,7 +3135,7 @@ void k_sample(const LaunchDesc* __restrict__ D) {
     const uint32_t hub_window = D->hub_window;
     AGIS_GMEM double* xout = D->xout;
     SlotQueue queue(D->queue, total, grab);
-    uint32_t sg = 0;  // segment of the current slot (within a part, slots only increase)
+    uint32_t sg = 0;  // segment of the current slot (of one counter, slots only increase)
     uint64_t cur = queue.first();
     for (;;) {
         if (cur == kNoSlot) {
@@ -3152,7 +3144,7 @@ void k_sample(const LaunchDesc* __restrict__ D) {
         }
         if (cur == kNoSlot) break;
         const uint64_t next = queue.take();  // requested before the current grab runs
-        const uint64_t j1 = (cur + grab) < queue.hi ? (cur + grab) : queue.hi;
+        const uint64_t j1 = queue.end(cur);
         for (uint64_t j = cur; j < j1; ++j) {
             while (sg + 1 < round->nseg && j >= round->seg[sg].base + round->seg[sg].count) ++sg;
             const Segment& S = round->seg[sg];
@@ -3412,7 +3404,7 @@ __global__ __launch_bounds__(256) void k_sample_lanes(const LaunchDesc* __restri
     const DevGraph g = D->g;
     AGIS_GMEM double* xout = D->xout;
     SlotQueue queue(D->queue, total, span);
-    uint32_t sg = 0;  // this lane's segment (within a part, a lane's slots only increase)
+    uint32_t sg = 0;  // this lane's segment (of one counter, a lane's slots only increase)
     uint64_t cur = queue.first();
     for (;;) {
         if (cur == kNoSlot) {
@@ -3421,7 +3413,7 @@ __global__ __launch_bounds__(256) void k_sample_lanes(const LaunchDesc* __restri
         }
         if (cur == kNoSlot) break;
         const uint64_t next = queue.take();
-        const uint64_t j1 = (cur + span) < queue.hi ? (cur + span) : queue.hi;
+        const uint64_t j1 = queue.end(cur);
         for (uint64_t j = cur + (uint64_t)lane; j < j1; j += kWave) {
             while (sg + 1 < round->nseg && j >= round->seg[sg].base + round->seg[sg].count) ++sg;
             const Segment& S = round->seg[sg];
@@ -3664,7 +3656,7 @@ __device__ __forceinline__ bool eps_joins(const EpsDesc& E, uint32_t rank) {
             while (wall_clock64() - since < E.look_ticks) __builtin_amdgcn_s_sleep(32);
             since = wall_clock64();
             const bool runs = lane < E.npat && ld_dev(&E.pat[lane].stop) == 0u;
-            double sum = 0.0, num = 0.0;
+            double sum = 0.0, num = 0.0, merged = lane < E.npat ? (double)ld_dev(&E.pat[lane].merged) : 0.0;
             for (uint32_t b = lane; b < E.rank_blocks; b += kWave) {
                 const uint32_t c = ld_dev(E.costs + b);
                 sum += (double)c;
@@ -3673,10 +3665,12 @@ __device__ __forceinline__ bool eps_joins(const EpsDesc& E, uint32_t rank) {
             for (int o = 1; o < kWave; o <<= 1) {
                 sum += __shfl_xor(sum, o, kWave);
                 num += __shfl_xor(num, o, kWave);
+                merged += __shfl_xor(merged, o, kWave);
             }
             if (!__ballot(runs))
                 in = 0u;
-            else if (sum >= num * (double)E.join_ticks)  // (none has finished one: long)
+            else if (sum >= num * (double)E.join_ticks ||  // (none has finished one: long)
+                     (merged >= (double)E.late_merged && sum >= num * (double)E.late_ticks))
                 in = 1u;
         }
         if (lane == 0) {
