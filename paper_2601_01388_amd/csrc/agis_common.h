@@ -329,8 +329,7 @@ struct EpsDesc {
     uint32_t rank_blocks;
     uint32_t look_ticks;        // wall-clock ticks between two looks of a waiting workgroup
     uint32_t join_ticks;        // mean ticks of a sample from which the others join
-    uint32_t late_ticks;        // the same once late_merged samples are merged
-    uint64_t late_merged;
+    uint32_t pad0;
     double z;
     double eps;
 };

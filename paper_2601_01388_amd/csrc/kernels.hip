@@ -3656,7 +3656,7 @@ __device__ __forceinline__ bool eps_joins(const EpsDesc& E, uint32_t rank) {
             while (wall_clock64() - since < E.look_ticks) __builtin_amdgcn_s_sleep(32);
             since = wall_clock64();
             const bool runs = lane < E.npat && ld_dev(&E.pat[lane].stop) == 0u;
-            double sum = 0.0, num = 0.0, merged = lane < E.npat ? (double)ld_dev(&E.pat[lane].merged) : 0.0;
+            double sum = 0.0, num = 0.0;
             for (uint32_t b = lane; b < E.rank_blocks; b += kWave) {
                 const uint32_t c = ld_dev(E.costs + b);
                 sum += (double)c;
@@ -3665,12 +3665,10 @@ __device__ __forceinline__ bool eps_joins(const EpsDesc& E, uint32_t rank) {
             for (int o = 1; o < kWave; o <<= 1) {
                 sum += __shfl_xor(sum, o, kWave);
                 num += __shfl_xor(num, o, kWave);
-                merged += __shfl_xor(merged, o, kWave);
             }
             if (!__ballot(runs))
                 in = 0u;
-            else if (sum >= num * (double)E.join_ticks ||  // (none has finished one: long)
-                     (merged >= (double)E.late_merged && sum >= num * (double)E.late_ticks))
+            else if (sum >= num * (double)E.join_ticks)  // (none has finished one: long)
                 in = 1u;
         }
         if (lane == 0) {
