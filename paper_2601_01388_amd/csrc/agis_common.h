@@ -309,7 +309,8 @@ static_assert(sizeof(EpsPattern) == 256, "two 128-byte lines per pattern");
 //
 // Ranks: workgroup b has rank b / rank_blocks (rank_blocks: one per compute
 // unit).  Ranks below kEpsFirst sample from the start; the others look now
-// and then whether samples are worth more waves, and join or leave.
+// and then whether the samples or the run are worth more waves, and join or
+// leave.
 constexpr uint32_t kEpsFirst = 2;
 struct EpsDesc {
     AGIS_GMEM EpsPattern* pat;
@@ -329,7 +330,8 @@ struct EpsDesc {
     uint32_t rank_blocks;
     uint32_t look_ticks;        // wall-clock ticks between two looks of a waiting workgroup
     uint32_t join_ticks;        // mean ticks of a sample from which the others join
-    uint32_t pad0;
+    uint32_t late_ticks;        // the same once late_merged samples are merged
+    uint64_t late_merged;
     double z;
     double eps;
 };

@@ -1193,10 +1193,13 @@ int run_rounds(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, std::ve
 // Offsets in the context's small device buffer of the launch's start clock
 // and of the fault flag of a run to epsilon in one launch.
 constexpr uint32_t kClockOffset = 520;
-// A run to epsilon's later workgroups: time between two looks, and the mean
-// time of a sample from which they join (see eps_joins).
+// A run to epsilon's later workgroups: time between two looks, the mean time
+// of a sample from which they join, and the same in a run that has merged
+// kEpsLateMerged samples (see eps_joins).
 constexpr int kEpsLookMicroseconds = 40;
 constexpr int kEpsJoinMicroseconds = 16;
+constexpr int kEpsLateMicroseconds = 4;
+constexpr uint64_t kEpsLateMerged = 1ull << 18;
 constexpr uint32_t kFaultOffset = 528;
 
 // Runs every pattern to epsilon (or its budget) in one persistent launch
@@ -1301,6 +1304,8 @@ int run_device_eps(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, std
     E.rank_blocks = rank_blocks;
     E.look_ticks = (uint32_t)((int64_t)kEpsLookMicroseconds * ctx->wall_clock_khz / 1000);
     E.join_ticks = (uint32_t)((int64_t)kEpsJoinMicroseconds * ctx->wall_clock_khz / 1000);
+    E.late_ticks = (uint32_t)((int64_t)kEpsLateMicroseconds * ctx->wall_clock_khz / 1000);
+    E.late_merged = kEpsLateMerged;
     E.z = z;
     E.eps = pp->eps;
     AGIS_HIP(ctx, hipMemcpyAsync(ctx->d_launch, &ld, sizeof(ld), hipMemcpyHostToDevice, ctx->stream), "upload launch");

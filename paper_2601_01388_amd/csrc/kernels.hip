@@ -3635,7 +3635,8 @@ constexpr uint32_t kWindowSpins = 1u << 22;
 constexpr uint32_t kJoinLooks = 1u << 20;  // bound of a workgroup's looks before it joins
 
 // Whether a workgroup of a later rank samples: waits until the samples of
-// rank 0 prove to be long (true), or every pattern has stopped (false).
+// rank 0 prove to be long or the run does (true), or every pattern has
+// stopped (false).
 // Every wave takes its slots from the pattern's counter and counts them into
 // their tile, and atomics on one address are served one at a time, about 7.5
 // million per second: with 6144 waves at once, the first slot of each alone
@@ -3643,9 +3644,17 @@ constexpr uint32_t kJoinLooks = 1u << 20;  // bound of a workgroup's looks befor
 // needs.  2048 waves serve those (R-MAT-15 3-star to 1%, 4096 samples: 0.79
 // ms with all waves, 0.28 with 2 workgroups per CU; triangles at 188K samples
 // 2.7 and 1.0), all of them samples of 20 us and more (R-MAT-20 house: 5.2
-// and 8.9).  Costs of runs that want all waves lie above 16 us a sample and
-// those of runs that do not below 12 (joining from 8 us on gave the latter
-// 2.0 ms instead of 1.0).
+// and 8.9).  Costs of runs that want all waves from the start lie above 16 us
+// a sample and those of runs that do not below 12 (joining from 8 us on gave
+// the latter 2.0 ms instead of 1.0).
+// A run that goes on wants all waves in the end: once late_merged samples are
+// merged, a wave takes as many at a time as the launch allows, and the join
+// costs some 0.25 ms once.  R-MAT-16 house to 0.3%, 4.4M samples of 11 us:
+// 30.0 ms with 2048 waves to the end, 15.5 with the others from 2^18 samples
+// on (R-MAT-18 4-cycles, 16.8M of 8 us, 87 and 41; triangles of 5 us 61 and
+// 33).  Joining from 2^17 on costs runs that end soon after it 20% and from
+// 2^19 on costs longer ones 6 to 15%; below 4 us a sample the counter bounds
+// the run either way (wedges on R-MAT-12: 11.1 with 2048 waves, 11.9).
 __device__ __forceinline__ bool eps_joins(const EpsDesc& E, uint32_t rank) {
     __shared__ uint32_t joins;
     if (threadIdx.x < kWave) {
@@ -3656,7 +3665,7 @@ __device__ __forceinline__ bool eps_joins(const EpsDesc& E, uint32_t rank) {
             while (wall_clock64() - since < E.look_ticks) __builtin_amdgcn_s_sleep(32);
             since = wall_clock64();
             const bool runs = lane < E.npat && ld_dev(&E.pat[lane].stop) == 0u;
-            double sum = 0.0, num = 0.0;
+            double sum = 0.0, num = 0.0, merged = lane < E.npat ? (double)ld_dev(&E.pat[lane].merged) : 0.0;
             for (uint32_t b = lane; b < E.rank_blocks; b += kWave) {
                 const uint32_t c = ld_dev(E.costs + b);
                 sum += (double)c;
@@ -3665,10 +3674,12 @@ __device__ __forceinline__ bool eps_joins(const EpsDesc& E, uint32_t rank) {
             for (int o = 1; o < kWave; o <<= 1) {
                 sum += __shfl_xor(sum, o, kWave);
                 num += __shfl_xor(num, o, kWave);
+                merged += __shfl_xor(merged, o, kWave);
             }
             if (!__ballot(runs))
                 in = 0u;
-            else if (sum >= num * (double)E.join_ticks)  // (none has finished one: long)
+            else if (sum >= num * (double)E.join_ticks ||  // (none has finished one: long)
+                     (merged >= (double)E.late_merged && sum >= num * (double)E.late_ticks))
                 in = 1u;
         }
         if (lane == 0) {
