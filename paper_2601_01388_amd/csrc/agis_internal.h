@@ -204,8 +204,8 @@ hipError_t launch_hub_slots(agis_ctx* ctx, const DevGraph& g, uint32_t min_deg, 
 hipError_t launch_pair_counts(agis_ctx* ctx, const DevGraph& g, uint32_t max_deg, int32_t* pair_slot, uint64_t H,
                               uint32_t* pair_hub, uint32_t* pair_count, uint32_t* pair_quart);
 // hub: scratch of `hubs` entries, the vertices by slot.
-hipError_t launch_hub_bits(const DevGraph& g, const int32_t* hub_slot, uint64_t hubs, uint32_t* hub, uint64_t words,
-                           uint32_t* bits, hipStream_t stream);
+hipError_t launch_hub_bits(agis_ctx* ctx, const DevGraph& g, uint32_t max_deg, const int32_t* hub_slot, uint64_t hubs,
+                           uint32_t* hub, uint64_t words, uint32_t* bits);
 // Degree orientation: the kept slots (mask, one bit each, orient_words of
 // them) and their counts per run of slots, scanned (run_kept, orient_runs + 1
 // entries), the offsets into off_out (n + 1); then the neighbours into
@@ -312,7 +312,7 @@ hipError_t launch_core_rows(agis_ctx* ctx, const uint32_t* pair_count, uint64_t 
 // Core-pair lists of the pair hubs 0 .. C - 1: core_slot[pair_hub[c]] = c,
 // the index (see DevTables), and the lists; those of c with the hubs below
 // it start at entry row_start[c] (device).  Synchronises the stream.
-hipError_t launch_core_pairs(agis_ctx* ctx, const DevGraph& g, const uint32_t* pair_hub, uint64_t H,
+hipError_t launch_core_pairs(agis_ctx* ctx, const DevGraph& g, uint32_t max_deg, const uint32_t* pair_hub, uint64_t H,
                              const uint32_t* pair_count, const uint32_t* pair_quart, uint64_t C,
                              const uint64_t* row_start, int32_t* core_slot, uint64_t* core_start, uint32_t* core_len,
                              uint32_t* core_nbr);

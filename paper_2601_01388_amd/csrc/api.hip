@@ -455,8 +455,8 @@ hipError_t build_core_pairs(agis_ctx* ctx, const agis_graph* g, agis_tables* t, 
     if (e == hipSuccess)
         e = hipMemcpyAsync(d_rows, start.data(), C * sizeof(uint64_t), hipMemcpyHostToDevice, ctx->stream);
     if (e == hipSuccess)
-        e = agis::launch_core_pairs(ctx, g->g, pair_hub, H, t->pair_count, t->pair_quart, C, d_rows, t->core_slot,
-                                    t->core_start, t->core_len, t->core_nbr);
+        e = agis::launch_core_pairs(ctx, g->g, g->max_deg, pair_hub, H, t->pair_count, t->pair_quart, C, d_rows,
+                                    t->core_slot, t->core_start, t->core_len, t->core_nbr);
     (void)hipStreamSynchronize(ctx->stream);
     ctx->pool->free(d_rows);
     if (e == hipSuccess) {
@@ -525,7 +525,7 @@ hipError_t build_hub_bitmaps(agis_ctx* ctx, const agis_graph* g, agis_tables* t)
     if (e == hipErrorOutOfMemory) return drop_out_of_memory();
     if (e == hipSuccess) e = hipMemsetAsync(t->hub_bits, 0, hubs * words * sizeof(uint32_t), ctx->stream);
     // (flags is free again: it takes the hubs by slot)
-    if (e == hipSuccess) e = agis::launch_hub_bits(g->g, t->hub_slot, hubs, flags, words, t->hub_bits, ctx->stream);
+    if (e == hipSuccess) e = agis::launch_hub_bits(ctx, g->g, g->max_deg, t->hub_slot, hubs, flags, words, t->hub_bits);
     if (e == hipSuccess) {
         t->hub_words = words;
         t->hubs = hubs;

@@ -1232,10 +1232,24 @@ __global__ __launch_bounds__(256) void k_hub_bits(DevGraph g, const uint32_t* __
 
 __global__ void k_pair_hubs(const int32_t* __restrict__ pair_slot, uint64_t n, uint32_t* __restrict__ hub);
 
-hipError_t launch_hub_bits(const DevGraph& g, const int32_t* hub_slot, uint64_t hubs, uint32_t* hub, uint64_t words,
-                           uint32_t* bits, hipStream_t stream) {
+// Slices of a row for a kernel with workgroups of 256 threads per hub and
+// slice: four, and where few hubs would leave the chip idle as many as give
+// every compute unit four workgroups, down to an element a thread.  With four
+// slices the bitmap of a single hub of 2.7M neighbours took 5.8 ms (0.14
+// now), and the tables of its graph 5.2 ms (1.2); from 256 hubs on four are
+// as fast.
+static unsigned hub_slices(const agis_ctx* ctx, uint64_t hubs, uint32_t max_deg) {
+    const uint64_t fill = ((uint64_t)ctx->num_cus * 4 + hubs - 1) / hubs;
+    return (unsigned)std::max<uint64_t>(4, std::min<uint64_t>(fill, ((uint64_t)max_deg + 255) / 256));
+}
+
+hipError_t launch_hub_bits(agis_ctx* ctx, const DevGraph& g, uint32_t max_deg, const int32_t* hub_slot, uint64_t hubs,
+                           uint32_t* hub, uint64_t words, uint32_t* bits) {
+    hipStream_t stream = ctx->stream;
     hipLaunchKernelGGL(k_pair_hubs, dim3(grid_for(g.n, 256)), dim3(256), 0, stream, hub_slot, g.n, hub);
-    if (hubs) hipLaunchKernelGGL(k_hub_bits, dim3((unsigned)hubs, 4), dim3(256), 0, stream, g, hub, words, bits);
+    if (hubs)
+        hipLaunchKernelGGL(k_hub_bits, dim3((unsigned)hubs, hub_slices(ctx, hubs, max_deg)), dim3(256), 0, stream, g,
+                           hub, words, bits);
     return hipGetLastError();
 }
 
@@ -1418,11 +1432,12 @@ static hipError_t alloc_rows(agis_ctx* ctx, const DevGraph& g, uint64_t hubs, ui
 }
 
 // The rows of the panel of hubs base .. base + hubs - 1.
-static hipError_t fill_rows(const DevGraph& g, const uint32_t* pair_hub, uint64_t base, uint64_t hubs, uint32_t lw,
-                            uint32_t* rows, hipStream_t st) {
-    const hipError_t e = hipMemsetAsync(rows, 0, g.n * lw * sizeof(uint32_t), st);
+static hipError_t fill_rows(agis_ctx* ctx, const DevGraph& g, uint32_t max_deg, const uint32_t* pair_hub,
+                            uint64_t base, uint64_t hubs, uint32_t lw, uint32_t* rows) {
+    const hipError_t e = hipMemsetAsync(rows, 0, g.n * lw * sizeof(uint32_t), ctx->stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_hub_rows, dim3((unsigned)hubs, 4), dim3(256), 0, st, g, pair_hub, base, lw, rows);
+    hipLaunchKernelGGL(k_hub_rows, dim3((unsigned)hubs, hub_slices(ctx, hubs, max_deg)), dim3(256), 0, ctx->stream, g,
+                       pair_hub, base, lw, rows);
     return hipGetLastError();
 }
 
@@ -1441,7 +1456,7 @@ hipError_t launch_pair_counts(agis_ctx* ctx, const DevGraph& g, uint32_t max_deg
         const bool small = max_deg / kPairParts + 1 < (1u << 16);
         const uint64_t panel = 32ull * lw;
         for (uint64_t base = 0; base + 1 < H && e == hipSuccess; base += panel) {
-            e = fill_rows(g, pair_hub, base, std::min<uint64_t>(panel, H - base), lw, rows, st);
+            e = fill_rows(ctx, g, max_deg, pair_hub, base, std::min<uint64_t>(panel, H - base), lw, rows);
             if (e != hipSuccess) break;
             const dim3 grid((unsigned)(H - base - 1));
             if (small)
@@ -1671,7 +1686,7 @@ hipError_t launch_core_rows(agis_ctx* ctx, const uint32_t* pair_count, uint64_t 
     return hipGetLastError();
 }
 
-hipError_t launch_core_pairs(agis_ctx* ctx, const DevGraph& g, const uint32_t* pair_hub, uint64_t H,
+hipError_t launch_core_pairs(agis_ctx* ctx, const DevGraph& g, uint32_t max_deg, const uint32_t* pair_hub, uint64_t H,
                              const uint32_t* pair_count, const uint32_t* pair_quart, uint64_t C,
                              const uint64_t* row_start, int32_t* core_slot, uint64_t* core_start, uint32_t* core_len,
                              uint32_t* core_nbr) {
@@ -1683,7 +1698,7 @@ hipError_t launch_core_pairs(agis_ctx* ctx, const DevGraph& g, const uint32_t* p
     hipError_t e = alloc_rows(ctx, g, C, &lw, &rows);
     const uint64_t panel = 32ull * lw;
     for (uint64_t base = 0; base + 1 < C && e == hipSuccess; base += panel) {
-        e = fill_rows(g, pair_hub, base, std::min<uint64_t>(panel, C - base), lw, rows, st);
+        e = fill_rows(ctx, g, max_deg, pair_hub, base, std::min<uint64_t>(panel, C - base), lw, rows);
         if (e != hipSuccess) break;
         hipLaunchKernelGGL(k_core_fill, dim3((unsigned)(C - base - 1), (lw + 15) / 16, kPairParts), dim3(256), 0, st,
                            g, rows, lw, pair_hub, H, base, pair_quart, C, core_start, core_nbr);
