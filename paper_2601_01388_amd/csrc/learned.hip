@@ -66,14 +66,16 @@ __device__ __forceinline__ float row_rotated(float x) {
 // concatenated list (element e belongs to the lane whose exclusive prefix
 // of degrees is the last one <= e), so the loads are independent; each such
 // lane then scans its histogram column from h = d down.  Vertices of degree
-// up to kWaveDeg go to the front of a list for k_features_wave, the others to
+// up to kWaveDeg go to the front of a list for features_by_wave, the others to
 // its back for k_features_big.
 //
-// k_features_wave: one wave per listed vertex holds the neighbour degrees in
+// features_by_wave: one wave per listed vertex holds the neighbour degrees in
 // registers (each is gathered once) and finds the h-index by bisection, a
-// count being one compare and one scalar bit count per 64 neighbours.
-// R-MAT-22 (4M vertices): 0.74 ms; with every vertex past kLaneDeg in
-// k_features_big, whose barriers then were most of the work, 3.9 ms.
+// count being one compare and one scalar bit count per 64 neighbours.  A
+// launch of its own where the largest degree is at most kWaveDeg, else the
+// end of k_features_big's.  R-MAT-22 (4M vertices): 0.92 ms with the rows of
+// up to kHubDeg (1.0 in two launches); with every vertex past kLaneDeg in
+// k_features_big, whose barriers then were most of the work, 3.8 ms.
 //
 // k_features_big: one workgroup per listed vertex narrows [lo, hi] (lo
 // always feasible) by histograms (a bucket a thread) of the degrees >= lo: bucket b
@@ -82,7 +84,7 @@ __device__ __forceinline__ float row_rotated(float x) {
 // >= lo + b w, and the feasible thresholds form a prefix of the buckets.
 // Three passes cover any degree below 2^24.  Workgroups of 256 take the rows
 // up to kHubDeg, of 1024 the others (one hub at a time holds up the kernel:
-// 1.58 ms with 256 threads for all, 0.25 + 0.44 so); kHeldPer neighbours per
+// 1.58 ms with 256 threads for all, 0.25 + 0.44 in two launches); kHeldPer neighbours per
 // thread stay in registers from one pass to the next, and longer rows are
 // read that many per thread at a time, so their loads overlap.
 // ---------------------------------------------------------------------------
@@ -209,13 +211,12 @@ __device__ __forceinline__ uint32_t wave_hindex(const uint4* __restrict__ rec, c
     return lo;
 }
 
-__global__ __launch_bounds__(kFeatThreads) void k_features_wave(DevGraph g, const uint4* __restrict__ rec,
-                                                                const uint64_t* __restrict__ s2,
-                                                                const uint64_t* __restrict__ hits,
-                                                                const uint64_t* __restrict__ trials,
-                                                                float* __restrict__ feats,
-                                                                const uint32_t* __restrict__ list,
-                                                                const uint32_t* __restrict__ nlist) {
+// The listed rows of up to kWaveDeg, a wave each.
+__device__ __forceinline__ void features_by_wave(const DevGraph& g, const uint4* __restrict__ rec,
+                                                 const uint64_t* __restrict__ s2, const uint64_t* __restrict__ hits,
+                                                 const uint64_t* __restrict__ trials, float* __restrict__ feats,
+                                                 const uint32_t* __restrict__ list,
+                                                 const uint32_t* __restrict__ nlist) {
     const uint32_t m = nlist[0];
     const uint32_t wave = blockIdx.x * kFeatWaves + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     for (uint32_t i = wave; i < m; i += gridDim.x * kFeatWaves) {
@@ -236,6 +237,15 @@ __global__ __launch_bounds__(kFeatThreads) void k_features_wave(DevGraph g, cons
             h = wave_hindex<16>(rec, row, d);
         if (lane_id() == 0) write_features(feats, v, d, s2[v], hits[v], trials[v], h);
     }
+}
+__global__ __launch_bounds__(kFeatThreads) void k_features_wave(DevGraph g, const uint4* __restrict__ rec,
+                                                                const uint64_t* __restrict__ s2,
+                                                                const uint64_t* __restrict__ hits,
+                                                                const uint64_t* __restrict__ trials,
+                                                                float* __restrict__ feats,
+                                                                const uint32_t* __restrict__ list,
+                                                                const uint32_t* __restrict__ nlist) {
+    features_by_wave(g, rec, s2, hits, trials, feats, list, nlist);
 }
 static_assert(kWaveDeg == 16 * kWave, "the widest row of k_features_wave");
 
@@ -330,6 +340,9 @@ __global__ __launch_bounds__(kThreads) void k_features_big(DevGraph g, const uin
         }
         if (t == 0) write_features(feats, v, d, s2[v], hits[v], trials[v], lo);
     }
+    // (in the same launch: one of their own costs a small graph, or one whose
+    // rows all are longer, 6 us: 36.7 instead of 31.6 on R-MAT-12)
+    if (kThreads == kFeatThreads) features_by_wave(g, rec, s2, hits, trials, feats, list, nlist);
 }
 
 // ---------------------------------------------------------------------------
@@ -1019,7 +1032,7 @@ int agis_features(agis_ctx* ctx, const agis_tables* t, float* feats) {
                            nlist, 0u, agis::kHubDeg);
         e = hipGetLastError();
     }
-    if (e == hipSuccess && dmax > agis::kLaneDeg) {
+    if (e == hipSuccess && dmax > agis::kLaneDeg && dmax <= agis::kWaveDeg) {
         hipLaunchKernelGGL(agis::k_features_wave, dim3((unsigned)ctx->num_cus * 8), dim3(agis::kFeatThreads), 0,
                            ctx->stream, g, t->rec, t->s2, t->hits, t->trials, feats, list, nlist);
         e = hipGetLastError();
