@@ -372,14 +372,15 @@ int agis_estimate_batch(agis_ctx* ctx, const agis_graph* g, const agis_tables* t
  * many as fit; each holds 16 KB of LDS, the weight decoder's table); grab = sample slots a wave takes from the queue at a time
  * (0 = chosen from the round size, at most 1024); variant = register
  * budget of the sampling kernel (0, 1 and 2 = small enough for 6, 7 and 8
- * resident waves per SIMD; a new context uses 2 for fixed-size runs, where
- * none of them spills and 2 is the fastest on R-MAT-20 -- the 5-cycle takes
- * 11.7 ms for 4M samples at 8 waves against 13.7 at 6, the 5-clique 42.3
- * against 45.3 -- and 0 for runs to epsilon);
+ * resident waves per SIMD; -1 = the launch's own, as in a new context: 2 for
+ * fixed-size runs, where none of them spills and 2 is the fastest on
+ * R-MAT-20 -- the 5-cycle takes 11.7 ms for 4M samples at 8 waves against
+ * 13.7 at 6, the 5-clique 42.3 against 45.3 -- and 0 for runs to epsilon);
  * hub_window: a high-degree vertex's neighbourhood bitmap (built with the
  * tables) replaces the merge with its list when the list is at least
  * hub_window / 64 times as long as the set it is intersected with (0 =
- * whenever there is a bitmap). */
+ * whenever there is a bitmap).  use_graphs 1, variant -1 and zeros give a new
+ * context's shape back. */
 int agis_set_launch(agis_ctx* ctx, int32_t use_graphs, int32_t blocks_per_cu, uint32_t grab, int32_t variant,
                     uint32_t hub_window);
 

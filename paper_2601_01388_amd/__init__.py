@@ -382,7 +382,7 @@ def agis_estimate_batch(ctx, g, t, patterns, budgets, seed: int, params: agis_ru
     return res
 
 
-def agis_set_launch(ctx, use_graphs: bool = True, blocks_per_cu: int = 0, grab: int = 0, variant: int = 0,
+def agis_set_launch(ctx, use_graphs: bool = True, blocks_per_cu: int = 0, grab: int = 0, variant: int = -1,
                     hub_window: int = 0):
     _check(ctx, lib().agis_set_launch(ctx, 1 if use_graphs else 0, blocks_per_cu, grab, variant, hub_window))
 

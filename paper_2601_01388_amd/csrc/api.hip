@@ -1899,7 +1899,7 @@ int agis_meter_samples(agis_ctx* ctx, const agis_graph* g, const agis_tables* t,
 
 int agis_set_launch(agis_ctx* ctx, int32_t use_graphs, int32_t blocks_per_cu, uint32_t grab, int32_t variant,
                     uint32_t hub_window) {
-    if (!ctx || blocks_per_cu < 0 || grab > 1024 || variant < 0 || variant > 2) return AGIS_E_INVALID_ARG;
+    if (!ctx || blocks_per_cu < 0 || grab > 1024 || variant < -1 || variant > 2) return AGIS_E_INVALID_ARG;
     ctx->use_graphs = use_graphs ? 1 : 0;
     ctx->tune_blocks_per_cu = blocks_per_cu;
     ctx->tune_grab = grab;

@@ -172,7 +172,9 @@ class Session:
         edges = [(p.k, [(a, b) for a in range(p.k) for b in range(a + 1, p.k) if p.adj[a] >> b & 1]) for p in pats]
         return {"patterns": edges, "results": res, "conc_edge": ce, "induced": ind, "conc_induced": ci}
 
-    def set_launch(self, use_graphs=True, blocks_per_cu=0, grab=0, variant=0, hub_window=0):
+    def set_launch(self, use_graphs=True, blocks_per_cu=0, grab=0, variant=-1, hub_window=0):
+        """Launch shape of later calls (agis_set_launch); without arguments that
+        of a new session."""
         agis_set_launch(self.ctx, use_graphs, blocks_per_cu, grab, variant, hub_window)
 
     def dump(self, graph: Graph, tables: Tables, pattern, seed: int, indices, order=None, **kw) -> np.ndarray:
