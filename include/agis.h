@@ -389,9 +389,9 @@ typedef struct {
     int32_t use_graphs;
     int32_t blocks_per_cu;
     uint32_t grab;
-    int32_t variant;
+    int32_t variant;         /* register budget of fixed-size runs, 0..2 */
     double seconds;          /* sampling-kernel time of the chosen configuration's pilot */
-    double default_seconds;  /* the same pilot under the default configuration */
+    double default_seconds;  /* the same pilot under a new context's register budget, grab 1 and no hub window */
     uint32_t hub_window;
     uint32_t reserved;
 } agis_tuning;
@@ -401,8 +401,10 @@ typedef struct {
  * launch configuration -- kernel register-budget variant (0, 1, 2) x queue
  * grab (1, 2, 4 slots), then the hub-bitmap window (256, 1024, 4096) --
  * and applies the fastest to the context (as agis_set_launch would); a
- * candidate must beat the best so far by 2% to be taken.  Results of later
- * calls do not depend on the choice. */
+ * candidate must beat the best so far by 2% to be taken, a new context's
+ * being the first.  Where the register budget chosen is a new context's own
+ * (2), it is applied as -1, so that runs to epsilon keep theirs.  Results of
+ * later calls do not depend on the choice. */
 int agis_autotune(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, uint32_t n_patterns,
                   const agis_pattern* patterns, uint64_t pilot_samples, const agis_run_params* params,
                   agis_tuning* out);

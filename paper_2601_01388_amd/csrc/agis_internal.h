@@ -276,6 +276,11 @@ hipError_t launch_fill_u32(uint32_t* a, uint64_t n, uint32_t v, hipStream_t stre
 // lists: 2 n + 2 uint32 of scratch (the lists of longer rows and their lengths).
 hipError_t launch_rowtab(agis_ctx* ctx, const DevGraph& g, const int32_t* sw, uint64_t* pre, uint32_t* lists);
 
+// A launch's own register budgets (see sample_kernel), unless the context has
+// one set.
+constexpr int kFixedVariant = 2;
+constexpr int kEpsVariant = 0;
+
 struct SampleLaunch {
     int blocks = 0;
     int threads = 256;

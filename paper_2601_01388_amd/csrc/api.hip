@@ -1930,9 +1930,11 @@ int agis_autotune(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, uint
     // first the register budget x queue grab, then the hub-bitmap window
     // with the best of those
     // explicit grabs (the automatic one depends on the round size, which
-    // differs between the pilots and the runs the tuning is for)
-    Cand cands[9 + 3] = {{0, 1, 0}, {1, 1, 0}, {2, 1, 0}, {0, 2, 0}, {1, 2, 0},
-                         {2, 2, 0}, {0, 4, 0}, {1, 4, 0}, {2, 4, 0}};
+    // differs between the pilots and the runs the tuning is for); the
+    // launch's own register budget (kFixedVariant) first, as the default
+    static_assert(agis::kFixedVariant == 2, "the budgets tried beside the launch's own");
+    Cand cands[9 + 3] = {{-1, 1, 0}, {0, 1, 0}, {1, 1, 0}, {-1, 2, 0}, {0, 2, 0},
+                         {1, 2, 0}, {-1, 4, 0}, {0, 4, 0}, {1, 4, 0}};
     double best = INFINITY, first = 0.0;
     Cand best_c = cands[0];
     auto time_config = [&](const Cand& c, double* secs) -> int {
@@ -1960,7 +1962,7 @@ int agis_autotune(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, uint
         if (rc != AGIS_OK) break;
         if (ci == 0) first = secs;
         // a candidate must beat the best so far by 2%: pilot times carry
-        // noise of about that size (the first candidate is the compiler's
+        // noise of about that size (the first candidate is the launch's own
         // register budget, grab 1, no hub window)
         if (secs < best * 0.98) {
             best = secs;
@@ -1976,7 +1978,7 @@ int agis_autotune(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, uint
     out->use_graphs = 1;
     out->blocks_per_cu = 0;
     out->grab = best_c.grab;
-    out->variant = best_c.variant;
+    out->variant = best_c.variant < 0 ? agis::kFixedVariant : best_c.variant;
     out->hub_window = best_c.window;
     out->seconds = best;
     out->default_seconds = first;

@@ -101,3 +101,22 @@ for bad in (-2, 3):
     else:
         raise AssertionError(bad)
 """)
+
+
+@pytest.mark.parametrize("times,fixed,eps,variant,default,best", [
+    # the default is the fastest, or within the 2% of the fastest
+    ((3.0, 2.9, 2.0), "ILi0ELi8E", "_epsILi6EL", 2, 2.0, 2.0),
+    ((1.99, 2.9, 2.0), "ILi0ELi8E", "_epsILi6EL", 2, 2.0, 2.0),
+    ((3.0, 1.0, 2.0), "ILi0ELi7E", "_epsILi7EL", 1, 2.0, 1.0),
+    ((1.0, 3.0, 2.0), "ILi0ELi6E", "_epsILi6EL", 0, 2.0, 1.0),
+])
+def test_autotune_starts_from_the_default_and_keeps_it_for_runs_to_epsilon(stand_in, times, fixed, eps, variant,
+                                                                           default, best):
+    run(stand_in, KERNELS + f"""
+for name, ms in zip((b"k_sampleILi0ELi6E", b"k_sampleILi0ELi7E", b"k_sampleILi0ELi8E"), {times}):
+    H.host_hip_time(name, ms)
+tun = A.agis_autotune(ctx, g, t, [TRI], 1000, A.make_params(mode="uniform"))
+assert tun.variant == {variant}, tun.variant
+assert abs(tun.default_seconds * 1e3 - {default}) < 1e-5 and abs(tun.seconds * 1e3 - {best}) < 1e-5
+assert kernels(ctx, g, t) == ({fixed!r}, {eps!r}), kernels(ctx, g, t)
+""")
