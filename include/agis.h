@@ -233,10 +233,11 @@ const char* agis_last_error(const agis_ctx* ctx);
  * [8, 64] GiB), the round weights and partials, and the run-to-eps
  * buffers.  For callers that allocate memory of their own between
  * estimates; the next estimate allocates what it needs again, with the
- * same results.  Also gives back the buffers (at most 8 GiB, none of them
- * kept while less than 128 GiB of device memory is free) that the context
- * keeps of destroyed tables, oriented graphs and finished calls for later
- * ones.  Waits for the context's stream and drops its captured
+ * same results.  Also gives back the buffers that the context keeps of
+ * destroyed tables, oriented graphs and finished calls for later ones: at
+ * most 8 GiB, and at most 64 MiB of them when a buffer comes back, or a call
+ * that takes such buffers begins, while less than 128 GiB of device memory is
+ * free.  Waits for the context's stream and drops its captured
  * launch graph.  Graphs, tables and their proposal-table caches are kept
  * (agis_tables_destroy frees those). */
 int agis_release_scratch(agis_ctx* ctx);

@@ -19,16 +19,18 @@ namespace agis {
 // that is given back before it hands it out again, at about 38 GB/s here
 // once the wiped pages have run out: a program that builds and destroys the
 // tables of R-MAT-20 (7.5 GB a time) is paced by that, 196 ms a build
-// against 18 ms of work.  Kept buffers are bounded (kPoolBudget), none are
-// kept while less than kPoolFreeFloor of device memory is free, an
-// allocation that fails gives them all back first, and so do
+// against 18 ms of work.  Kept buffers are bounded: kPoolBudget in all, and
+// no more than kPoolUnasked while less than kPoolFreeFloor of the device's
+// memory is free -- asked for when a buffer comes back and by check(), at the
+// start of the calls that allocate here, since others take memory too (asking
+// takes 5 us).  An allocation that fails gives them all back first, and so do
 // agis_release_scratch and agis_destroy.  Tables and graphs hold the pool
 // alive (they may outlive their context; it keeps nothing from then on).
 // Buffers come back only after the work that uses them has ended.
 constexpr size_t kPoolBudget = 8ull << 30;
 constexpr size_t kPoolFreeFloor = 128ull << 30;
-constexpr size_t kPoolMin = 1ull << 20;          // smaller buffers are not kept
-constexpr size_t kPoolFloorCheck = 64ull << 20;  // buffers of this size on ask for the free memory
+constexpr size_t kPoolMin = 1ull << 20;       // smaller buffers are not kept
+constexpr size_t kPoolUnasked = 64ull << 20;  // kept without a look at the free memory
 
 class DevPool {
   public:
@@ -39,9 +41,11 @@ class DevPool {
         return alloc((void**)p, bytes);
     }
     void free(void* p);
+    void check();  // gives the kept buffers back where too little memory is free
     void trim();   // gives every kept buffer back
     void close();  // trim, and keep nothing from now on
     size_t kept();
+    void set_device(int device) { device_ = device; }
 
   private:
     struct Buf {
@@ -52,7 +56,10 @@ class DevPool {
     std::vector<Buf> idle_;  // oldest first
     std::unordered_map<void*, size_t> live_;
     size_t idle_bytes_ = 0;
+    size_t unasked_ = 0;  // bytes kept since the free memory was last asked for
+    int device_ = 0;
     bool open_ = true;
+    bool room_locked();
     void trim_locked();
 };
 

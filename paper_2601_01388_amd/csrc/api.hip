@@ -56,6 +56,19 @@ hipError_t DevPool::alloc(void** p, size_t bytes) {
     return e;
 }
 
+// Whether kept buffers leave the device enough free memory (on the pool's
+// device, whichever the calling thread has current).
+bool DevPool::room_locked() {
+    int cur = device_;
+    (void)hipGetDevice(&cur);
+    if (cur != device_) (void)hipSetDevice(device_);
+    size_t free_b = 0, total_b = 0;
+    const bool room = hipMemGetInfo(&free_b, &total_b) == hipSuccess && free_b >= kPoolFreeFloor;
+    if (cur != device_) (void)hipSetDevice(cur);
+    unasked_ = 0;
+    return room;
+}
+
 void DevPool::free(void* p) {
     if (!p) return;
     std::lock_guard<std::mutex> lk(mu_);
@@ -63,9 +76,9 @@ void DevPool::free(void* p) {
     const size_t bytes = it == live_.end() ? 0 : it->second;
     if (it != live_.end()) live_.erase(it);
     bool keep = open_ && bytes >= kPoolMin && bytes <= kPoolBudget;
-    if (keep && bytes >= kPoolFloorCheck) {
-        size_t free_b = 0, total_b = 0;
-        keep = hipMemGetInfo(&free_b, &total_b) == hipSuccess && free_b >= kPoolFreeFloor;
+    if (keep && unasked_ + bytes > kPoolUnasked && !room_locked()) {
+        trim_locked();
+        keep = false;
     }
     if (!keep) {
         (void)hipFree(p);
@@ -78,12 +91,19 @@ void DevPool::free(void* p) {
     }
     idle_.push_back(Buf{p, bytes});
     idle_bytes_ += bytes;
+    unasked_ += bytes;
+}
+
+void DevPool::check() {
+    std::lock_guard<std::mutex> lk(mu_);
+    if (idle_bytes_ > kPoolUnasked && !room_locked()) trim_locked();
 }
 
 void DevPool::trim_locked() {
     for (const Buf& b : idle_) (void)hipFree(b.p);
     idle_.clear();
     idle_bytes_ = 0;
+    unasked_ = 0;
 }
 
 void DevPool::trim() {
@@ -1401,6 +1421,7 @@ int agis_create(agis_ctx** out, int device, void* hip_stream) {
     agis_ctx* ctx = new (std::nothrow) agis_ctx();
     if (!ctx) return AGIS_E_OOM;
     ctx->device = device;
+    ctx->pool->set_device(device);
     ctx->stream = (hipStream_t)hip_stream;
     hipError_t e = hipSetDevice(device);
     if (e == hipSuccess) {
@@ -1571,6 +1592,7 @@ int agis_orient(agis_ctx* ctx, const agis_graph* g, agis_graph** out) {
     *out = nullptr;
     if (g->parent) return fail(ctx, AGIS_E_INVALID_ARG, "the graph is already oriented");
     AGIS_HIP(ctx, hipSetDevice(ctx->device), "set device");
+    ctx->pool->check();
     const uint64_t n = g->g.n;
     agis_graph* o = new (std::nothrow) agis_graph();
     if (!o) return fail(ctx, AGIS_E_OOM, "host allocation");
@@ -1630,6 +1652,7 @@ int agis_build_proposal_tables(agis_ctx* ctx, const agis_graph* g, uint64_t cv_s
     *out = nullptr;
     if (lc_min_q16 > 0) return fail(ctx, AGIS_E_INVALID_ARG, "log2 of the clustering floor must be <= 0");
     AGIS_HIP(ctx, hipSetDevice(ctx->device), "set device");
+    ctx->pool->check();
     agis_tables* t = new (std::nothrow) agis_tables();
     if (t) t->cache = new (std::nothrow) TableCache();
     if (!t || !t->cache) {

@@ -1000,6 +1000,7 @@ int agis_mlp_param_count(void) { return kMlpParams; }
 int agis_features(agis_ctx* ctx, const agis_tables* t, float* feats) {
     if (!ctx || !t || t->ctx != ctx || !feats) return AGIS_E_INVALID_ARG;
     LHIP(ctx, hipSetDevice(ctx->device), "set device");
+    ctx->pool->check();
     const agis::DevGraph& g = t->graph->g;
     if (g.n == 0) return AGIS_OK;
     if (g.n > UINT32_MAX) return lfail(ctx, AGIS_E_INVALID_ARG, "features: more than 2^32 - 1 vertices");
@@ -1049,6 +1050,7 @@ int agis_learn_targets(agis_ctx* ctx, const agis_graph* g, const agis_tables* t,
     if (!ctx || !g || !t || !p || !sums || !counts) return AGIS_E_INVALID_ARG;
     if (p->k < 2 || p->k > 8) return lfail(ctx, AGIS_E_PATTERN, "pattern size must be in [2, 8]");
     LHIP(ctx, hipSetDevice(ctx->device), "set device");
+    ctx->pool->check();
     const uint64_t n = g->g.n;
     LHIP(ctx, hipMemsetAsync(sums, 0, (size_t)p->k * n * sizeof(double), ctx->stream), "clear sums");
     LHIP(ctx, hipMemsetAsync(counts, 0, (size_t)p->k * n * sizeof(uint32_t), ctx->stream), "clear counts");
@@ -1083,6 +1085,7 @@ int agis_learn_rows(agis_ctx* ctx, const double* sums, const uint32_t* counts, u
     if (!ctx || !sums || !counts || !vtx || !cls || !target || !weight || !rows || k == 0 || k > 8)
         return AGIS_E_INVALID_ARG;
     LHIP(ctx, hipSetDevice(ctx->device), "set device");
+    ctx->pool->check();
     *rows = 0;
     if (n == 0) return AGIS_OK;
     // (on the null stream: ordered with the work of every blocking stream, as
@@ -1118,6 +1121,7 @@ int agis_mlp_grad(agis_ctx* ctx, const float* params, const float* feats, const 
     if (!ctx || !params || !feats || !vtx || !cls || !target || !weight || !grad || rows == 0 || !(weight_sum > 0))
         return AGIS_E_INVALID_ARG;
     LHIP(ctx, hipSetDevice(ctx->device), "set device");
+    ctx->pool->check();
     const uint64_t slots = grad_tiles(rows);
     float* partial = nullptr;
     LHIP(ctx, ctx->pool->alloc(&partial, (size_t)slots * agis::kGradSlot * sizeof(float)), "allocate gradient partials");
@@ -1139,6 +1143,7 @@ int agis_mlp_train(agis_ctx* ctx, float* params, const float* feats, const uint3
         return AGIS_E_INVALID_ARG;
     if (rows >= (1ull << 32)) return lfail(ctx, AGIS_E_INVALID_ARG, "at most 2^32 - 1 rows");
     LHIP(ctx, hipSetDevice(ctx->device), "set device");
+    ctx->pool->check();
     const uint64_t bt = std::min<uint64_t>(batch, rows);
     const uint64_t most = grad_tiles(bt);
     std::vector<float> w(rows);

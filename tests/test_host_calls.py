@@ -120,3 +120,100 @@ assert tun.variant == {variant}, tun.variant
 assert abs(tun.default_seconds * 1e3 - {default}) < 1e-5 and abs(tun.seconds * 1e3 - {best}) < 1e-5
 assert kernels(ctx, g, t) == ({fixed!r}, {eps!r}), kernels(ctx, g, t)
 """)
+
+
+POOL = """
+MiB = 1 << 20
+
+def held():
+    return H.host_hip_live_bytes() - base
+
+ctx = A.agis_create(0, 0)
+base = H.host_hip_live_bytes()
+H.host_hip_free_memory(200 * GiB, 0)
+
+def tables(n, free_at_end):
+    g = graph(ctx, n)
+    t = A.agis_build_proposal_tables(ctx, g, 1, A.LC_MIN_DEFAULT, False)
+    H.host_hip_free_memory(free_at_end, 0)
+    A.agis_tables_destroy(t)
+    A.agis_graph_destroy(g)
+"""
+
+
+def test_kept_buffers_go_back_on_request(stand_in):
+    run(stand_in, POOL + """
+tables(8 << 20, 200 * GiB)   # 128 + 3 x 64 MiB
+kept = held()
+assert kept >= 320 * MiB, kept
+before = H.host_hip_mallocs()
+tables(8 << 20, 200 * GiB)   # from the kept buffers
+assert held() == kept and H.host_hip_mallocs() == before
+A.agis_release_scratch(ctx)
+assert held() == 0, held()
+tables(8 << 20, 200 * GiB)
+A.agis_destroy(ctx)
+assert H.host_hip_live_bytes() == 0
+""")
+
+
+@pytest.mark.parametrize("n,count", [(8 << 20, 1), (300_000, 40)])
+def test_no_more_than_64_mib_is_kept_where_memory_is_short(stand_in, n, count):
+    run(stand_in, POOL + f"""
+gs = [graph(ctx, {n}) for _ in range({count})]
+ts = [A.agis_build_proposal_tables(ctx, g, 1, A.LC_MIN_DEFAULT, False) for g in gs]
+assert held() > 300 * MiB
+H.host_hip_free_memory(100 * GiB, 0)
+for t in ts:
+    A.agis_tables_destroy(t)
+assert held() <= 64 * MiB, held()
+""")
+
+
+def test_kept_buffers_go_back_at_a_call_that_finds_memory_short(stand_in):
+    run(stand_in, POOL + """
+small = graph(ctx, 1000)
+t = A.agis_build_proposal_tables(ctx, small, 1, A.LC_MIN_DEFAULT, False)
+feats = np.zeros((1000, 4), dtype=np.float32)
+w = np.ones(4801, dtype=np.float32)
+row = np.zeros(4, dtype=np.uint32), np.zeros(4, dtype=np.uint8), np.zeros(4, dtype=np.float32), np.ones(4, dtype=np.float32)
+ptr = [x.ctypes.data for x in row]
+grad = np.zeros(4801, dtype=np.float32)
+sums, counts, base_ = np.zeros((3, 1000)), np.zeros((3, 1000), dtype=np.uint32), held()
+out = [np.zeros(3000, dtype=d) for d in (np.uint32, np.uint8, np.float32, np.float32)]
+calls = {
+    "tables": lambda: A.agis_tables_destroy(A.agis_build_proposal_tables(ctx, small, 1, A.LC_MIN_DEFAULT, False)),
+    "orient": lambda: A.agis_graph_destroy(A.agis_orient(ctx, small)),
+    "features": lambda: A.agis_features(ctx, t, feats.ctypes.data),
+    "targets": lambda: A.agis_learn_targets(ctx, small, t, TRI, 10, 1, A.make_params(), sums.ctypes.data, counts.ctypes.data),
+    "rows": lambda: A.agis_learn_rows(ctx, sums.ctypes.data, counts.ctypes.data, 3, 1000, 7, 2, *[o.ctypes.data for o in out]),
+    "grad": lambda: A.agis_mlp_grad(ctx, w.ctypes.data, feats.ctypes.data, *ptr, 4, 4.0, grad.ctypes.data, 0),
+    "train": lambda: A.agis_mlp_train(ctx, w.ctypes.data, feats.ctypes.data, *ptr, 4, 1, 4, 1e-3, 1),
+    "estimate": lambda: A.agis_estimate(ctx, small, t, TRI, 100, 1, A.make_params(mode="uniform")),
+}
+for name, call in calls.items():
+    H.host_hip_free_memory(200 * GiB, 0)
+    call()   # (what the call itself leaves with the context)
+    A.agis_release_scratch(ctx)
+    call()
+    after = held()
+    tables(8 << 20, 200 * GiB)
+    assert held() >= after + 300 * MiB, name
+    H.host_hip_free_memory(100 * GiB, 0)
+    call()
+    assert held() <= after + 64 * MiB, (name, held(), after)
+""")
+
+
+def test_free_memory_is_asked_of_the_contexts_device(stand_in):
+    run(stand_in, POOL + """
+g = graph(ctx, 8 << 20)
+t = A.agis_build_proposal_tables(ctx, g, 1, A.LC_MIN_DEFAULT, False)
+H.host_hip_current_device(3)
+asked = H.host_hip_memory_queries()
+A.agis_tables_destroy(t)
+assert H.host_hip_memory_queries() > asked and H.host_hip_queried_device() == 0
+d = ctypes.c_int(-1)
+H.hipGetDevice(ctypes.byref(d))
+assert d.value == 3
+""")
