@@ -26,7 +26,9 @@ namespace agis {
 // takes 5 us).  An allocation that fails gives them all back first, and so do
 // agis_release_scratch and agis_destroy.  Tables and graphs hold the pool
 // alive (they may outlive their context; it keeps nothing from then on).
-// Buffers come back only after the work that uses them has ended.
+// Buffers come back after the work that uses them has ended, or with it
+// ahead on the context's stream, where their later uses are too (work on
+// another stream waits for that stream first and is waited for after).
 constexpr size_t kPoolBudget = 8ull << 30;
 constexpr size_t kPoolFreeFloor = 128ull << 30;
 constexpr size_t kPoolMin = 1ull << 20;       // smaller buffers are not kept

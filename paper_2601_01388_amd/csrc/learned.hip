@@ -1110,6 +1110,8 @@ int agis_learn_rows(agis_ctx* ctx, const double* sums, const uint32_t* counts, u
     hipError_t e = hipGetLastError();
     uint64_t r = 0;
     if (e == hipSuccess) e = hipMemcpy(&r, d_first + all, sizeof(r), hipMemcpyDeviceToHost);
+    // (the next use of the buffer is on the context's stream)
+    if (e != hipSuccess) (void)hipStreamSynchronize(stream);
     ctx->pool->free(buf);
     LHIP(ctx, e, "training rows");
     *rows = r;

@@ -24,6 +24,7 @@ struct State {
     std::vector<std::string>* capture = nullptr;
     size_t live_bytes = 0, free_bytes = 200ull << 30;
     long long queries = 0, mallocs = 0, fail_malloc = 0, launches = 0, fail_launch = 0;
+    long long unwaited = 0;  // launches since the last wait
     int error = 0, device = 0, queried_device = -1;
     bool subtract = false;  // free memory falls with what is allocated
 };
@@ -32,6 +33,12 @@ State& S() {
     return *s;
 }
 long long g_new_until_fail = -1;  // operator new calls until one throws, -1: never
+thread_local int g_inside = 0;    // in this file: its own allocations never fail
+struct Inside {
+    Inside() { ++g_inside; }
+    ~Inside() { --g_inside; }
+};
+bool fails_now() { return g_inside == 0 && g_new_until_fail >= 0 && g_new_until_fail-- == 0; }
 int set(int e) {
     if (e) S().error = e;
     return e;
@@ -42,13 +49,13 @@ struct Dim3 {
 }  // namespace
 
 void* operator new(size_t n) {
-    if (g_new_until_fail >= 0 && g_new_until_fail-- == 0) throw std::bad_alloc();
+    if (fails_now()) throw std::bad_alloc();
     void* p = std::malloc(n ? n : 1);
     if (!p) throw std::bad_alloc();
     return p;
 }
 void* operator new(size_t n, const std::nothrow_t&) noexcept {
-    if (g_new_until_fail >= 0 && g_new_until_fail-- == 0) return nullptr;
+    if (fails_now()) return nullptr;
     return std::malloc(n ? n : 1);
 }
 void operator delete(void* p) noexcept { std::free(p); }
@@ -72,6 +79,7 @@ void host_hip_fail_malloc(long long n) { S().fail_malloc = n ? S().mallocs + n :
 void host_hip_fail_launch(long long n) { S().fail_launch = n ? S().launches + n : 0; }
 long long host_hip_mallocs() { return S().mallocs; }
 long long host_hip_launches() { return S().launches; }
+long long host_hip_unwaited() { return S().unwaited; }
 // launches whose name holds `part` take `ms`
 void host_hip_time(const char* part, float ms) { S().ms.emplace_back(part, ms); }
 // the launches since the last call, one name a line
@@ -103,6 +111,7 @@ int __hipPopCallConfiguration(Dim3* g, Dim3* b, size_t* sh, void** st) {
     return 0;
 }
 int hipLaunchKernel(const void* f, Dim3, Dim3, void**, size_t, void*) {
+    Inside inside;
     std::lock_guard<std::mutex> lk(S().mu);
     if (++S().launches == S().fail_launch) return set(719);
     const std::string& n = S().name[f];
@@ -111,10 +120,12 @@ int hipLaunchKernel(const void* f, Dim3, Dim3, void**, size_t, void*) {
         return 0;
     }
     S().log.push_back(n);
+    ++S().unwaited;
     if (n.find("k_sample") != std::string::npos) S().last = n;
     return 0;
 }
 int hipMalloc(void** p, size_t n) {
+    Inside inside;
     std::lock_guard<std::mutex> lk(S().mu);
     *p = nullptr;
     if (++S().mallocs == S().fail_malloc || (S().subtract && S().live_bytes + n > S().free_bytes)) return set(2);
@@ -124,6 +135,7 @@ int hipMalloc(void** p, size_t n) {
     return 0;
 }
 int hipFree(void* p) {
+    Inside inside;
     std::lock_guard<std::mutex> lk(S().mu);
     const auto it = S().live.find(p);
     if (!p) return 0;
@@ -141,6 +153,7 @@ int hipMemGetInfo(size_t* f, size_t* t) {
     return 0;
 }
 int hipMemcpy(void* d, const void* s, size_t n, int) {
+    S().unwaited = 0;
     std::memcpy(d, s, n);
     return 0;
 }
@@ -179,7 +192,10 @@ int hipSetDevice(int d) {
     S().device = d;
     return 0;
 }
-int hipDeviceSynchronize() { return 0; }
+int hipDeviceSynchronize() {
+    S().unwaited = 0;
+    return 0;
+}
 int hipDeviceGetAttribute(int* v, int, int) {
     *v = 100000;
     return 0;
@@ -206,7 +222,10 @@ int hipStreamDestroy(void* s) {
     std::free(s);
     return 0;
 }
-int hipStreamSynchronize(void*) { return 0; }
+int hipStreamSynchronize(void*) {
+    S().unwaited = 0;
+    return 0;
+}
 int hipStreamWaitEvent(void*, void*, unsigned) { return 0; }
 int hipEventCreate(void** e) {
     *e = std::malloc(1);
@@ -230,6 +249,7 @@ int hipEventElapsedTime(float* ms, void*, void*) {
     return 0;
 }
 int hipStreamBeginCapture(void*, int) {
+    Inside inside;
     S().capture = new std::vector<std::string>;
     return 0;
 }
@@ -239,10 +259,12 @@ int hipStreamEndCapture(void*, void** g) {
     return 0;
 }
 int hipGraphInstantiate(void** x, void* g, void*, char*, size_t) {
+    Inside inside;
     *x = new std::vector<std::string>(*(std::vector<std::string>*)g);
     return 0;
 }
 int hipGraphLaunch(void* x, void*) {
+    Inside inside;
     for (const std::string& n : *(std::vector<std::string>*)x) {
         S().log.push_back(n);
         if (n.find("k_sample") != std::string::npos) S().last = n;

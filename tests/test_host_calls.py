@@ -21,7 +21,7 @@ import paper_2601_01388_amd as A
 H = ctypes.CDLL({so!r})
 for f in ("host_hip_live_bytes", "host_hip_log"):
     getattr(H, f).restype = ctypes.c_size_t
-for f in ("host_hip_memory_queries", "host_hip_mallocs", "host_hip_launches", "host_hip_new_left"):
+for f in ("host_hip_memory_queries", "host_hip_mallocs", "host_hip_launches", "host_hip_unwaited", "host_hip_new_left"):
     getattr(H, f).restype = ctypes.c_longlong
 H.host_hip_free_memory.argtypes = [ctypes.c_size_t, ctypes.c_int]
 for f in ("host_hip_fail_malloc", "host_hip_fail_launch", "host_hip_fail_new"):
@@ -216,4 +216,23 @@ assert H.host_hip_memory_queries() > asked and H.host_hip_queried_device() == 0
 d = ctypes.c_int(-1)
 H.hipGetDevice(ctypes.byref(d))
 assert d.value == 3
+""")
+
+
+def test_training_rows_wait_for_their_stream_where_a_launch_fails(stand_in):
+    run(stand_in, POOL + """
+sums, counts = np.ones((3, 1000)), np.full((3, 1000), 5, dtype=np.uint32)
+out = [np.zeros(3000, dtype=d) for d in (np.uint32, np.uint8, np.float32, np.float32)]
+bp = np.zeros((3, 1000), dtype=np.int32)
+failed = 0
+for n in range(1, 5):
+    H.host_hip_fail_launch(n)
+    try:
+        A.agis_learn_rows(ctx, sums.ctypes.data, counts.ctypes.data, 3, 1000, 7, 2, *[o.ctypes.data for o in out],
+                          bp.ctypes.data)
+    except A.AgisError as e:
+        assert e.code == A.AGIS_E_HIP
+        failed += 1
+    assert H.host_hip_unwaited() == 0, n
+assert failed == 4
 """)
