@@ -62,6 +62,7 @@ class DevPool {
     int device_ = 0;
     bool open_ = true;
     bool room_locked();
+    void track_locked(void* p, size_t bytes) noexcept;
     void trim_locked();
 };
 
@@ -162,6 +163,13 @@ struct agis_tables {
 };
 
 namespace agis {
+
+// No C++ exception crosses the C boundary: an entry point whose host
+// allocations fail ends with AGIS_CATCH (a function-try-block), which reports
+// AGIS_E_OOM.  ctx may be null.
+int host_oom(agis_ctx* ctx) noexcept;
+#define AGIS_CATCH(ctx) \
+    catch (...) { return agis::host_oom(ctx); }
 
 // hipMalloc for the context's own buffers: a failed allocation gives the
 // pool's kept buffers back and tries once more.

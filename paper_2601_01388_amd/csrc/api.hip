@@ -41,7 +41,7 @@ hipError_t DevPool::alloc(void** p, size_t bytes) {
             const Buf b = idle_[best];
             idle_.erase(idle_.begin() + (std::ptrdiff_t)best);
             idle_bytes_ -= b.bytes;
-            live_[b.p] = b.bytes;
+            track_locked(b.p, b.bytes);
             *p = b.p;
             return hipSuccess;
         }
@@ -52,8 +52,16 @@ hipError_t DevPool::alloc(void** p, size_t bytes) {
         trim_locked();
         e = hipMalloc(p, bytes);
     }
-    if (e == hipSuccess && bytes >= kPoolMin) live_[*p] = bytes;
+    if (e == hipSuccess && bytes >= kPoolMin) track_locked(*p, bytes);
     return e;
+}
+
+// Notes a buffer handed out (one that cannot be noted is not kept later).
+void DevPool::track_locked(void* p, size_t bytes) noexcept {
+    try {
+        live_[p] = bytes;
+    } catch (...) {
+    }
 }
 
 // Whether kept buffers leave the device enough free memory (on the pool's
@@ -89,7 +97,12 @@ void DevPool::free(void* p) {
         idle_bytes_ -= idle_.front().bytes;
         idle_.erase(idle_.begin());
     }
-    idle_.push_back(Buf{p, bytes});
+    try {
+        idle_.push_back(Buf{p, bytes});
+    } catch (...) {  // (called from destructors)
+        (void)hipFree(p);
+        return;
+    }
     idle_bytes_ += bytes;
     unasked_ += bytes;
 }
@@ -120,6 +133,11 @@ void DevPool::close() {
 size_t DevPool::kept() {
     std::lock_guard<std::mutex> lk(mu_);
     return idle_bytes_;
+}
+
+int host_oom(agis_ctx* ctx) noexcept {
+    if (ctx) ctx->err.assign("host allocation");  // (fits a string's own storage)
+    return AGIS_E_OOM;
 }
 
 hipError_t ctx_malloc(agis_ctx* ctx, void** p, size_t bytes) {
@@ -381,15 +399,17 @@ struct StepTables {
             for (CacheEntry* c : held) --c->users;
         }
         if (arena || !ctx) return;
-        std::vector<void*> own;  // tables of this call alone
+        bool waited = false;
+        auto give_back = [&](void* b) {  // a table of this call alone
+            if (!waited) (void)hipStreamSynchronize(ctx->stream);
+            waited = true;
+            ctx->pool->free(b);
+        };
         for (Entry& x : e)
-            if (!x.cached) own.push_back(x.buf);
+            if (!x.cached) give_back(x.buf);
         for (RowEntry& x : rows)
-            if (!x.cached) own.push_back(x.buf);
-        if (long_rows && !cache) own.push_back(long_rows);
-        if (own.empty()) return;
-        (void)hipStreamSynchronize(ctx->stream);
-        for (void* b : own) ctx->pool->free(b);
+            if (!x.cached) give_back(x.buf);
+        if (long_rows && !cache) give_back(long_rows);
     }
 };
 constexpr uint64_t kStepTableBudgetBytes = 16ull << 30;
@@ -435,6 +455,7 @@ hipError_t build_core_pairs(agis_ctx* ctx, const agis_graph* g, agis_tables* t, 
     const uint64_t n = g->g.n;
     const uint64_t most = std::min<uint64_t>(H, kCoreMax);
     std::vector<uint64_t> rows(most), start;
+    start.reserve(most);
     uint64_t* d_rows = nullptr;
     hipError_t e = ctx->pool->alloc(&d_rows, most * sizeof(uint64_t));
     if (e == hipErrorOutOfMemory) {
@@ -1415,7 +1436,7 @@ int check_handles(const agis_ctx* ctx, const agis_graph* g, const agis_tables* t
 
 extern "C" {
 
-int agis_create(agis_ctx** out, int device, void* hip_stream) {
+int agis_create(agis_ctx** out, int device, void* hip_stream) try {
     if (!out) return AGIS_E_INVALID_ARG;
     *out = nullptr;
     agis_ctx* ctx = new (std::nothrow) agis_ctx();
@@ -1469,7 +1490,7 @@ int agis_create(agis_ctx** out, int device, void* hip_stream) {
     }
     *out = ctx;
     return AGIS_OK;
-}
+} AGIS_CATCH(nullptr)
 
 void agis_destroy(agis_ctx* ctx) {
     if (!ctx) return;
@@ -1494,7 +1515,7 @@ void agis_destroy(agis_ctx* ctx) {
     delete ctx;
 }
 
-int agis_release_scratch(agis_ctx* ctx) {
+int agis_release_scratch(agis_ctx* ctx) try {
     if (!ctx) return AGIS_E_INVALID_ARG;
     AGIS_HIP(ctx, hipSetDevice(ctx->device), "set device");
     AGIS_HIP(ctx, hipStreamSynchronize(ctx->stream), "wait for the context's stream");
@@ -1514,12 +1535,12 @@ int agis_release_scratch(agis_ctx* ctx) {
     ctx->eps_bytes = 0;
     ctx->pool->trim();
     return AGIS_OK;
-}
+} AGIS_CATCH(ctx)
 
 const char* agis_last_error(const agis_ctx* ctx) { return ctx ? ctx->err.c_str() : "null context"; }
 
 int agis_load_csr(agis_ctx* ctx, const uint64_t* off, const uint32_t* nbr, uint64_t n, uint64_t nnz, uint32_t flags,
-                  agis_graph** out) {
+                  agis_graph** out) try {
     if (!ctx || !out) return AGIS_E_INVALID_ARG;
     *out = nullptr;
     if (n == 0 || n >= (1ull << 32)) return fail(ctx, AGIS_E_INVALID_ARG, "n must be in [1, 2^32)");
@@ -1575,7 +1596,7 @@ int agis_load_csr(agis_ctx* ctx, const uint64_t* off, const uint32_t* nbr, uint6
     g->max_deg = cells[1];
     *out = g;
     return AGIS_OK;
-}
+} AGIS_CATCH(ctx)
 
 void agis_graph_destroy(agis_graph* g) {
     if (!g) return;
@@ -1587,7 +1608,7 @@ void agis_graph_destroy(agis_graph* g) {
     delete g;
 }
 
-int agis_orient(agis_ctx* ctx, const agis_graph* g, agis_graph** out) {
+int agis_orient(agis_ctx* ctx, const agis_graph* g, agis_graph** out) try {
     if (!ctx || !g || !out || g->ctx != ctx) return AGIS_E_INVALID_ARG;
     *out = nullptr;
     if (g->parent) return fail(ctx, AGIS_E_INVALID_ARG, "the graph is already oriented");
@@ -1634,7 +1655,7 @@ int agis_orient(agis_ctx* ctx, const agis_graph* g, agis_graph** out) {
     o->max_deg = maxd;
     *out = o;
     return AGIS_OK;
-}
+} AGIS_CATCH(ctx)
 
 int agis_graph_export(agis_ctx* ctx, const agis_graph* g, uint64_t* n, uint64_t* nnz, const uint64_t** off,
                       const uint32_t** nbr) {
@@ -1647,7 +1668,7 @@ int agis_graph_export(agis_ctx* ctx, const agis_graph* g, uint64_t* n, uint64_t*
 }
 
 int agis_build_proposal_tables(agis_ctx* ctx, const agis_graph* g, uint64_t cv_seed, int32_t lc_min_q16,
-                               int32_t exact_cv, agis_tables** out) {
+                               int32_t exact_cv, agis_tables** out) try {
     if (!ctx || !g || !out || g->ctx != ctx) return AGIS_E_INVALID_ARG;
     *out = nullptr;
     if (lc_min_q16 > 0) return fail(ctx, AGIS_E_INVALID_ARG, "log2 of the clustering floor must be <= 0");
@@ -1659,6 +1680,7 @@ int agis_build_proposal_tables(agis_ctx* ctx, const agis_graph* g, uint64_t cv_s
         delete t;
         return fail(ctx, AGIS_E_OOM, "host allocation");
     }
+    std::unique_ptr<agis_tables, void (*)(agis_tables*)> hold(t, agis_tables_destroy);
     t->ctx = ctx;
     t->pool = t->cache->pool = ctx->pool;
     t->device = ctx->device;
@@ -1674,13 +1696,10 @@ int agis_build_proposal_tables(agis_ctx* ctx, const agis_graph* g, uint64_t cv_s
         e = agis::launch_build_tables(ctx, g->g, g->parent ? g->parent->g : g->g, *t, (uint32_t)cv_seed,
                                       (uint32_t)(cv_seed >> 32), lc_min_q16, exact_cv ? 1 : 0);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    if (e != hipSuccess) {
-        agis_tables_destroy(t);
-        return hip_fail(ctx, e, "build proposal tables");
-    }
-    *out = t;
+    if (e != hipSuccess) return hip_fail(ctx, e, "build proposal tables");
+    *out = hold.release();
     return AGIS_OK;
-}
+} AGIS_CATCH(ctx)
 
 void agis_tables_destroy(agis_tables* t) {
     if (!t) return;
@@ -1694,7 +1713,7 @@ void agis_tables_destroy(agis_tables* t) {
 }
 
 int agis_tables_export(agis_ctx* ctx, const agis_tables* t, uint32_t* deg, uint64_t* s2, uint64_t* hits,
-                       uint64_t* trials, int32_t* la, int32_t* lc) {
+                       uint64_t* trials, int32_t* la, int32_t* lc) try {
     if (!ctx || !t || t->ctx != ctx) return AGIS_E_INVALID_ARG;
     AGIS_HIP(ctx, hipSetDevice(ctx->device), "set device");
     const uint64_t n = t->graph->g.n;
@@ -1705,17 +1724,17 @@ int agis_tables_export(agis_ctx* ctx, const agis_tables* t, uint32_t* deg, uint6
     AGIS_HIP(ctx, agis::launch_export_tables(*t, n, deg, la, lc, st), "export tables");
     AGIS_HIP(ctx, hipStreamSynchronize(st), "export tables");
     return AGIS_OK;
-}
+} AGIS_CATCH(ctx)
 
-int agis_compile_pattern(const agis_pattern* p, const uint8_t* order, const agis_run_params* params, agis_plan* out) {
+int agis_compile_pattern(const agis_pattern* p, const uint8_t* order, const agis_run_params* params, agis_plan* out) try {
     const agis_run_params dp = default_params();
     const agis_run_params* pp = params ? params : &dp;
     std::string err;
     return agis::compile_plan(p, order, pp->mode, pp->beta_num, pp->beta_den, out, &err);
-}
+} AGIS_CATCH(nullptr)
 
 int agis_step1_weights(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, const agis_pattern* p,
-                       const uint8_t* order, const agis_run_params* params, uint32_t* q1, uint64_t* total) {
+                       const uint8_t* order, const agis_run_params* params, uint32_t* q1, uint64_t* total) try {
     int rc = check_handles(ctx, g, t);
     if (rc != AGIS_OK) return ctx ? fail(ctx, rc, "bad handle") : rc;
     if (!p || !q1 || !total) return fail(ctx, AGIS_E_INVALID_ARG, "null pattern, weights or total");
@@ -1744,23 +1763,23 @@ int agis_step1_weights(agis_ctx* ctx, const agis_graph* g, const agis_tables* t,
     }
     AGIS_HIP(ctx, hipStreamSynchronize(ctx->stream), "first-step weights");
     return AGIS_OK;
-}
+} AGIS_CATCH(ctx)
 
-int agis_connected_patterns(uint32_t k, agis_pattern* out, uint32_t cap, uint32_t* count) {
+int agis_connected_patterns(uint32_t k, agis_pattern* out, uint32_t cap, uint32_t* count) try {
     if (!count) return AGIS_E_INVALID_ARG;
     std::string err;
     return agis::connected_patterns(k, out, cap, count, &err);
-}
+} AGIS_CATCH(nullptr)
 
 int agis_concentrations(uint32_t n_patterns, const agis_pattern* patterns, const double* copies, double* conc_edge,
-                        double* induced, double* conc_induced) {
+                        double* induced, double* conc_induced) try {
     std::string err;
     return agis::concentrations(n_patterns, patterns, copies, conc_edge, induced, conc_induced, &err);
-}
+} AGIS_CATCH(nullptr)
 
 int agis_estimate(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, const agis_pattern* p,
                   const uint8_t* order, uint64_t n_samples, uint64_t seed, const agis_run_params* params,
-                  agis_result* out) {
+                  agis_result* out) try {
     int rc = check_handles(ctx, g, t);
     if (rc != AGIS_OK) return ctx ? fail(ctx, rc, "bad handle") : rc;
     if (!p || !out) return fail(ctx, AGIS_E_INVALID_ARG, "null pattern or result");
@@ -1784,11 +1803,11 @@ int agis_estimate(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, cons
     if (cancelled) return fail(ctx, AGIS_E_CANCELLED, "cancelled by the caller");
     if (pp->eps > 0 && !runs[0].converged) return fail(ctx, AGIS_E_NOT_CONVERGED, "sample budget reached before eps");
     return AGIS_OK;
-}
+} AGIS_CATCH(ctx)
 
 int agis_estimate_noalloc(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, const agis_pattern* p,
                           const uint8_t* order, uint64_t n_samples, uint64_t seed, const agis_run_params* params,
-                          agis_result* out) {
+                          agis_result* out) try {
     int rc = check_handles(ctx, g, t);
     if (rc != AGIS_OK) return ctx ? fail(ctx, rc, "bad handle") : rc;
     if (!p || !out) return fail(ctx, AGIS_E_INVALID_ARG, "null pattern or result");
@@ -1818,11 +1837,11 @@ int agis_estimate_noalloc(agis_ctx* ctx, const agis_graph* g, const agis_tables*
     if (cancelled) return fail(ctx, AGIS_E_CANCELLED, "cancelled by the caller");
     if (pp->eps > 0 && !runs[0].converged) return fail(ctx, AGIS_E_NOT_CONVERGED, "sample budget reached before eps");
     return AGIS_OK;
-}
+} AGIS_CATCH(ctx)
 
 int agis_estimate_batch(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, uint32_t n_patterns,
                         const agis_pattern* patterns, const uint64_t* budgets, uint64_t seed,
-                        const agis_run_params* params, agis_result* out) {
+                        const agis_run_params* params, agis_result* out) try {
     int rc = check_handles(ctx, g, t);
     if (rc != AGIS_OK) return ctx ? fail(ctx, rc, "bad handle") : rc;
     if (n_patterns == 0 || n_patterns > agis::kMaxSegs) return fail(ctx, AGIS_E_INVALID_ARG, "1..64 patterns per batch");
@@ -1860,7 +1879,7 @@ int agis_estimate_batch(agis_ctx* ctx, const agis_graph* g, const agis_tables* t
     if (cancelled) return fail(ctx, AGIS_E_CANCELLED, "cancelled by the caller");
     if (pp->eps > 0 && !all) return fail(ctx, AGIS_E_NOT_CONVERGED, "a pattern reached its budget before eps");
     return AGIS_OK;
-}
+} AGIS_CATCH(ctx)
 
 // Runs the samples listed in idx (device uint64[m]) once: with `out` the
 // record-writing kernel writes one record each; with `meter` the metering
@@ -1908,17 +1927,17 @@ static int run_indexed(agis_ctx* ctx, const agis_graph* g, const agis_tables* t,
 
 int agis_dump_samples(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, const agis_pattern* p,
                       const uint8_t* order, uint64_t seed, const agis_run_params* params, const uint64_t* idx,
-                      uint64_t m, agis_record* out) {
+                      uint64_t m, agis_record* out) try {
     if (ctx && m > 0 && !out) return fail(ctx, AGIS_E_INVALID_ARG, "null output");
     return run_indexed(ctx, g, t, p, order, seed, params, idx, m, out, nullptr);
-}
+} AGIS_CATCH(ctx)
 
 int agis_meter_samples(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, const agis_pattern* p,
                        const uint8_t* order, uint64_t seed, const agis_run_params* params, const uint64_t* idx,
-                       uint64_t m, uint64_t* out) {
+                       uint64_t m, uint64_t* out) try {
     if (ctx && m > 0 && !out) return fail(ctx, AGIS_E_INVALID_ARG, "null output");
     return run_indexed(ctx, g, t, p, order, seed, params, idx, m, nullptr, out);
-}
+} AGIS_CATCH(ctx)
 
 int agis_set_launch(agis_ctx* ctx, int32_t use_graphs, int32_t blocks_per_cu, uint32_t grab, int32_t variant,
                     uint32_t hub_window) {
@@ -1933,7 +1952,7 @@ int agis_set_launch(agis_ctx* ctx, int32_t use_graphs, int32_t blocks_per_cu, ui
 
 int agis_autotune(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, uint32_t n_patterns,
                   const agis_pattern* patterns, uint64_t pilot_samples, const agis_run_params* params,
-                  agis_tuning* out) {
+                  agis_tuning* out) try {
     int rc = check_handles(ctx, g, t);
     if (rc != AGIS_OK) return ctx ? fail(ctx, rc, "bad handle") : rc;
     if (!patterns || !out || n_patterns == 0 || n_patterns > agis::kMaxSegs || pilot_samples == 0)
@@ -2006,7 +2025,7 @@ int agis_autotune(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, uint
     out->seconds = best;
     out->default_seconds = first;
     return agis_set_launch(ctx, 1, 0, best_c.grab, best_c.variant, best_c.window);
-}
+} AGIS_CATCH(ctx)
 
 int agis_fixed_point_tables(int32_t* logtab, uint32_t* exp2tab) {
     if (!logtab || !exp2tab) return AGIS_E_INVALID_ARG;

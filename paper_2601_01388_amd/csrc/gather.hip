@@ -83,7 +83,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather(const unsigned char* 
 
 extern "C" int agis_gather_bench(agis_ctx* ctx, const void* buffer, uint64_t bytes, uint32_t seg_bytes,
                                  int32_t dependent, uint32_t waves_per_cu, uint32_t rounds, uint64_t seed,
-                                 void* sink, double* seconds, double* useful_bytes) {
+                                 void* sink, double* seconds, double* useful_bytes) try {
     if (!ctx) return AGIS_E_INVALID_ARG;
     if (!buffer || !sink || !seconds || !useful_bytes || rounds == 0 || waves_per_cu == 0 || waves_per_cu % 4 != 0 ||
         waves_per_cu > 32) {
@@ -132,4 +132,4 @@ extern "C" int agis_gather_bench(agis_ctx* ctx, const void* buffer, uint64_t byt
     *seconds = 1e-3 * (double)ms;
     *useful_bytes = (double)waves * 64.0 * (double)rounds * (double)bytes_per_lane_round;
     return AGIS_OK;
-}
+} AGIS_CATCH(ctx)

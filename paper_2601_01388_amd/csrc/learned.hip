@@ -979,6 +979,27 @@ int lfail(agis_ctx* ctx, int code, const std::string& msg) {
                          std::string(what) + ": " + hipGetErrorString(e_));                      \
     } while (0)
 
+// Buffers of one call, back in the context's pool on every way out of it
+// (after the work that uses them).
+template <int kCount>
+struct CallBuffers {
+    agis_ctx* ctx;
+    void* p[kCount] = {};
+    explicit CallBuffers(agis_ctx* c) : ctx(c) {}
+    CallBuffers(const CallBuffers&) = delete;
+    CallBuffers& operator=(const CallBuffers&) = delete;
+    ~CallBuffers() {
+        (void)hipStreamSynchronize(ctx->stream);
+        for (void* b : p) ctx->pool->free(b);
+    }
+    template <class T>
+    hipError_t take(int i, T** out, size_t bytes) {
+        const hipError_t e = ctx->pool->alloc(&p[i], bytes);
+        *out = (T*)p[i];
+        return e;
+    }
+};
+
 unsigned grid1(uint64_t n, unsigned t) { return (unsigned)((n + t - 1) / t); }
 
 uint64_t grad_tiles(uint64_t rows) { return (rows + agis::kTile - 1) / agis::kTile; }
@@ -997,7 +1018,7 @@ extern "C" {
 
 int agis_mlp_param_count(void) { return kMlpParams; }
 
-int agis_features(agis_ctx* ctx, const agis_tables* t, float* feats) {
+int agis_features(agis_ctx* ctx, const agis_tables* t, float* feats) try {
     if (!ctx || !t || t->ctx != ctx || !feats) return AGIS_E_INVALID_ARG;
     LHIP(ctx, hipSetDevice(ctx->device), "set device");
     ctx->pool->check();
@@ -1042,11 +1063,11 @@ int agis_features(agis_ctx* ctx, const agis_tables* t, float* feats) {
     ctx->pool->free(list);
     LHIP(ctx, e, "features");
     return AGIS_OK;
-}
+} AGIS_CATCH(ctx)
 
 int agis_learn_targets(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, const agis_pattern* p,
                        const uint8_t* order, uint64_t n_samples, uint64_t seed, const agis_run_params* params,
-                       double* sums, uint32_t* counts) {
+                       double* sums, uint32_t* counts) try {
     if (!ctx || !g || !t || !p || !sums || !counts) return AGIS_E_INVALID_ARG;
     if (p->k < 2 || p->k > 8) return lfail(ctx, AGIS_E_PATTERN, "pattern size must be in [2, 8]");
     LHIP(ctx, hipSetDevice(ctx->device), "set device");
@@ -1057,12 +1078,10 @@ int agis_learn_targets(agis_ctx* ctx, const agis_graph* g, const agis_tables* t,
     const uint64_t chunk = 1ull << 20;
     uint64_t* d_idx = nullptr;
     agis::Record* d_rec = nullptr;
-    LHIP(ctx, ctx->pool->alloc(&d_idx, chunk * sizeof(uint64_t)), "allocate indices");
-    hipError_t e = ctx->pool->alloc(&d_rec, chunk * sizeof(agis::Record));
-    if (e != hipSuccess) {
-        ctx->pool->free(d_idx);
-        return lfail(ctx, AGIS_E_OOM, "allocate records");
-    }
+    CallBuffers<2> buffers(ctx);
+    LHIP(ctx, buffers.take(0, &d_idx, chunk * sizeof(uint64_t)), "allocate indices");
+    hipError_t e = buffers.take(1, &d_rec, chunk * sizeof(agis::Record));
+    if (e != hipSuccess) return lfail(ctx, AGIS_E_OOM, "allocate records");
     int rc = AGIS_OK;
     for (uint64_t done = 0; done < n_samples && rc == AGIS_OK; done += chunk) {
         const uint64_t m = std::min(chunk, n_samples - done);
@@ -1074,14 +1093,12 @@ int agis_learn_targets(agis_ctx* ctx, const agis_graph* g, const agis_tables* t,
         e = hipStreamSynchronize(ctx->stream);
         if (e != hipSuccess) rc = lfail(ctx, AGIS_E_HIP, std::string("targets: ") + hipGetErrorString(e));
     }
-    ctx->pool->free(d_idx);
-    ctx->pool->free(d_rec);
     return rc;
-}
+} AGIS_CATCH(ctx)
 
 int agis_learn_rows(agis_ctx* ctx, const double* sums, const uint32_t* counts, uint32_t k, uint64_t n,
                     uint32_t step_mask, uint32_t min_count, const int32_t* base, uint32_t* vtx, uint8_t* cls,
-                    float* target, float* weight, uint64_t* rows) {
+                    float* target, float* weight, uint64_t* rows) try {
     if (!ctx || !sums || !counts || !vtx || !cls || !target || !weight || !rows || k == 0 || k > 8)
         return AGIS_E_INVALID_ARG;
     LHIP(ctx, hipSetDevice(ctx->device), "set device");
@@ -1116,10 +1133,10 @@ int agis_learn_rows(agis_ctx* ctx, const double* sums, const uint32_t* counts, u
     LHIP(ctx, e, "training rows");
     *rows = r;
     return AGIS_OK;
-}
+} AGIS_CATCH(ctx)
 
 int agis_mlp_grad(agis_ctx* ctx, const float* params, const float* feats, const uint32_t* vtx, const uint8_t* cls,
-                  const float* target, const float* weight, uint64_t rows, float weight_sum, float* grad, float* loss) {
+                  const float* target, const float* weight, uint64_t rows, float weight_sum, float* grad, float* loss) try {
     if (!ctx || !params || !feats || !vtx || !cls || !target || !weight || !grad || rows == 0 || !(weight_sum > 0))
         return AGIS_E_INVALID_ARG;
     LHIP(ctx, hipSetDevice(ctx->device), "set device");
@@ -1136,11 +1153,11 @@ int agis_mlp_grad(agis_ctx* ctx, const float* params, const float* feats, const 
     ctx->pool->free(partial);
     LHIP(ctx, e, "mlp gradient");
     return AGIS_OK;
-}
+} AGIS_CATCH(ctx)
 
 int agis_mlp_train(agis_ctx* ctx, float* params, const float* feats, const uint32_t* vtx, const uint8_t* cls,
                    const float* target, const float* weight, uint64_t rows, uint32_t epochs, uint32_t batch,
-                   float lr, uint64_t shuffle_seed, float* loss_per_epoch) {
+                   float lr, uint64_t shuffle_seed, float* loss_per_epoch) try {
     if (!ctx || !params || !feats || !vtx || !cls || !target || !weight || rows == 0 || batch == 0)
         return AGIS_E_INVALID_ARG;
     if (rows >= (1ull << 32)) return lfail(ctx, AGIS_E_INVALID_ARG, "at most 2^32 - 1 rows");
@@ -1155,16 +1172,25 @@ int agis_mlp_train(agis_ctx* ctx, float* params, const float* feats, const uint3
     constexpr size_t kLossSteps = 4096;
     float *partial = nullptr, *m1 = nullptr, *m2 = nullptr, *loss = nullptr;
     uint32_t* order = nullptr;
-    hipError_t e = ctx->pool->alloc(&partial, (size_t)most * agis::kGradSlot * sizeof(float));
-    if (e == hipSuccess) e = ctx->pool->alloc(&m1, kMlpParams * sizeof(float));
-    if (e == hipSuccess) e = ctx->pool->alloc(&m2, kMlpParams * sizeof(float));
-    if (e == hipSuccess && loss_per_epoch) e = ctx->pool->alloc(&loss, kLossSteps * sizeof(float));
-    if (e == hipSuccess) e = ctx->pool->alloc(&order, rows * sizeof(uint32_t));
+    // (host memory first, and on the way out last: the uploads read it)
+    std::vector<uint32_t> perm(rows), sent[2];
+    for (std::vector<uint32_t>& s : sent) s.reserve(rows);
+    struct Events {
+        hipEvent_t e[2] = {nullptr, nullptr};
+        ~Events() {
+            for (hipEvent_t ev : e)
+                if (ev) (void)hipEventDestroy(ev);
+        }
+    } copied;
+    CallBuffers<5> buffers(ctx);
+    hipError_t e = buffers.take(0, &partial, (size_t)most * agis::kGradSlot * sizeof(float));
+    if (e == hipSuccess) e = buffers.take(1, &m1, kMlpParams * sizeof(float));
+    if (e == hipSuccess) e = buffers.take(2, &m2, kMlpParams * sizeof(float));
+    if (e == hipSuccess && loss_per_epoch) e = buffers.take(3, &loss, kLossSteps * sizeof(float));
+    if (e == hipSuccess) e = buffers.take(4, &order, rows * sizeof(uint32_t));
     if (e == hipSuccess) e = hipMemsetAsync(m1, 0, kMlpParams * sizeof(float), ctx->stream);
     if (e == hipSuccess) e = hipMemsetAsync(m2, 0, kMlpParams * sizeof(float), ctx->stream);
-    std::vector<uint32_t> perm(rows), sent[2];
-    hipEvent_t copied[2] = {nullptr, nullptr};
-    for (hipEvent_t& ev : copied)
+    for (hipEvent_t& ev : copied.e)
         if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
     for (uint64_t i = 0; i < perm.size(); ++i) perm[i] = (uint32_t)i;
     std::mt19937_64 rng(shuffle_seed);
@@ -1201,11 +1227,11 @@ int agis_mlp_train(agis_ctx* ctx, float* params, const float* feats, const uint3
         // its copy
         std::vector<uint32_t>& src = sent[ep & 1u];
         std::shuffle(perm.begin(), perm.end(), rng);
-        if (ep >= 2) e = hipEventSynchronize(copied[ep & 1u]);
+        if (ep >= 2) e = hipEventSynchronize(copied.e[ep & 1u]);
         src = perm;
         if (e == hipSuccess)
             e = hipMemcpyAsync(order, src.data(), rows * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->stream);
-        if (e == hipSuccess) e = hipEventRecord(copied[ep & 1u], ctx->stream);
+        if (e == hipSuccess) e = hipEventRecord(copied.e[ep & 1u], ctx->stream);
         for (uint64_t s0 = 0; s0 < rows && e == hipSuccess; s0 += bt) {
             const uint64_t cnt = std::min(bt, rows - s0);
             double ws = whole ? wt : 0.0;
@@ -1229,25 +1255,21 @@ int agis_mlp_train(agis_ctx* ctx, float* params, const float* feats, const uint3
     const hipError_t es = hipStreamSynchronize(ctx->stream);
     if (e == hipSuccess) e = es;
     for (uint32_t ep = 0; loss_per_epoch && ep < epochs; ++ep) loss_per_epoch[ep] = (float)(ep_loss[ep] / wt);
-    for (void* q : {(void*)partial, (void*)m1, (void*)m2, (void*)loss, (void*)order})
-        ctx->pool->free(q);
-    for (hipEvent_t ev : copied)
-        if (ev) (void)hipEventDestroy(ev);
     LHIP(ctx, e, "mlp training");
     return AGIS_OK;
-}
+} AGIS_CATCH(ctx)
 
 int agis_step_log_weights(agis_ctx* ctx, const agis_tables* t, uint32_t b, uint32_t f1, uint32_t ie, uint32_t f2,
-                          int32_t* out) {
+                          int32_t* out) try {
     if (!ctx || !t || t->ctx != ctx || !out || b > 7 || f1 > 7 || ie > 7 || f2 > 64) return AGIS_E_INVALID_ARG;
     LHIP(ctx, hipSetDevice(ctx->device), "set device");
     LHIP(ctx, agis::launch_step_log_weights(*t, t->graph->g.n, b, f1, ie, f2, nullptr, out, ctx->stream), "step log weights");
     LHIP(ctx, hipStreamSynchronize(ctx->stream), "step log weights");
     return AGIS_OK;
-}
+} AGIS_CATCH(ctx)
 
 int agis_mlp_infer(agis_ctx* ctx, const float* params, const float* feats, uint64_t n, uint32_t position_class,
-                   const int32_t* base, float y_min, float y_max, int32_t* lt, float* y) {
+                   const int32_t* base, float y_min, float y_max, int32_t* lt, float* y) try {
     if (!ctx || !params || !feats || !lt || position_class > 3 || !(y_min <= y_max)) return AGIS_E_INVALID_ARG;
     LHIP(ctx, hipSetDevice(ctx->device), "set device");
     if (n == 0) return AGIS_OK;
@@ -1258,6 +1280,6 @@ int agis_mlp_infer(agis_ctx* ctx, const float* params, const float* feats, uint6
     LHIP(ctx, hipGetLastError(), "mlp inference");
     LHIP(ctx, hipStreamSynchronize(ctx->stream), "mlp inference");
     return AGIS_OK;
-}
+} AGIS_CATCH(ctx)
 
 }  // extern "C"

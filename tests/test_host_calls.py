@@ -236,3 +236,72 @@ for n in range(1, 5):
     assert H.host_hip_unwaited() == 0, n
 assert failed == 4
 """)
+
+
+CALLS = POOL + """
+n0 = 300_000
+g = graph(ctx, n0)
+t = A.agis_build_proposal_tables(ctx, g, 1, A.LC_MIN_DEFAULT, False)
+feats = np.zeros((n0, 4), dtype=np.float32)
+w = np.ones(4801, dtype=np.float32)
+R = 300_000
+row = np.zeros(R, dtype=np.uint32), np.zeros(R, dtype=np.uint8), np.zeros(R, dtype=np.float32), np.ones(R, dtype=np.float32)
+ptr = [x.ctypes.data for x in row]
+grad = np.zeros(4801, dtype=np.float32)
+sums, counts = np.zeros((3, n0)), np.zeros((3, n0), dtype=np.uint32)
+out = [np.zeros(3 * n0, dtype=d) for d in (np.uint32, np.uint8, np.float32, np.float32)]
+lt = np.zeros(n0, dtype=np.int32)
+idx, rec = np.arange(100, dtype=np.uint64), np.zeros(100 * A.RECORD_BYTES, dtype=np.uint8)
+mt, q1 = np.zeros(400, dtype=np.uint64), np.zeros(n0, dtype=np.uint32)
+H5 = A.make_pattern(5, [0b11010, 0b10101, 0b1010, 0b101, 0b11, 0, 0, 0])
+PR = dict(mode="always", rowtab="on")
+LE = dict(mode="learned", learned={i: lt.ctypes.data for i in range(5)}, rowtab="on")
+calls = {
+    "tables": lambda: A.agis_tables_destroy(A.agis_build_proposal_tables(ctx, g, 1, A.LC_MIN_DEFAULT, False)),
+    "orient": lambda: A.agis_graph_destroy(A.agis_orient(ctx, g)),
+    "features": lambda: A.agis_features(ctx, t, feats.ctypes.data),
+    "targets": lambda: A.agis_learn_targets(ctx, g, t, TRI, 10, 1, A.make_params(), sums.ctypes.data, counts.ctypes.data),
+    "rows": lambda: A.agis_learn_rows(ctx, sums.ctypes.data, counts.ctypes.data, 3, n0, 7, 2, *[o.ctypes.data for o in out]),
+    "grad": lambda: A.agis_mlp_grad(ctx, w.ctypes.data, feats.ctypes.data, *ptr, R, 4.0, grad.ctypes.data, 0),
+    "train": lambda: A.agis_mlp_train(ctx, w.ctypes.data, feats.ctypes.data, *ptr, R, 3, 100000, 1e-3, 1),
+    "estimate": lambda: A.agis_estimate(ctx, g, t, H5, 100000, 1, A.make_params(**PR)),
+    "blocked": lambda: A.agis_estimate(ctx, g, t, H5, 100000, 1, A.make_params(step1="blocks", **PR)),
+    "learned": lambda: A.agis_estimate(ctx, g, t, H5, 100000, 1, A.make_params(**LE)),
+    "eps": lambda: A.agis_estimate(ctx, g, t, H5, 100000, 1, A.make_params(eps=0.01, check_every=4096, **PR)),
+    "batch": lambda: A.agis_estimate_batch(ctx, g, t, [H5, TRI], [1000, 1000], 1, A.make_params(**PR)),
+    "dump": lambda: A.agis_dump_samples(ctx, g, t, H5, 1, A.make_params(**PR), idx.ctypes.data, 100, rec.ctypes.data),
+    "meter": lambda: A.agis_meter_samples(ctx, g, t, H5, 1, A.make_params(**PR), idx.ctypes.data, 100, mt.ctypes.data),
+    "step1": lambda: A.agis_step1_weights(ctx, g, t, H5, A.make_params(**PR), q1.ctypes.data),
+    "load": lambda: A.agis_graph_destroy(graph(ctx, 1000)),
+    "autotune": lambda: A.agis_autotune(ctx, g, t, [TRI, H5], 100, A.make_params(**PR)),
+    "patterns": lambda: A.agis_connected_patterns(5),
+    "compile": lambda: A.agis_compile_pattern(H5),
+    "concentrations": lambda: A.agis_concentrations([TRI, A.make_pattern(3, [6, 1, 1, 0, 0, 0, 0, 0])], [5.0, 9.0]),
+    "create": lambda: A.agis_destroy(A.agis_create(0, 0)),
+}
+"""
+
+
+def test_a_failed_host_allocation_is_a_code_and_no_exception(stand_in):
+    run(stand_in, CALLS + """
+for name, call in calls.items():
+    failed, n = 0, 0
+    while True:
+        A.agis_tables_destroy(t)   # (nothing cached)
+        t = A.agis_build_proposal_tables(ctx, g, 1, A.LC_MIN_DEFAULT, False)
+        H.host_hip_fail_new(n)
+        try:
+            call()
+            code = 0
+        except A.AgisError as e:
+            code = e.code
+        through = H.host_hip_new_left() >= 0
+        H.host_hip_fail_new(-1)
+        assert code in (0, A.AGIS_E_OOM, A.AGIS_E_NOT_CONVERGED), (name, n, code)
+        failed += code == A.AGIS_E_OOM
+        if through:
+            break
+        n += 1
+    call()   # the context still serves
+    print(name, n, failed, flush=True)
+""")
