@@ -376,7 +376,8 @@ int agis_estimate_batch(agis_ctx* ctx, const agis_graph* g, const agis_tables* t
  * resident waves per SIMD; -1 = the launch's own, as in a new context: 2 for
  * fixed-size runs, where none of them spills and 2 is the fastest on
  * R-MAT-20 -- the 5-cycle takes 11.7 ms for 4M samples at 8 waves against
- * 13.7 at 6, the 5-clique 42.3 against 45.3 -- and 0 for runs to epsilon);
+ * 13.7 at 6, the 5-clique 42.3 against 45.3 -- or 1 on graphs of more than
+ * 2^27 CSR slots, and 0 for runs to epsilon);
  * hub_window: a high-degree vertex's neighbourhood bitmap (built with the
  * tables) replaces the merge with its list when the list is at least
  * hub_window / 64 times as long as the set it is intersected with (0 =
@@ -403,8 +404,8 @@ typedef struct {
  * grab (1, 2, 4 slots), then the hub-bitmap window (256, 1024, 4096) --
  * and applies the fastest to the context (as agis_set_launch would); a
  * candidate must beat the best so far by 2% to be taken, a new context's
- * being the first.  Where the register budget chosen is a new context's own
- * (2), it is applied as -1, so that runs to epsilon keep theirs.  Results of
+ * being the first.  Where the register budget chosen is a new context's own,
+ * it is applied as -1, so that runs to epsilon keep theirs.  Results of
  * later calls do not depend on the choice. */
 int agis_autotune(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, uint32_t n_patterns,
                   const agis_pattern* patterns, uint64_t pilot_samples, const agis_run_params* params,

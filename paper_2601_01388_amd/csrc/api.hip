@@ -1973,10 +1973,11 @@ int agis_autotune(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, uint
     // with the best of those
     // explicit grabs (the automatic one depends on the round size, which
     // differs between the pilots and the runs the tuning is for); the
-    // launch's own register budget (kFixedVariant) first, as the default
-    static_assert(agis::kFixedVariant == 2, "the budgets tried beside the launch's own");
-    Cand cands[9 + 3] = {{-1, 1, 0}, {0, 1, 0}, {1, 1, 0}, {-1, 2, 0}, {0, 2, 0},
-                         {1, 2, 0}, {-1, 4, 0}, {0, 4, 0}, {1, 4, 0}};
+    // launch's own register budget (-1) first, as the default, then the others
+    const int own = agis::fixed_variant(g->g);
+    const int budgets_tried[3] = {-1, own == 0 ? 1 : 0, own == 2 ? 1 : 2};
+    Cand cands[9 + 3];
+    for (uint32_t i = 0; i < 9; ++i) cands[i] = Cand{budgets_tried[i % 3], 1u << (i / 3), 0};
     double best = INFINITY, first = 0.0;
     Cand best_c = cands[0];
     auto time_config = [&](const Cand& c, double* secs) -> int {
@@ -2020,7 +2021,7 @@ int agis_autotune(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, uint
     out->use_graphs = 1;
     out->blocks_per_cu = 0;
     out->grab = best_c.grab;
-    out->variant = best_c.variant < 0 ? agis::kFixedVariant : best_c.variant;
+    out->variant = best_c.variant < 0 ? own : best_c.variant;
     out->hub_window = best_c.window;
     out->seconds = best;
     out->default_seconds = first;

@@ -3941,11 +3941,7 @@ int plan_sample_launch(agis_ctx* ctx, const agis_graph& g, uint64_t max_slots, u
         const uint64_t q = (uint64_t)free_b / 2 + ctx->scratch_bytes / 2;
         budget = q < (8ull << 30) ? (8ull << 30) : (q > (64ull << 30) ? (64ull << 30) : q);
     }
-    // register budget: 8 waves per SIMD for fixed-size runs, 6 for runs to
-    // epsilon (a pass of 4M 5-cycle samples takes 11.7 ms at 8 and 13.7 at 6;
-    // a house to 1% takes 5.45 at 8 and 5.22 at 6, short runs 10 to 25% less
-    // at 6, the 5-vertex concentrations 53.3 at 8 and 54.3 at 6)
-    L->variant = ctx->tune_variant >= 0 ? ctx->tune_variant : (L->eps ? kEpsVariant : kFixedVariant);
+    L->variant = ctx->tune_variant >= 0 ? ctx->tune_variant : (L->eps ? kEpsVariant : fixed_variant(g.g));
     L->hub_window = ctx->tune_hub_window;
     int& cached = L->lanes ? ctx->lanes_blocks_per_cu : ctx->sample_blocks_per_cu[L->variant * 2 + (L->pairs ? 1 : 0)];
     if (cached == 0) {

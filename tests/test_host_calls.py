@@ -103,6 +103,17 @@ for bad in (-2, 3):
 """)
 
 
+@pytest.mark.parametrize("slots,kernel", [(1 << 27, "ILi0ELi8E"), ((1 << 27) + 2, "ILi0ELi7E")])
+def test_large_graphs_sample_at_seven_waves(stand_in, slots, kernel):
+    # (the neighbours are not read: no kernel runs)
+    run(stand_in, KERNELS + f"""
+off = np.array([0, {slots}, {slots}, {slots}], dtype=np.uint64)
+big = A.agis_load_csr(ctx, off.ctypes.data, off.ctypes.data, 3, {slots}, 0)
+tb = A.agis_build_proposal_tables(ctx, big, 1, A.LC_MIN_DEFAULT, False)
+assert kernels(ctx, big, tb) == ({kernel!r}, "_epsILi6EL"), kernels(ctx, big, tb)
+""")
+
+
 @pytest.mark.parametrize("times,fixed,eps,variant,default,best", [
     # the default is the fastest, or within the 2% of the fastest
     ((3.0, 2.9, 2.0), "ILi0ELi8E", "_epsILi6EL", 2, 2.0, 2.0),
