@@ -34,6 +34,9 @@ constexpr size_t kPoolFreeFloor = 128ull << 30;
 constexpr size_t kPoolMin = 1ull << 20;       // smaller buffers are not kept
 constexpr size_t kPoolUnasked = 64ull << 20;  // kept without a look at the free memory
 
+// Words of a vertex's membership row (see k_hub_rows) at most.
+constexpr uint32_t kPairRowWords = 64;
+
 class DevPool {
   public:
     ~DevPool() { trim(); }
@@ -88,6 +91,7 @@ struct agis_ctx {
     agis::LaunchDesc* d_launch = nullptr;  // the current round
     int sample_blocks_per_cu[6] = {0, 0, 0, 0, 0, 0};  // resident blocks per CU of each kernel (variant, pairs)
     int lanes_blocks_per_cu = 0;                       // the same for the lane sampler
+    uint32_t max_row_words = agis::kPairRowWords;  // widest membership rows of the pair hubs (tests narrow them)
     // launch tuning (0 = default): resident blocks per CU, slots per grab
     int tune_blocks_per_cu = 0;
     uint32_t tune_grab = 0;

@@ -1950,6 +1950,14 @@ int agis_set_launch(agis_ctx* ctx, int32_t use_graphs, int32_t blocks_per_cu, ui
     return AGIS_OK;
 }
 
+// For tests (not declared in the header): rows of at most `words` words (a
+// power of two up to 64), as where memory is short.
+__attribute__((visibility("default"))) int agis_internal_row_words(agis_ctx* ctx, uint32_t words) {
+    if (!ctx || words == 0 || words > agis::kPairRowWords || (words & (words - 1))) return AGIS_E_INVALID_ARG;
+    ctx->max_row_words = words;
+    return AGIS_OK;
+}
+
 int agis_autotune(agis_ctx* ctx, const agis_graph* g, const agis_tables* t, uint32_t n_patterns,
                   const agis_pattern* patterns, uint64_t pilot_samples, const agis_run_params* params,
                   agis_tuning* out) try {

@@ -1301,7 +1301,6 @@ __global__ __launch_bounds__(256) void k_pair_rank(DevGraph g, const uint32_t* _
 // all words is a run of consecutive hubs and the results are written as
 // whole lines.  A panel is counted for the lists of the hubs of larger slot
 // only: the longest lists (smallest slots) meet the fewest panels.
-constexpr uint32_t kPairRowWords = 64;
 constexpr int kPairThreads = kPairParts * kWave;
 // Scratch for the rows; narrower rows (more panels, the same row words in
 // all) where 256 bytes per vertex would pass it.
@@ -1418,7 +1417,7 @@ __global__ __launch_bounds__(kPairThreads) void k_pair_counts(DevGraph g, const 
 // The row scratch of panels over `hubs` hubs: *lw words per vertex, at most
 // kPairRowWords, fewer for few hubs or little memory.
 static hipError_t alloc_rows(agis_ctx* ctx, const DevGraph& g, uint64_t hubs, uint32_t* lw, uint32_t** rows) {
-    *lw = kPairRowWords;
+    *lw = ctx->max_row_words;
     while (*lw > 1 && 32ull * (*lw / 2) >= hubs) *lw /= 2;
     size_t free_b = 0, total_b = 0;
     uint64_t budget = kPairRowsBudget;
