@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <chrono>
 #include <memory>
 #include <mutex>
 #include <string>
@@ -23,7 +24,7 @@ namespace agis {
 // no more than kPoolUnasked while less than kPoolFreeFloor of the device's
 // memory is free -- asked for when a buffer comes back and by check(), at the
 // start of the calls that allocate here, since others take memory too (asking
-// takes 5 us).  An allocation that fails gives them all back first, and so do
+// takes 5 us, so check() asks once a millisecond at most).  An allocation that fails gives them all back first, and so do
 // agis_release_scratch and agis_destroy.  Tables and graphs hold the pool
 // alive (they may outlive their context; it keeps nothing from then on).
 // Buffers come back after the work that uses them has ended, or with it
@@ -62,6 +63,7 @@ class DevPool {
     std::unordered_map<void*, size_t> live_;
     size_t idle_bytes_ = 0;
     size_t unasked_ = 0;  // bytes kept since the free memory was last asked for
+    std::chrono::steady_clock::time_point asked_{};  // when the free memory was last asked for
     int device_ = 0;
     bool open_ = true;
     bool room_locked();

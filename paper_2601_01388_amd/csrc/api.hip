@@ -74,6 +74,7 @@ bool DevPool::room_locked() {
     const bool room = hipMemGetInfo(&free_b, &total_b) == hipSuccess && free_b >= kPoolFreeFloor;
     if (cur != device_) (void)hipSetDevice(cur);
     unasked_ = 0;
+    asked_ = std::chrono::steady_clock::now();
     return room;
 }
 
@@ -109,7 +110,9 @@ void DevPool::free(void* p) {
 
 void DevPool::check() {
     std::lock_guard<std::mutex> lk(mu_);
-    if (idle_bytes_ > kPoolUnasked && !room_locked()) trim_locked();
+    if (idle_bytes_ <= kPoolUnasked) return;
+    if (std::chrono::steady_clock::now() - asked_ < std::chrono::milliseconds(1)) return;
+    if (!room_locked()) trim_locked();
 }
 
 void DevPool::trim_locked() {

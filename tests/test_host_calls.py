@@ -14,7 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 
 PRELUDE = """
-import ctypes, sys
+import ctypes, sys, time
 sys.path.insert(0, {root!r})
 import numpy as np
 import paper_2601_01388_amd as A
@@ -211,6 +211,7 @@ for name, call in calls.items():
     tables(8 << 20, 200 * GiB)
     assert held() >= after + 300 * MiB, name
     H.host_hip_free_memory(100 * GiB, 0)
+    time.sleep(0.005)   # (asked once a millisecond at most)
     call()
     assert held() <= after + 64 * MiB, (name, held(), after)
 """)
