@@ -377,7 +377,7 @@ int agis_estimate_batch(agis_ctx* ctx, const agis_graph* g, const agis_tables* t
  * fixed-size runs, where none of them spills and 2 is the fastest on
  * R-MAT-20 -- the 5-cycle takes 11.7 ms for 4M samples at 8 waves against
  * 13.7 at 6, the 5-clique 42.3 against 45.3 -- or 1 on graphs of more than
- * 2^27 CSR slots, and 0 for runs to epsilon);
+ * 384 MiB of neighbour lists, and 0 for runs to epsilon);
  * hub_window: a high-degree vertex's neighbourhood bitmap (built with the
  * tables) replaces the merge with its list when the list is at least
  * hub_window / 64 times as long as the set it is intersected with (0 =

@@ -301,15 +301,16 @@ hipError_t launch_rowtab(agis_ctx* ctx, const DevGraph& g, const int32_t* sw, ui
 
 // A launch's own register budgets (see sample_kernel), unless the context has
 // one set.  Fixed-size runs: 8 waves per SIMD, and 7 on graphs whose neighbour
-// lists are more than twice the 256 MB of the last-level cache, where more
-// waves also mean more traffic to memory.  At 6, 7 and 8 waves: R-MAT-20 (126
-// MB) 5-clique 3.60, 3.43, 3.38 ms and 5-cycle 1.65, 1.52, 1.46; R-MAT-21 (265
-// MB) 5.82, 5.80, 5.83 and 2.93, 2.76, 2.75; R-MAT-22 (528 MB) 12.20, 12.42,
-// 12.60 and 4.34, 4.32, 4.37, a tailed triangle 4.95, 4.99, 5.08 and a diamond
-// 9.88, 9.30, 8.92; R-MAT-24 (2.1 GB) 20.1, 20.6, 21.1 and 8.56, 8.29, 8.29.
+// lists are more than one and a half times the 256 MB of the last-level
+// cache, where more waves also mean more traffic to memory.  At 6, 7 and 8
+// waves: R-MAT-20 (126 MB) 5-clique 3.60, 3.43, 3.38 ms and 5-cycle 1.65, 1.52,
+// 1.46; R-MAT-21 (254 MB) 5.82, 5.80, 5.83 and 2.93, 2.76, 2.75; R-MAT-22 (513
+// MB) 12.20, 12.42, 12.60 and 4.34, 4.32, 4.37, a tailed triangle 4.95, 4.99,
+// 5.08 and a diamond 9.88, 9.30, 8.92; R-MAT-24 (2.1 GB) 20.1, 20.6, 21.1 and
+// 8.56, 8.29, 8.29.
 // Runs to epsilon: 6 waves (a house to 1% takes 5.45 at 8 and 5.22 at 6, short
 // runs 10 to 25% less at 6).
-constexpr uint64_t kFewerWavesBytes = 512ull << 20;
+constexpr uint64_t kFewerWavesBytes = 384ull << 20;
 constexpr int kEpsVariant = 0;
 inline int fixed_variant(const DevGraph& g) { return g.nnz * sizeof(uint32_t) > kFewerWavesBytes ? 1 : 2; }
 

@@ -103,7 +103,7 @@ for bad in (-2, 3):
 """)
 
 
-@pytest.mark.parametrize("slots,kernel", [(1 << 27, "ILi0ELi8E"), ((1 << 27) + 2, "ILi0ELi7E")])
+@pytest.mark.parametrize("slots,kernel", [(96 << 20, "ILi0ELi8E"), ((96 << 20) + 2, "ILi0ELi7E")])
 def test_large_graphs_sample_at_seven_waves(stand_in, slots, kernel):
     # (the neighbours are not read: no kernel runs)
     run(stand_in, KERNELS + f"""
