@@ -1083,7 +1083,12 @@ def main():
     footprint = "128MiB" if hot_bytes <= (256 << 20) else "8GiB"
     gather_peak = None
     if not args.skip_gather:
-        wpc = 4 * (6 + (tuning["variant"] if tuning else 0))
+        # the register budget of the runs above: the tuned one, or the launch's
+        # own (8 waves per SIMD, 7 above 384 MiB of neighbour lists)
+        variant = tuning["variant"] if tuning else -1
+        if variant < 0:
+            variant = 1 if 4 * g.nnz > (384 << 20) else 2
+        wpc = 4 * (6 + variant)
         log(f"random-gather ceiling at {wpc} waves per CU")
         gather = gather_ceiling(sess, wpc)
         s_match = min(GATHER_SIZES, key=lambda s: abs(math.log2(s) - math.log2(max(bytes_per_segment, 1.0))))
