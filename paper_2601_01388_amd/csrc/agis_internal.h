@@ -24,9 +24,10 @@ namespace agis {
 // no more than kPoolUnasked while less than kPoolFreeFloor of the device's
 // memory is free -- asked for when a buffer comes back and by check(), at the
 // start of the calls that allocate here, since others take memory too (asking
-// takes 5 us, so check() asks once a millisecond at most).  An allocation that fails gives them all back first, and so do
-// agis_release_scratch and agis_destroy.  Tables and graphs hold the pool
-// alive (they may outlive their context; it keeps nothing from then on).
+// takes 5 us, so check() asks once a millisecond at most).  An allocation that
+// fails gives them all back first, and so do agis_release_scratch and
+// agis_destroy.  Tables and graphs hold the pool alive (they may outlive their
+// context; it keeps nothing from then on).
 // Buffers come back after the work that uses them has ended, or with it
 // ahead on the context's stream, where their later uses are too (work on
 // another stream waits for that stream first and is waited for after).

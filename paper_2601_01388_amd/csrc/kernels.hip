@@ -94,8 +94,9 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
 // A wave-uniform read of data that no kernel writes while this one runs (the
 // graph and its tables): through the scalar cache.  As a vector load it
 // would take 16 accesses of the first-level cache for its 64 equal
-// addresses, and those accesses are what the sampler runs at: one per cycle
-// (5-clique and 5-cycle on R-MAT-20).
+// addresses, and with such loads those accesses were what the sampler ran at:
+// one per cycle (5-clique and 5-cycle on R-MAT-20; 0.95 and 0.52 of one with
+// the reads below).
 template <class P>
 __device__ __forceinline__ auto sload(P p) {
     using T = decltype(p[0] + 0);
@@ -3122,13 +3123,16 @@ struct SlotQueue {
 // kernel carries none of that state.  kWavesPerEU:
 // register budget of the variant -- at least that many waves per SIMD must
 // fit (6, 7 and 8 waves: 80, 72 and 64 registers, none of them spilled to
-// memory); the autotuner picks the fastest.  The chains of dependent loads of
-// a sample bound it, and the access rate of the first-level cache (one
+// memory); the autotuner picks the fastest.  What bounds it depends on the
+// pattern.  R-MAT-20 5-cliques: the access rate of the first-level cache (one
 // 64-byte access a cycle and compute unit; 16 for a coalesced or uniform
-// 4-byte load, 64 for a gather), of which it uses 0.98 (R-MAT-20 5-cycle) and
-// 1.05 (5-clique): so wave-uniform reads go through the scalar cache, scans
-// through lane rotations, and 8 waves beat 6 (4M samples: 5-cycle 13.7 ->
-// 11.7 ms, 5-clique 45.3 -> 42.3).
+// 4-byte load, 64 for a gather), 0.95 of it used, and the traffic beyond L2,
+// 7.0 TB/s of it.  5-cycles: issue and the chains of dependent loads (scalar
+// units 0.77 and vector units 0.63 busy, 0.52 of the accesses, 5.2 TB/s).
+// 7-cycles on R-MAT-22: traffic beyond L2, 7.5 TB/s.  So wave-uniform reads go
+// through the scalar cache, scans through lane rotations, and 8 waves beat 6
+// (4M samples: 5-cycle 13.7 -> 11.7 ms, 5-clique 45.3 -> 42.3; 10.9 and 41.6
+// with what came after).
 template <int kMode, int kWavesPerEU, bool kPairs>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU)))
 void k_sample(const LaunchDesc* __restrict__ D) {
